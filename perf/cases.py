@@ -248,3 +248,101 @@ def run(state):
         bd.spcfg_mbr_decode(s["span_post"], s["lengths"], s["spans"], s["score"], s["scratch"])
         out.update(span_post=s["span_post"], span_label=s["span_label"], spans=s["spans"], score=s["score"])
     return out
+
+
+def exact(case, seed):
+    """What run() returns for these inputs, in 64 bits: plain torch over dense slices, one per span width.
+
+    Everything is in probability space.  Emissions are taken relative to their mean over the preterminals, token by
+    token, and a span's weight then falls off like a power of its width, which 64 bits hold without scaling.  Labels
+    and trees are whole numbers that ties may change: None.
+    """
+    if case["kind"] == "rules":
+        return _exact_rules(case, seed)
+    st = prepare(case, seed)
+    N, P, n_max = case["N"], case["P"], st["n_max"]
+    if case["B"] * n_max * n_max * (N + P) * 24 > 1e11:  # bytes of a chart and its adjoints: seconds of work, and room
+        return None
+    log_root, L, R, log_emit = [x.double() for x in st["inputs"]]
+    real = (torch.arange(n_max)[None, :] < torch.from_numpy(st["lengths"]).long()[:, None]).to(log_emit.device)
+    shift = torch.logsumexp(log_emit, -1) - math.log(P)  # [B, n_max]
+    leaf = torch.exp(log_emit - shift[:, :, None]) * real[:, :, None]
+    last = [(int(n), b) for b, n in enumerate(st["lengths"])]
+    # project a [B, spans, .] slice through the columns of a factor that its kind of child has
+    cols = lambda w: slice(N, N + P) if w == 1 else slice(0, N)
+    proj = lambda beta, X, w: torch.matmul(beta, X[..., cols(w)].transpose(-1, -2).contiguous())
+
+    beta, eta, zeta = {1: leaf}, {}, {}
+    for w in range(1, n_max + 1):
+        m = n_max - w + 1  # starts 0 .. m - 1
+        if w >= 2:
+            acc = torch.zeros(case["B"], m, N, dtype=torch.float64, device=leaf.device)
+            for k in range(1, w):
+                acc.addcmul_(eta[k][:, :m], zeta[w - k][:, k:k + m])
+            beta[w] = acc
+        if w < n_max:
+            eta[w], zeta[w] = proj(beta[w], L, w), proj(beta[w], R, w)
+    root = torch.exp(log_root)
+    root = root if case["per_sentence"] else root.expand(case["B"], N)
+    top = torch.stack([beta[n][b, 0] for n, b in last])
+    Z = (root * top).sum(-1)
+    logZ = torch.log(Z) + (shift * real).sum(-1)
+    if case["kind"] == "eval":
+        return logZ
+
+    grad_log_root = root * top / Z[:, None]
+    g_L, g_R = torch.zeros_like(L), torch.zeros_like(R)
+    zeros = lambda w: torch.zeros(case["B"], n_max - w + 1, N, dtype=torch.float64, device=leaf.device)
+    d_eta, d_zeta = {w: zeros(w) for w in eta}, {w: zeros(w) for w in zeta}
+    post = torch.zeros(case["B"], n_max, n_max, dtype=torch.float64, device=leaf.device)
+    for w in range(n_max, 0, -1):
+        m = n_max - w + 1
+        if w < n_max:
+            for d, g, X in ((d_eta[w], g_L, L), (d_zeta[w], g_R, R)):
+                if case["per_sentence"]:
+                    g[..., cols(w)] += torch.matmul(d.transpose(-1, -2).contiguous(), beta[w])
+                else:
+                    g[..., cols(w)] += d.reshape(-1, N).t() @ beta[w].reshape(-1, beta[w].shape[-1])
+            d_beta = torch.matmul(d_eta[w], L[..., cols(w)]) + torch.matmul(d_zeta[w], R[..., cols(w)])
+        else:
+            d_beta = zeros(w)
+        if w >= 2:
+            for n, b in last:
+                if n == w:
+                    d_beta[b, 0] += root[b] / Z[b]
+            post[:, torch.arange(m), torch.arange(w - 1, n_max)] = (beta[w] * d_beta).sum(-1)
+            for k in range(1, w):
+                d_eta[k][:, :m].addcmul_(d_beta, zeta[w - k][:, k:k + m])
+                d_zeta[w - k][:, k:k + m].addcmul_(d_beta, eta[k][:, :m])
+            del beta[w], d_beta
+    grad_log_emit = leaf * d_beta
+    out = dict(logZ=logZ, grad_L=g_L, grad_R=g_R,
+               grad_log_root=grad_log_root if case["per_sentence"] else grad_log_root.sum(0), grad_log_emit=grad_log_emit)
+    if case["kind"] == "parse":
+        best = {1: torch.zeros(case["B"], n_max, dtype=torch.float64, device=leaf.device)}
+        for w in range(2, n_max + 1):
+            m = n_max - w + 1
+            kids = torch.stack([best[k][:, :m] + best[w - k][:, k:k + m] for k in range(1, w)])
+            best[w] = post[:, torch.arange(m), torch.arange(w - 1, n_max)] + kids.amax(0)
+        score = torch.stack([best[n][b, 0] for n, b in last])
+        starts = torch.arange(n_max)
+        post[:, starts, starts] = real.double()  # words are in every tree
+        out.update(span_post=post, span_label=None, spans=None, score=score)
+    return out
+
+
+def _exact_rules(case, seed):
+    st = prepare(case, seed)
+    P, V = case["P"], case["V"]
+    real = st["tokens"] >= 0
+    tokens = st["tokens"].clamp_min(0).long()
+    root, L, R, emis = [st[k].double() for k in ("root_logits", "L_logits", "R_logits", "emis_logits")]
+    g_root, g_L, g_R, g_emit = [g.double() for g in st["grads"]]
+    log_root, L, R, table = torch.log_softmax(root, -1), torch.softmax(L, -1), torch.softmax(R, -1), torch.log_softmax(emis, -1)
+    back = lambda p, g: p * (g - (p * g).sum(-1, keepdim=True))
+    # token by token into the table's gradient (positions past a sentence's end carry nothing)
+    per_word = g_emit[real]  # [words, P]
+    d_table = torch.zeros(V, P, dtype=torch.float64, device=emis.device).index_add_(0, tokens[real], per_word).t()
+    return dict(log_root=log_root, L=L, R=R, log_emit=table.t()[tokens] * real[:, :, None],
+                grad_root=g_root - torch.exp(log_root) * g_root.sum(), grad_L=back(L, g_L), grad_R=back(R, g_R),
+                grad_emis=d_table - torch.exp(table) * per_word.sum(0)[:, None])
