@@ -356,6 +356,7 @@ void launch_gemm_nt(const NtArgs& a, hipStream_t st) {
     launch_gemm_nt(b, st);
     return;
   }
+  if (launch_gemm_short(a, st)) return;
   switch (a.epilogue) {
     case NT_EPI_ROWSCALE: launch_bm<NT_EPI_ROWSCALE>(a, st); break;
     case NT_EPI_MASKROWS: launch_bm<NT_EPI_MASKROWS>(a, st); break;

@@ -189,6 +189,7 @@ struct NtArgs {
 void launch_gemm_nt(const NtArgs& a, hipStream_t st);
 void launch_gemm_nt16(const NtArgs& a, hipStream_t st);  // bf16-operand variant (called through launch_gemm_nt)
 void launch_gemm_nt3(const NtArgs& a, hipStream_t st);   // pre-cut three-plane operands (called through launch_gemm_nt)
+bool launch_gemm_short(const NtArgs& a, hipStream_t st);  // few rows (called through launch_gemm_nt); false: not the faster kernel here, nothing launched
 bool gemm_nt_keep_parts(NtArgs& a);             // drops the parts of a launch that would not save work
 bool gemm_nt_reads_planes(const NtArgs& a);     // whether launch_gemm_nt will read the plane operands (A3 / Bm3)
 int gemm_nt_tiles(int rows, int cols);           // number of output tiles (= arrival counters needed)
