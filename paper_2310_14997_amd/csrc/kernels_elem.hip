@@ -386,6 +386,271 @@ __global__ void k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, i
   }
 }
 
+// ------------------------------------------------------------------------------------------ bands of widths
+// Most of the split-point sums of kBandW consecutive widths w0 .. w0 + kBandW - 1 in one pass, before the first of them
+// (forward), resp. before the last of them (reverse), is finished.  A launch per width reads two rows per term: span
+// (i, j) needs the rows eta(i, .) and zeta(., j), and no other span of its width shares one.  Spans of neighbouring
+// widths do: over a tile of kBandI starts x kBandW widths the sums are outer products
+//   forward          beta(i, j)      = sum_s eta(i, s) * zeta(s, j)            both children narrower than w0
+//   adjoint of eta   adj eta(i, j)   = sum_s adj beta(i, s) * zeta(j, s)       parents wider than the band
+//   adjoint of zeta  adj zeta(i, j)  = sum_s adj beta(s, j) * eta(s, i)        parents wider than the band
+// so for each s the wavefront loads 4 rows X(i, s) and 7 rows Y(s, j) and uses them for 16 terms: 0.69 rows a term
+// instead of 2.  The few terms that touch the band itself (at most 2 * (w - w0) forward, w0 + kBandW - 1 - w a side
+// in reverse) are left to the kernel of their width, which adds them to this partial sum; the partial sum lies in the row's
+// place in T (UV) with an exponent of its own (bexp).  Every term is scaled by an exact power of two against the largest
+// exponent of its own sum, as in the kernels of one width.
+// A workgroup is one tile; with enough of them its four wavefronts have 64 nonterminals each, with few of them (late
+// widths of small batches) they share 64 nonterminals, take every fourth group of four s and meet in LDS in wavefront
+// order.  blockIdx.x is the block of nonterminals: the XCD that a tile's neighbours run on is the same, and three of
+// their seven Y rows are shared in its L2.
+// Bound by reading rows (6-8 TB/s through the L2s at the large launches).  Split-point sums of a whole pass before and
+// after: B = 4, N = 1024, n <= 200: reverse 10.1 -> 6.2 ms, forward 5.6 -> 4.0 ms; B = 32, N = 4096, n = 40: 4.2 -> 2.7 and
+// 2.7 -> 1.8 ms.  kBandShare wavefronts per 64 nonterminals: at n = 200 the launches of the last widths fall from 62 us (four
+// wavefronts) to 25 us; above kBandMinWaves wavefronts in all a wavefront per 64 nonterminals is the faster form, because the
+// tables are built once for four blocks of nonterminals (60 against 85 us there).
+constexpr int kBandI = 4;
+constexpr int kBandQ = kBandI + kBandW - 1;  // ends of the tile's spans
+constexpr int kBandWaves = 4;    // wavefronts of a workgroup with 64 nonterminals each
+constexpr int kBandShare = 16;   // wavefronts of a workgroup that share 64 nonterminals
+constexpr int kBandMinWaves = 1536;
+enum { BAND_FWD = 0, BAND_ETA = 1, BAND_ZETA = 2 };
+
+// LDS words of the tables for S (a multiple of 4) values of s, and of the wavefronts' partial sums
+__host__ __device__ constexpr int band_words(int S) { return 3 * (kBandI + kBandQ) * S; }
+constexpr int kBandSumWords = kBandShare * kBandI * kBandW * 64;
+constexpr int band_threads(int KS) { return 64 * (KS > 1 ? KS : kBandWaves); }
+
+template <int ROLE, int KS>
+__device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np, int64_t S1, int stride, int n, int S_max,
+                                           const int32_t* __restrict__ rowtab, const float* __restrict__ HZ,
+                                           const float* __restrict__ BH, const int32_t* __restrict__ mexp,
+                                           const uint32_t* __restrict__ tmaxb, const int32_t* __restrict__ hmaxb,
+                                           const int32_t* __restrict__ zmaxb, const int32_t* __restrict__ uexp,
+                                           const uint32_t* __restrict__ umaxb, float* __restrict__ out, int64_t out_ld,
+                                           int64_t out_row0, int32_t* __restrict__ bexp, int32_t* lds, int32_t* s_m) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // KS == 1: every wavefront has 64 nonterminals of its own; KS > 1: KS of them share 64 and take turns in s
+  const int a = (KS > 1 ? (int)blockIdx.x : (int)blockIdx.x * kBandWaves + wave) * 64 + lane;
+  const int al = min(a, Np - 1);  // (a last workgroup may have wavefronts past the end: they load, and store nothing)
+  const int wt = w0 + kBandW;
+  // the values of s that some span of the tile uses
+  const int s_lo = ROLE == BAND_FWD ? i0 + 1 : (ROLE == BAND_ETA ? i0 + wt : 0);
+  const int s_hi = ROLE == BAND_FWD ? min(i0 + kBandI + w0 - 2, n - 1) : (ROLE == BAND_ETA ? n : i0 + kBandI - 2);
+  const int S = max(0, s_hi - s_lo + 1), S4 = (S + 3) & ~3;
+  int32_t* x_row = lds;                        // [kBandI][S_max] row of X
+  int32_t* x_max = x_row + kBandI * S_max;     // its exponent
+  int32_t* x_app = x_max + kBandI * S_max;     // its exponent as stored (without the shift of a projected half)
+  int32_t* y_row = x_app + kBandI * S_max;     // [kBandQ][S_max] row of Y
+  int32_t* y_exp = y_row + kBandQ * S_max;
+  float* y_sc = reinterpret_cast<float*>(y_exp + kBandQ * S_max);  // scale of its shift
+  // a row that has been written, for the entries that take no part (their coefficient is zero)
+  const int safe_hz = rowtab[B + b], safe_bh = rowtab[n * B + b];
+  // one row of the tables at a time per wavefront; `count` strides of 64 values of s together, so that their two dependent
+  // lookups (row, then its exponents) overlap
+  auto fill_x = [&](int p, int k0, auto count) {
+    constexpr int U = decltype(count)::value;
+    const int i = i0 + p;
+    int row[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = s_lo + k0 + 64 * u;
+      ok[u] = ROLE == BAND_FWD ? (s > i && s < i + w0 && s < n)
+                               : (ROLE == BAND_ETA ? (s >= i + wt && s <= n) : (s < i && i < n));
+      const int width = ROLE == BAND_ZETA ? i - s : s - i, start = ROLE == BAND_ZETA ? s : i;
+      row[u] = ok[u] ? row_of(rowtab, stride, B, width, b, start, n) : (ROLE == BAND_ETA ? safe_bh : safe_hz);
+    }
+    int em[U], ea[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (ROLE == BAND_ETA) {
+        em[u] = ea[u] = norm_exp(uexp[row[u]], umaxb[row[u]]);
+      } else {
+        em[u] = proj_exp(mexp[row[u]], tmaxb[row[u]], hmaxb[row[u]]);
+        ea[u] = em[u] == kExpZero ? kExpZero : em[u] - proj_shift(tmaxb[row[u]], hmaxb[row[u]]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u;
+      if (k >= S4) continue;
+      x_row[p * S_max + k] = row[u];
+      x_max[p * S_max + k] = ok[u] ? em[u] : kExpZero;
+      x_app[p * S_max + k] = ok[u] ? ea[u] : kExpZero;
+    }
+  };
+  auto fill_y = [&](int q, int k0, auto count) {
+    constexpr int U = decltype(count)::value;
+    const int j = i0 + w0 + q;
+    int row[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = s_lo + k0 + 64 * u;
+      // (an end j = 0 exists in the lowest band only, for its width 0, which is no span)
+      ok[u] = j <= n && (ROLE == BAND_FWD ? (s > j - w0 && s < j) : (ROLE == BAND_ETA ? (s > j && s <= n && j > 0) : (s <= j - wt)));
+      const int width = ROLE == BAND_ETA ? s - j : j - s, start = ROLE == BAND_ETA ? j : s;
+      row[u] = ok[u] ? row_of(rowtab, stride, B, width, b, start, n) : (ROLE == BAND_ZETA ? safe_bh : safe_hz);
+    }
+    int e[U];
+    float sc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (ROLE == BAND_ZETA) {
+        e[u] = norm_exp(uexp[row[u]], umaxb[row[u]]);
+        sc[u] = 1.0f;
+      } else {
+        e[u] = proj_exp(mexp[row[u]], tmaxb[row[u]], zmaxb[row[u]]);
+        sc[u] = pow2i(-proj_shift(tmaxb[row[u]], zmaxb[row[u]]));
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 64 * u;
+      if (k >= S4) continue;
+      y_row[q * S_max + k] = row[u];
+      y_exp[q * S_max + k] = ok[u] ? e[u] : kExpZero;
+      y_sc[q * S_max + k] = ok[u] ? sc[u] : 0.0f;
+    }
+  };
+  for (int pq = wave; pq < kBandI + kBandQ; pq += band_threads(KS) / 64) {
+    if (S4 <= 64) {
+      if (pq < kBandI) fill_x(pq, lane, std::integral_constant<int, 1>{});
+      else fill_y(pq - kBandI, lane, std::integral_constant<int, 1>{});
+    } else {
+      for (int k0 = lane; k0 < S4; k0 += 256) {
+        if (pq < kBandI) fill_x(pq, k0, std::integral_constant<int, 4>{});
+        else fill_y(pq - kBandI, k0, std::integral_constant<int, 4>{});
+      }
+    }
+  }
+  __syncthreads();
+  {  // largest exponent of every span's sum: sixteen threads a span
+    const int pair = (tid >> 4) % (kBandI * kBandW), p = pair / kBandW, q = p + pair % kBandW;
+    int m = kExpZero;
+    for (int k = tid & 15; k < S4; k += 16) m = max(m, add_exp(x_max[p * S_max + k], y_exp[q * S_max + k]));
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if ((tid & 15) == 0 && tid < 16 * kBandI * kBandW) s_m[pair] = m;
+  }
+  __syncthreads();
+
+  float acc[kBandI][kBandW];
+  int neg_m[kBandI][kBandW];
+#pragma unroll
+  for (int p = 0; p < kBandI; ++p)
+#pragma unroll
+    for (int d = 0; d < kBandW; ++d) {
+      acc[p][d] = 0.0f;
+      const int m = __builtin_amdgcn_readfirstlane(s_m[p * kBandW + d]);
+      neg_m[p][d] = m == kExpZero ? 0 : -m;
+    }
+  const int64_t ldx = ROLE == BAND_ETA ? Np : 2 * (int64_t)Np, ldy = ROLE == BAND_ZETA ? Np : 2 * (int64_t)Np;
+  const float* xb = ROLE == BAND_ETA ? BH : HZ;                              // eta is the first half of a row of HZ
+  const float* yb = ROLE == BAND_ZETA ? BH : HZ + Np;                        // zeta the second
+  const int64_t xs = ROLE == BAND_ETA ? S1 : 0, ys = ROLE == BAND_ZETA ? S1 : 0;  // BH starts at the rows of width 2
+  for (int k = KS > 1 ? wave * 4 : 0; k < S4; k += KS * 4) {
+    float x[kBandI][4], y[kBandQ][4];
+    int4 xa[kBandI], ye[kBandQ];
+#pragma unroll
+    for (int p = 0; p < kBandI; ++p) {
+      const int4 r = *reinterpret_cast<const int4*>(x_row + p * S_max + k);
+      xa[p] = *reinterpret_cast<const int4*>(x_app + p * S_max + k);
+      x[p][0] = (xb + (__builtin_amdgcn_readfirstlane(r.x) - xs) * ldx)[al];
+      x[p][1] = (xb + (__builtin_amdgcn_readfirstlane(r.y) - xs) * ldx)[al];
+      x[p][2] = (xb + (__builtin_amdgcn_readfirstlane(r.z) - xs) * ldx)[al];
+      x[p][3] = (xb + (__builtin_amdgcn_readfirstlane(r.w) - xs) * ldx)[al];
+    }
+#pragma unroll
+    for (int q = 0; q < kBandQ; ++q) {
+      const int4 r = *reinterpret_cast<const int4*>(y_row + q * S_max + k);
+      ye[q] = *reinterpret_cast<const int4*>(y_exp + q * S_max + k);
+      y[q][0] = (yb + (__builtin_amdgcn_readfirstlane(r.x) - ys) * ldy)[al];
+      y[q][1] = (yb + (__builtin_amdgcn_readfirstlane(r.y) - ys) * ldy)[al];
+      y[q][2] = (yb + (__builtin_amdgcn_readfirstlane(r.z) - ys) * ldy)[al];
+      y[q][3] = (yb + (__builtin_amdgcn_readfirstlane(r.w) - ys) * ldy)[al];
+    }
+#pragma unroll
+    for (int q = 0; q < kBandQ; ++q) {
+      const float4 sc = *reinterpret_cast<const float4*>(y_sc + q * S_max + k);
+      y[q][0] *= sc.x; y[q][1] *= sc.y; y[q][2] *= sc.z; y[q][3] *= sc.w;
+    }
+#pragma unroll
+    for (int p = 0; p < kBandI; ++p)
+#pragma unroll
+      for (int d = 0; d < kBandW; ++d) {
+        const int q = p + d;
+        acc[p][d] = fmaf(__builtin_amdgcn_ldexpf(x[p][0], xa[p].x + ye[q].x + neg_m[p][d]), y[q][0], acc[p][d]);
+        acc[p][d] = fmaf(__builtin_amdgcn_ldexpf(x[p][1], xa[p].y + ye[q].y + neg_m[p][d]), y[q][1], acc[p][d]);
+        acc[p][d] = fmaf(__builtin_amdgcn_ldexpf(x[p][2], xa[p].z + ye[q].z + neg_m[p][d]), y[q][2], acc[p][d]);
+        acc[p][d] = fmaf(__builtin_amdgcn_ldexpf(x[p][3], xa[p].w + ye[q].w + neg_m[p][d]), y[q][3], acc[p][d]);
+      }
+  }
+  if (KS > 1) {
+    __syncthreads();  // the tables have been read: their place holds the wavefronts' sums now
+    float* sum = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int p = 0; p < kBandI; ++p)
+#pragma unroll
+      for (int d = 0; d < kBandW; ++d) sum[((wave * kBandI + p) * kBandW + d) * 64 + lane] = acc[p][d];
+    __syncthreads();
+#pragma unroll
+    for (int pair = 0; pair < kBandI * kBandW; ++pair) {
+      if (pair % KS != wave) continue;  // each wavefront finishes its share of the spans
+      float t = 0.0f;
+#pragma unroll
+      for (int q = 0; q < KS; ++q) t += sum[(q * kBandI * kBandW + pair) * 64 + lane];
+      acc[pair / kBandW][pair % kBandW] = t;
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < kBandI; ++p)
+#pragma unroll
+    for (int d = 0; d < kBandW; ++d) {
+      const int i = i0 + p, w = w0 + d;
+      if (KS > 1 && (p * kBandW + d) % KS != wave) continue;
+      // no such span (the lowest band's width 0 among them); the root span has no parents
+      if (w == 0 || i + w > n || (ROLE != BAND_FWD && w == n)) continue;
+      const int r = row_of(rowtab, stride, B, w, b, i, n);
+      if (a < Np) out[(r - out_row0) * out_ld + a] = acc[p][d];
+      if (blockIdx.x == 0 && lane == 0 && (KS > 1 || wave == 0)) bexp[r] = s_m[p * kBandW + d];
+    }
+}
+
+template <int KS>
+__global__ void __launch_bounds__(band_threads(KS))
+k_split_band_fwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const int32_t* __restrict__ lens,
+                 const int32_t* __restrict__ rowtab, const float* __restrict__ HZ, const int32_t* __restrict__ mexp,
+                 const uint32_t* __restrict__ tmaxb, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb,
+                 float* __restrict__ T, int32_t* __restrict__ bexp) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int32_t s_m[kBandI * kBandW];
+  const int b = blockIdx.z, n = lens[b], i0 = blockIdx.y * kBandI;
+  if (i0 + w0 > n) return;
+  split_band<BAND_FWD, KS>(w0, b, i0, B, Np, S1, stride, n, S_max, rowtab, HZ, nullptr, mexp,
+                       tmaxb, hmaxb, zmaxb, nullptr, nullptr, T, Np, S1, bexp, reinterpret_cast<int32_t*>(smem), s_m);
+}
+
+// blockIdx.z: sentence, and which of the two adjoints
+template <int KS>
+__global__ void __launch_bounds__(band_threads(KS))
+k_split_band_bwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const int32_t* __restrict__ lens,
+                 const int32_t* __restrict__ rowtab, const float* __restrict__ HZ, const float* __restrict__ BH,
+                 const int32_t* __restrict__ mexp, const uint32_t* __restrict__ tmaxb, const int32_t* __restrict__ hmaxb,
+                 const int32_t* __restrict__ zmaxb, const int32_t* __restrict__ uexp, const uint32_t* __restrict__ umaxb,
+                 float* __restrict__ UV, int32_t* __restrict__ bexp, int64_t Sall) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int32_t s_m[kBandI * kBandW];
+  const int b = blockIdx.z >> 1, n = lens[b], i0 = blockIdx.y * kBandI;
+  if (i0 + w0 > n) return;
+  if ((blockIdx.z & 1) == 0)
+    split_band<BAND_ETA, KS>(w0, b, i0, B, Np, S1, stride, n, S_max, rowtab, HZ, BH, mexp, tmaxb, hmaxb, zmaxb, uexp, umaxb, UV,
+                         2 * (int64_t)Np, 0, bexp, reinterpret_cast<int32_t*>(smem), s_m);
+  else
+    split_band<BAND_ZETA, KS>(w0, b, i0, B, Np, S1, stride, n, S_max, rowtab, HZ, BH, mexp, tmaxb, hmaxb, zmaxb, uexp, umaxb,
+                          UV + Np, 2 * (int64_t)Np, 0, bexp + Sall, reinterpret_cast<int32_t*>(smem), s_m);
+}
+
 // ------------------------------------------------------------------------------------------ forward split
 // beta_ij = sum_k eta_ik * zeta_kj (Sec. 3.1 vector form) for every span of one width, in the scaled
 // representation: T = sum_k 2^(d_k - m) etat_ik * zetat_kj with d_k = e_ik + e_kj, m = max_k d_k.
@@ -405,32 +670,36 @@ k_split_fwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
             const int32_t* __restrict__ row_i, const float* __restrict__ HZ,
             float* __restrict__ T, int32_t* __restrict__ mexp, uint32_t* __restrict__ tmaxb, void* __restrict__ Tb,
             int planes, int64_t plane_stride, int32_t* __restrict__ hmaxb, int32_t* __restrict__ zmaxb,
-            const float* __restrict__ colmax, int Pp, int per_sentence) {
+            const float* __restrict__ colmax, int Pp, int per_sentence, int w0, const int32_t* __restrict__ bexp) {
   extern __shared__ __align__(16) unsigned char smem[];
-  float* s_c = reinterpret_cast<float*>(smem);                 // [w-1] coefficient of the left child's eta
-  float* s_cz = s_c + (w - 1);                                 // [w-1] coefficient of the right child's zeta
-  int32_t* s_l = reinterpret_cast<int32_t*>(s_cz + (w - 1));   // [w-1] row of the left child
-  int32_t* s_r = s_l + (w - 1);                                // [w-1] row of the right child
+  // split points of this launch: all w - 1, or (w0 > 0) those with a child of width w0 or more, the rest lies summed in T
+  const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
+  float* s_c = reinterpret_cast<float*>(smem);             // [nk] coefficient of the left child's eta
+  float* s_cz = s_c + nk;                                  // [nk] coefficient of the right child's zeta
+  int32_t* s_l = reinterpret_cast<int32_t*>(s_cz + nk);    // [nk] row of the left child
+  int32_t* s_r = s_l + nk;                                 // [nk] row of the right child
   const int lane = threadIdx.x;
   const int64_t r = row0 + blockIdx.x;
   const int b = row_b[r], i = row_i[r];
   const int n = lens[b];
-  int dmax = kExpZero;
-  for (int k = 1 + lane; k < w; k += 64) {
+  const int pe = w0 > 0 ? bexp[r] : kExpZero;
+  int dmax = pe;
+  for (int t = lane; t < nk; t += 64) {
+    const int k = (w0 > 0 && t >= w - w0) ? t + 2 * w0 - w : t + 1;
     const int lr = row_of(rowtab, stride, B, k, b, i, n);          // span (i, i+k)
     const int rr = row_of(rowtab, stride, B, w - k, b, i + k, n);  // span (i+k, i+w)
-    s_l[k - 1] = lr;
-    s_r[k - 1] = rr;
+    s_l[t] = lr;
+    s_r[t] = rr;
     const int d = add_exp(proj_exp(mexp[lr], tmaxb[lr], hmaxb[lr]), proj_exp(mexp[rr], tmaxb[rr], zmaxb[rr]));
-    s_c[k - 1] = __int_as_float(d);
-    s_cz[k - 1] = __int_as_float(proj_shift(tmaxb[lr], hmaxb[lr]));  // eta's shift, used once m is known
+    s_c[t] = __int_as_float(d);
+    s_cz[t] = __int_as_float(proj_shift(tmaxb[lr], hmaxb[lr]));  // eta's shift, used once m is known
     dmax = max(dmax, d);
   }
   const int m = wave_max_i(dmax);
   __syncthreads();
   // the term of split point k is 2^(d_k - m) * (2^-gh eta) * (2^-gz zeta): the first two factors go with eta
   // (coefficient 2^(d_k - m - gh)), the last with zeta (coefficient 2^-gz); both products stay at or below 1
-  for (int k = lane; k < w - 1; k += 64) {
+  for (int k = lane; k < nk; k += 64) {
     const int d = __float_as_int(s_c[k]);
     const int gh = __float_as_int(s_cz[k]);
     s_c[k] = (d == kExpZero) ? 0.0f : pow2i(d - m - gh);
@@ -446,10 +715,15 @@ k_split_fwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   int hsum = 0, zsum = 0;
   if (a < Np) {  // always true for KG > 1 (the padded width is a multiple of 64): the shuffles below see every lane
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (w0 > 0 && kg == 0) {
+      const float c = pe == kExpZero ? 0.0f : pow2i(pe - m);
+      const float4 t = *reinterpret_cast<const float4*>(T + (r - S1) * Np + a);
+      acc = make_float4(c * t.x, c * t.y, c * t.z, c * t.w);
+    }
     const float* hz_l = HZ + a;
     const float* hz_r = HZ + Np + a;
     int k = 0;
-    for (; k + 8 * KG <= w - 1; k += 8 * KG) {
+    for (; k + 8 * KG <= nk; k += 8 * KG) {
       float4 h[8], z[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -465,14 +739,14 @@ k_split_fwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
         acc.w = fmaf(c * h[u].w, cz * z[u].w, acc.w);
       }
     }
-    for (; k < w - 1; k += 4 * KG) {  // remainder in masked groups of four: no serial chain of dependent loads
+    for (; k < nk; k += 4 * KG) {  // remainder in masked groups of four: no serial chain of dependent loads
       float4 h[4], z[4];
       float c[4], cz[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int idx = k + u * KG + kg;
-        const int kk = min(idx, w - 2);
-        c[u] = (idx < w - 1) ? s_c[kk] : 0.0f;
+        const int kk = min(idx, nk - 1);
+        c[u] = (idx < nk) ? s_c[kk] : 0.0f;
         cz[u] = s_cz[kk];
         h[u] = *reinterpret_cast<const float4*>(hz_l + s_l[kk] * ld);
         z[u] = *reinterpret_cast<const float4*>(hz_r + s_r[kk] * ld);
@@ -639,7 +913,8 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
             const float* __restrict__ HZ, const float* __restrict__ BH, const int32_t* __restrict__ mexp,
             const uint32_t* __restrict__ tmaxb, float* __restrict__ UV, int32_t* __restrict__ uexp,
             uint32_t* __restrict__ umaxb, float* __restrict__ gsc, void* __restrict__ UVb, int planes,
-            int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb) {
+            int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb, int wt,
+            const int32_t* __restrict__ bexp, int64_t Sall) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
   const int64_t r = row0 + blockIdx.x;
@@ -647,15 +922,18 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   const int b = row_b[r], i = row_i[r];
   const int n = lens[b];
   const int j = i + w;
-  const int nl = n - j;  // parents (i, j'), j' = j+1..n   (this span is their left child)
-  const int nr = i;      // parents (i', j), i' = 0..i-1   (this span is their right child)
+  // parents of this launch: all, or (wt > 0) those narrower than wt, the rest lies summed in UV
+  const int most = wt > 0 ? wt - 1 - w : n;
+  const int nl = min(n - j, most);  // parents (i, j'), j' = j+1..   (this span is their left child)
+  const int nr = min(i, most);      // parents (i', j), i' = ..i-1   (this span is their right child)
   const int nt = nl + nr;
   float* s_c = reinterpret_cast<float*>(smem);             // [nt] coefficient of the parent's adjoint
   float* s_cs = s_c + nt;                                  // [nt] coefficient of the sibling's projection
   int32_t* s_p = reinterpret_cast<int32_t*>(s_cs + nt);    // [nt] parent row (index into BH: row - S1)
   int32_t* s_s = s_p + nt;                                 // [nt] sibling row
 
-  int dmax = kExpZero;
+  const int peu = wt > 0 ? bexp[r] : kExpZero, pev = wt > 0 ? bexp[Sall + r] : kExpZero;
+  int dmax = max(peu, pev);
   for (int t = lane; t < nt; t += 64) {
     int pr, sr;
     if (t < nl) {
@@ -663,7 +941,7 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
       pr = row_of(rowtab, stride, B, jp - i, b, i, n);   // parent (i, j')
       sr = row_of(rowtab, stride, B, jp - j, b, j, n);   // sibling (j, j'), used through its zeta
     } else {
-      const int ip = t - nl;
+      const int ip = i - nr + (t - nl);
       pr = row_of(rowtab, stride, B, j - ip, b, ip, n);  // parent (i', j)
       sr = row_of(rowtab, stride, B, i - ip, b, ip, n);  // sibling (i', i), used through its eta
     }
@@ -689,6 +967,13 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   float amax = 0.0f;
   if (a < Np) {
     float4 u = make_float4(0.f, 0.f, 0.f, 0.f), v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (wt > 0) {
+      const float cu = peu == kExpZero ? 0.0f : pow2i(peu - m), cv = pev == kExpZero ? 0.0f : pow2i(pev - m);
+      u = *reinterpret_cast<const float4*>(UV + r * ld + a);
+      v = *reinterpret_cast<const float4*>(UV + r * ld + Np + a);
+      u = make_float4(cu * u.x, cu * u.y, cu * u.z, cu * u.w);
+      v = make_float4(cv * v.x, cv * v.y, cv * v.z, cv * v.w);
+    }
     const float* bh = BH + a;
     // left-child role: sibling zeta (second half of HZ); right-child role: sibling eta (first half)
 #define SPCFG_GATHER(ACC, T0, T1, HZOFF)                                                        \
@@ -815,6 +1100,11 @@ k_span_marginals(int B, int N, int Np, int n_max, int64_t S1, const int32_t* __r
   }
 }
 
+// the tables of a band over 1024-word sentences take 136 KB
+bool set_band_lds(const void* kernel) {
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * band_words(kMaxLen + 8)) == hipSuccess;
+}
+
 }  // namespace
 
 void launch_plan(const Layout& ly, const Ptrs& p, const LenArg& lens, hipStream_t st) {
@@ -888,19 +1178,40 @@ void launch_leaf_prep(const Layout& ly, const Ptrs& p, const float* log_emit, bo
 void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int64_t rows, bool write_planes,
                       hipStream_t st) {
   void* Tb = write_planes ? p.Tb : nullptr;
-  const size_t sh = (size_t)(w - 1) * 16;
+  const int stride = (ly.n_max + 1) * ly.B;
+  const int w0 = ly.band_fwd[w / kBandW] ? w / kBandW * kBandW : 0;
+  if (w == w0) {  // the first width of a band: all that its widths can do together
+    const int S_max = round_up(w0 + kBandI, 4);
+    const size_t lds = sizeof(int32_t) * (size_t)band_words(S_max), sums = sizeof(float) * (size_t)kBandSumWords;
+    const size_t lds_sum = lds > sums ? lds : sums;
+    const unsigned ti = (unsigned)((ly.n_long - w0 + kBandI) / kBandI), z = (unsigned)ly.B;
+    if ((int64_t)ti * z * (ly.Np / 64) >= kBandMinWaves) {
+      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_fwd<1>));
+      (void)attr;
+      launch_k(k_split_band_fwd<1>, dim3((unsigned)((ly.Np / 64 + kBandWaves - 1) / kBandWaves), ti, z), dim3(kBandWaves * 64), lds,
+               st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.mexp, p.tmaxb,
+             p.hmaxb, p.zmaxb, p.T, p.bexp);
+    } else {
+      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_fwd<kBandShare>));
+      (void)attr;
+      launch_k(k_split_band_fwd<kBandShare>, dim3((unsigned)(ly.Np / 64), ti, z), dim3(kBandShare * 64), lds_sum, st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.mexp, p.tmaxb,
+             p.hmaxb, p.zmaxb, p.T, p.bexp);
+    }
+  }
+  const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
+  const size_t sh = (size_t)nk * 16;
   const int chunks = (ly.Np + kChunk - 1) / kChunk;
-  if (rows * chunks < 1024 && w - 1 >= 64) {  // fewer than one wavefront per SIMD, long chains of split points
+  if (rows * chunks < 1024 && nk >= 64) {  // fewer than one wavefront per SIMD, long chains of split points
     const dim3 grid((unsigned)rows, (unsigned)(ly.Np / 64));
-    launch_k(k_split_fwd<4>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
+    launch_k(k_split_fwd<4>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
              p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
-             ly.G > 1 ? 1 : 0);
+             ly.G > 1 ? 1 : 0, w0, p.bexp);
     return;
   }
   const dim3 grid((unsigned)rows, (unsigned)chunks);
-  launch_k(k_split_fwd<1>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
+  launch_k(k_split_fwd<1>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
            p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
-           ly.G > 1 ? 1 : 0);
+           ly.G > 1 ? 1 : 0, w0, p.bexp);
 }
 
 void launch_root_fwd(const Layout& ly, const Ptrs& p, const float* log_root, float* logZ, hipStream_t st) {
@@ -922,11 +1233,35 @@ void launch_root_bwd(const Layout& ly, const Ptrs& p, const float* log_root, con
 
 void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int64_t rows, bool write_planes,
                       hipStream_t st) {
-  const size_t sh = (size_t)ly.n_max * 16;
+  const int stride = (ly.n_max + 1) * ly.B;
+  const bool band = ly.band_bwd[w / kBandW] != 0;
+  const int w0 = w / kBandW * kBandW, wt = band ? w0 + kBandW : 0;
+  // the widest launch of the band (the reverse pass starts one width below n_max, where all spans are roots)
+  int top = wt - 1 < ly.n_long ? wt - 1 : ly.n_long;
+  if (top > ly.n_max - 1) top = ly.n_max - 1;
+  if (band && w == top) {
+    const int S_max = round_up(ly.n_long - w0 + kBandI, 4);  // (adj eta: n - wt + 1, adj zeta: n - w0 + 3)
+    const size_t lds = sizeof(int32_t) * (size_t)band_words(S_max), sums = sizeof(float) * (size_t)kBandSumWords;
+    const size_t lds_sum = lds > sums ? lds : sums;
+    const unsigned ti = (unsigned)((ly.n_long - w0 + kBandI) / kBandI), z = (unsigned)(2 * ly.B);
+    if ((int64_t)ti * z * (ly.Np / 64) >= kBandMinWaves) {
+      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<1>));
+      (void)attr;
+      launch_k(k_split_band_bwd<1>, dim3((unsigned)((ly.Np / 64 + kBandWaves - 1) / kBandWaves), ti, z), dim3(kBandWaves * 64), lds,
+               st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.BH, p.mexp,
+             p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
+    } else {
+      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<kBandShare>));
+      (void)attr;
+      launch_k(k_split_band_bwd<kBandShare>, dim3((unsigned)(ly.Np / 64), ti, z), dim3(kBandShare * 64), lds_sum, st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.BH, p.mexp,
+             p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
+    }
+  }
+  const size_t sh = (size_t)(band ? 2 * (wt - 1 - w) : ly.n_max) * 16;
   const dim3 grid((unsigned)rows, (unsigned)((ly.Np + kChunk - 1) / kChunk));
-  launch_k(k_split_bwd, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, p.lens, p.rowbase, p.row_b,
+  launch_k(k_split_bwd, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b,
                      p.row_i, p.rootmask, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr, ly.planes_bwd,
-                     ly.uvb_plane, p.hmaxb, p.zmaxb);
+                     ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.bexp, ly.Sall);
 }
 
 void launch_zero_pad_emit(const Layout& ly, const Ptrs& p, float* grad_log_emit, hipStream_t st) {

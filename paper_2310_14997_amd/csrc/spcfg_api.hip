@@ -22,6 +22,11 @@ struct Plan {            // host-side copy of the span schedule
   LenArg lens;
 };
 
+// 50 MB are about 10 us, the cost of one more dependent launch with its tables: with bands from 25 MB on, the forward pass at
+// B = 64, N = 2048, n <= 40 lost 3 % instead of gaining 1 %
+constexpr double kBandBytes = 50e6;
+constexpr int kBandChain = 48;
+
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int check_cfg(const spcfg_config* c) {
@@ -73,6 +78,7 @@ Layout make_layout(int N, int P, int B, int n_max, int64_t S1, int64_t S2, int b
   ly.hmaxb = take(i4 * ly.Sall);
   ly.zmaxb = take(i4 * ly.Sall);
   ly.colmax = take(f4 * 2 * (size_t)(ly.Np + ly.Pp) * ly.G);
+  ly.bexp = take(i4 * 2 * ly.Sall);
   ly.gsc = take(f4 * ly.Sall);
   ly.xs = take(f4 * S1);
   // One arrival counter per output tile of the largest launch: at most max(S1, S2) rows (one width; grouped
@@ -143,6 +149,7 @@ Ptrs resolve(const Layout& ly, void* ws) {
   p.leafE = (float*)(b + ly.leafE); p.T = (float*)(b + ly.T); p.HZ = (float*)(b + ly.HZ);
   p.UV = (float*)(b + ly.UV); p.BH = (float*)(b + ly.BH);
   p.partial = (float*)(b + ly.partial); p.counters = (int32_t*)(b + ly.counters);
+  p.bexp = (int32_t*)(b + ly.bexp);
   p.sentrows = (int32_t*)(b + ly.sentrows); p.sentoff = (int32_t*)(b + ly.sentoff);
   p.Tb = ly.planes ? b + ly.Tb : nullptr; p.UVb = ly.planes_bwd ? b + ly.UVb : nullptr; p.leafEb = ly.planes ? b + ly.leafEb : nullptr;
   p.UVt_n = b + ly.UVt_n; p.Tt = b + ly.Tt; p.UVt_p = b + ly.UVt_p; p.Et = b + ly.Et;
@@ -150,6 +157,35 @@ Ptrs resolve(const Layout& ly, void* ws) {
   p.Wn3 = b + ly.Wn3; p.Wp3 = b + ly.Wp3; p.Wtn3 = b + ly.Wtn3; p.Wtp3 = b + ly.Wtp3;
   p.Wn = (float*)(b + ly.Wn); p.Wp = (float*)(b + ly.Wp); p.Wtn = (float*)(b + ly.Wtn); p.Wtp = (float*)(b + ly.Wtp);
   return p;
+}
+
+// Which bands of widths sum together (k_split_band_fwd / _bwd).  A band saves rows read (of Np floats) and costs a launch
+// of its own, the partial sums' rows written and read, and rows read for spans that a tile lacks; counted exactly here,
+// per tile of four starts.  It pays from kBandBytes saved on (see there); long chains of few spans are latency, not
+// bytes, and pay from 48 split points (or parents) on.
+void choose_bands(const Plan& plan, Layout* ly) {
+  ly->n_long = 2;
+  for (int b = 0; b < ly->B; ++b) ly->n_long = plan.lens.v[b] > ly->n_long ? plan.lens.v[b] : ly->n_long;
+  for (int k = 0; k * kBandW < ly->n_long; ++k) {
+    const int w0 = k * kBandW, wt = w0 + kBandW;
+    double fwd = 0, bwd = 0;  // rows saved
+    for (int b = 0; b < ly->B; ++b) {
+      const int n = plan.lens.v[b];
+      if (n < w0 || n < 2) continue;
+      const double tiles = (n - w0 + kBandW) / kBandW;
+      fwd -= tiles * (2 * kBandW + 3) * (w0 + 2);
+      bwd -= tiles * (2 * kBandW + 3) * (n - w0);
+      for (int w = w0 > 0 ? w0 : 1; w < wt && w <= n; ++w) {
+        const double spans = n - w + 1;
+        fwd += spans * (2.0 * (w - 1) - 4.0 * (w - w0) - 2.0);
+        const int near = wt - 1 - w < n - w ? wt - 1 - w : n - w;  // parents inside the band, at most, on either side
+        bwd += spans * (2.0 * (n - w) - 4.0 * near - 4.0);
+      }
+    }
+    // (below width 8 most split points have a child inside the band)
+    ly->band_fwd[k] = w0 >= 2 * kBandW && (4.0 * ly->Np * fwd >= kBandBytes || w0 >= kBandChain);
+    ly->band_bwd[k] = 4.0 * ly->Np * bwd >= kBandBytes || ly->n_long - w0 >= kBandChain;
+  }
 }
 
 int make_plan(const spcfg_config* cfg, const int32_t* lengths, int B, int n_max, Plan* plan, Layout* ly,
@@ -174,6 +210,7 @@ int make_plan(const spcfg_config* cfg, const int32_t* lengths, int B, int n_max,
   *ly = make_layout(cfg->N, cfg->P, B, n_max, S1, Sall - S1, cfg->precision == SPCFG_PRECISION_BF16,
                     (cfg->flags & SPCFG_FLAG_PER_SENTENCE_GRAMMAR) != 0, (cfg->flags & SPCFG_FLAG_FP32_MFMA) != 0,
                     (cfg->flags & SPCFG_FLAG_BF16_SINGLE_FORWARD) != 0, gemm_wgs);
+  choose_bands(*plan, ly);
   return SPCFG_OK;
 }
 

@@ -41,6 +41,8 @@ constexpr int kExpZero = -(1 << 24);     // exponent marking an all-zero vector
 constexpr int kMaxB = 960;               // lengths travel as one kernel argument
 constexpr int kMaxLen = 1024;
 
+constexpr int kBandW = 4;                // widths whose split-point sums share row reads (see k_split_band_fwd)
+
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
 struct Layout {
@@ -68,6 +70,10 @@ struct Layout {
   size_t Tg3, Eg3;              // tn3: three bf16 planes of gsc[s] * T[s] ([3][S2p32][Np]) and of gsc[s] * leafE[s] ([3][S1p32][Pp])
   size_t Tb, UVb, leafEb;       // planes > 0: bf16 planes of T, UV, leafE ([planes][rows][cols]), written by their producers
   size_t sentrows, sentoff;     // per-sentence grammars only: rows of width >= 2 listed sentence by sentence, first entry of each
+  size_t bexp;                  // [2][Sall] exponents of the partial split-point sums (forward: the first half)
+  // bands: widths kBandW * k .. + kBandW - 1 take their split-point sums (reverse: parent sums) partly in one pass
+  int n_long;                   // longest sentence of the batch (n_max may be larger)
+  uint8_t band_fwd[kMaxLen / kBandW + 1], band_bwd[kMaxLen / kBandW + 1];
   int n_counters;
   int gemm_wgs;          // workgroups the partial-tile scratch is sized for (kGemmWgs, fewer for the static scratch)
   size_t total;
@@ -85,6 +91,7 @@ struct Ptrs {  // device pointers resolved from a Layout
   void *Tb, *UVb, *leafEb;  // null when the layout has no planes
   void *Wn3, *Wp3, *Wtn3, *Wtp3;
   int32_t* counters;
+  int32_t* bexp;
   int32_t* sentrows; int32_t* sentoff;
 };
 
