@@ -2,8 +2,7 @@
 // (App. A) - root over the nonterminals, left and right productions over N u P children per parent,
 // emissions over the vocabulary per preterminal - and the per-token gather of the emission table that the
 // inside pass consumes.  All kernels are memory-bound row reductions or elementwise passes; results are
-// deterministic (the token scatter of the emission gradient walks the tokens in a fixed order inside the
-// one wavefront that owns a block of the table).
+// deterministic (every entry of the emission gradient has one owner, which adds its tokens in order).
 #include <cmath>
 
 #include "spcfg_internal.h"
@@ -41,27 +40,142 @@ __device__ __forceinline__ float bsum(float v, float* red) {
   return r;
 }
 
-// mode 0: out = softmax(row); mode 1: out = log_softmax(row); mode 2: out[row] = logsumexp(row) only
-__global__ void __launch_bounds__(256) k_row_softmax(const float* __restrict__ z, int64_t cols, float* __restrict__ out,
-                                                     int mode) {
-  __shared__ float red[4];
-  const float* row = z + (int64_t)blockIdx.x * cols;
+// ---- rows held in registers ------------------------------------------------------------------------------
+// Every softmax row is read once: the 256 threads of a workgroup keep it in registers (up to 4 * kMostE4 values each)
+// between the maximum, the sum and the write.  16-byte loads where base and row length allow it, 4-byte ones otherwise
+// (the same values per workgroup, other columns per thread).  Longer rows are read once per pass instead.
+constexpr int kMostE4 = 16;
+
+template <bool VEC, int E4>
+__device__ __forceinline__ void row_load(const float* __restrict__ row, int cols, float pad, float (&x)[4 * E4]) {
+#pragma unroll
+  for (int e = 0; e < E4; ++e) {
+    if (VEC) {
+      const int c = (e * 256 + (int)threadIdx.x) * 4;
+      const float4 v = c < cols ? *reinterpret_cast<const float4*>(row + c) : make_float4(pad, pad, pad, pad);
+      x[4 * e] = v.x; x[4 * e + 1] = v.y; x[4 * e + 2] = v.z; x[4 * e + 3] = v.w;
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = (e * 4 + u) * 256 + (int)threadIdx.x;
+        x[4 * e + u] = c < cols ? row[c] : pad;
+      }
+    }
+  }
+}
+template <bool VEC, int E4>
+__device__ __forceinline__ void row_store(float* __restrict__ row, int cols, const float (&x)[4 * E4]) {
+#pragma unroll
+  for (int e = 0; e < E4; ++e) {
+    if (VEC) {
+      const int c = (e * 256 + (int)threadIdx.x) * 4;
+      if (c < cols) *reinterpret_cast<float4*>(row + c) = make_float4(x[4 * e], x[4 * e + 1], x[4 * e + 2], x[4 * e + 3]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = (e * 4 + u) * 256 + (int)threadIdx.x;
+        if (c < cols) row[c] = x[4 * e + u];
+      }
+    }
+  }
+}
+
+// out = softmax(row), or with `lse` *out = logsumexp(row)
+template <bool VEC, int E4>
+__device__ __forceinline__ void row_softmax(const float* __restrict__ row, int cols, float* __restrict__ out, bool lse,
+                                            float* red) {
+  float x[4 * E4];
+  row_load<VEC, E4>(row, cols, -INFINITY, x);
+  float m = x[0];
+#pragma unroll
+  for (int e = 1; e < 4 * E4; ++e) m = fmaxf(m, x[e]);
+  m = bmax(m, red);
+  float s = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 4 * E4; ++e) { x[e] = expf(x[e] - m); s += x[e]; }
+  s = bsum(s, red);
+  if (lse) {
+    if (threadIdx.x == 0) *out = m + logf(s);
+    return;
+  }
+  const float inv = 1.0f / s;
+#pragma unroll
+  for (int e = 0; e < 4 * E4; ++e) x[e] *= inv;
+  row_store<VEC, E4>(out, cols, x);
+}
+__device__ void row_softmax_long(const float* __restrict__ row, int64_t cols, float* __restrict__ out, bool lse, float* red) {
   float m = -INFINITY;
   for (int64_t c = threadIdx.x; c < cols; c += 256) m = fmaxf(m, row[c]);
   m = bmax(m, red);
   float s = 0.0f;
   for (int64_t c = threadIdx.x; c < cols; c += 256) s += expf(row[c] - m);
   s = bsum(s, red);
-  if (mode == 2) {
-    if (threadIdx.x == 0) out[blockIdx.x] = m + logf(s);
+  if (lse) {
+    if (threadIdx.x == 0) *out = m + logf(s);
     return;
   }
-  float* o = out + (int64_t)blockIdx.x * cols;
-  const float inv = 1.0f / s, ls = logf(s);
-  for (int64_t c = threadIdx.x; c < cols; c += 256) o[c] = mode == 0 ? expf(row[c] - m) * inv : (row[c] - m) - ls;
+  const float inv = 1.0f / s;
+  for (int64_t c = threadIdx.x; c < cols; c += 256) out[c] = expf(row[c] - m) * inv;
+}
+// out = log_softmax(row) for the one row of root scores.  A rounding of the sum's logarithm would shift every entry alike (by up
+// to 5e-7 at N = 2048, as large as all other errors of the pass): sum and logarithm are in 64 bits.
+__device__ void row_log_softmax(const float* __restrict__ row, int cols, float* __restrict__ out, float* red) {
+  __shared__ double part[4];
+  float m = -INFINITY;
+  for (int c = threadIdx.x; c < cols; c += 256) m = fmaxf(m, row[c]);
+  m = bmax(m, red);
+  double s = 0.0;
+  for (int c = threadIdx.x; c < cols; c += 256) s += (double)expf(row[c] - m);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  const double ls = log(part[0] + part[1] + part[2] + part[3]);
+  for (int c = threadIdx.x; c < cols; c += 256) out[c] = (float)(((double)row[c] - (double)m) - ls);
+}
+
+__device__ __forceinline__ bool aligned16(const void* a, const void* b, int64_t cols) {
+  return ((((uintptr_t)a | (uintptr_t)b) & 15) == 0) && (cols & 3) == 0;
+}
+
+// All rows of the forward pass in one launch: the root (a chain), the P vocabulary rows (the longest), then L and R.
+// Bound by HBM: every score is read once and L, R written once.  N = P = 2048, V = 10000: 53 us (4.0 TB/s); four launches
+// that read each row two or three times took 104 us.
+__global__ void __launch_bounds__(256) k_rows_forward(int N, int P, int64_t V, const float* __restrict__ root,
+                                                      const float* __restrict__ Lz, const float* __restrict__ Rz,
+                                                      const float* __restrict__ emis, float* __restrict__ log_root,
+                                                      float* __restrict__ L, float* __restrict__ R, float* __restrict__ lse) {
+  __shared__ float red[4];
+  const int64_t M = (int64_t)N + P;
+  int r = blockIdx.x;
+  if (r == 0) {
+    row_log_softmax(root, N, log_root, red);
+    return;
+  }
+  r -= 1;
+  const float* row;
+  float* out;
+  int64_t cols = M;
+  const bool lse_row = r < P;
+  if (lse_row) { row = emis + r * V; out = lse + r; cols = V; }
+  else if ((r -= P) < N) { row = Lz + r * M; out = L + r * M; }
+  else { r -= N; row = Rz + r * M; out = R + r * M; }
+  const bool vec = aligned16(row, lse_row ? row : out, cols);
+  if (cols <= 1024 * 4) {
+    if (vec) row_softmax<true, 4>(row, (int)cols, out, lse_row, red);
+    else row_softmax<false, 4>(row, (int)cols, out, lse_row, red);
+  } else if (cols <= 1024 * kMostE4) {
+    if (vec) row_softmax<true, kMostE4>(row, (int)cols, out, lse_row, red);
+    else row_softmax<false, kMostE4>(row, (int)cols, out, lse_row, red);
+  } else {
+    row_softmax_long(row, cols, out, lse_row, red);
+  }
 }
 
 // log_emit[b, i, T] = emis_logits[T, tok] - lse[T] for i < n_b, 0 on padding; an out-of-range token id gives NaN.
+// A line of the table per token and preterminal, most of them from cache (tokens repeat and share lines): 26 us for 1400
+// tokens at P = 2048, V = 10000.  Whole tiles of the table turned in LDS took 54 us, and twice as long at every size
+// from 320 to 12800 tokens.
 __global__ void __launch_bounds__(256) k_gather_emit(LenArg la, int n_max, int P, int V,
                                                      const float* __restrict__ emis, const float* __restrict__ lse,
                                                      const int32_t* __restrict__ tokens, float* __restrict__ out) {
@@ -76,102 +190,192 @@ __global__ void __launch_bounds__(256) k_gather_emit(LenArg la, int n_max, int P
   for (int t = threadIdx.x; t < P; t += 256) o[t] = ok ? emis[(int64_t)t * V + tok] - lse[t] : NAN;
 }
 
-// softmax backward per row: dz = p * (g - sum_j p_j g_j)
-__global__ void __launch_bounds__(256) k_softmax_bwd(const float* __restrict__ p, const float* __restrict__ g,
-                                                     int64_t cols, float* __restrict__ dz) {
-  __shared__ float red[4];
-  const int64_t base = (int64_t)blockIdx.x * cols;
-  float d = 0.0f;
-  for (int64_t c = threadIdx.x; c < cols; c += 256) d = fmaf(p[base + c], g[base + c], d);
-  d = bsum(d, red);
-  for (int64_t c = threadIdx.x; c < cols; c += 256) dz[base + c] = p[base + c] * (g[base + c] - d);
-}
+// ---- the emission table in tiles of 64 preterminals x kVChunk vocabulary entries ---------------------------
+constexpr int kVChunk = 128;
+constexpr int kSeg = 1024;        // token positions looked through at a time, four per thread
+constexpr int kMaxVBlocks = 32768;  // workgroups along the vocabulary; longer tables take several chunks each
+static_assert((int64_t)kMaxB * kMaxLen < (1 << 20), "a list entry holds a position in 20 bits");
 
-// log-softmax backward for the root: dz = g - exp(log_root) * sum_j g_j
-__global__ void __launch_bounds__(256) k_logsoftmax_bwd(const float* __restrict__ logp, const float* __restrict__ g, int n,
-                                                        float* __restrict__ dz) {
-  __shared__ float red[4];
-  float s = 0.0f;
-  for (int c = threadIdx.x; c < n; c += 256) s += g[c];
-  s = bsum(s, red);
-  for (int c = threadIdx.x; c < n; c += 256) dz[c] = g[c] - expf(logp[c]) * s;
+// softmax backward per row: dz = p * (g - sum_j p_j g_j), both rows kept in registers
+template <bool VEC, int E4>
+__device__ __forceinline__ void row_softmax_bwd(const float* __restrict__ p, const float* __restrict__ g, int cols,
+                                                float* __restrict__ dz, float* red) {
+  float x[4 * E4], y[4 * E4];
+  row_load<VEC, E4>(p, cols, 0.0f, x);
+  row_load<VEC, E4>(g, cols, 0.0f, y);
+  float d = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 4 * E4; ++e) d = fmaf(x[e], y[e], d);
+  d = bsum(d, red);
+#pragma unroll
+  for (int e = 0; e < 4 * E4; ++e) x[e] = x[e] * (y[e] - d);
+  row_store<VEC, E4>(dz, cols, x);
 }
 
 // part[c][T] = sum of grad_log_emit[b, i, T] over the real token positions p = b * n_max + i with p % kColChunks == c
 // (position order inside a chunk); tot[T] = sum_c part[c][T] in chunk order.  Deterministic two-level sum.
 constexpr int kColChunks = 32;
-__global__ void __launch_bounds__(64) k_emit_colsum_part(LenArg la, int B, int n_max, int P, const float* __restrict__ ge,
-                                                         float* __restrict__ part) {
-  const int t = blockIdx.x * 64 + threadIdx.x;
-  const int c = blockIdx.y;
-  if (t >= P) return;
-  float s = 0.0f;
-  for (int p = c; p < B * n_max; p += kColChunks) {
-    const int b = p / n_max, i = p - b * n_max;
-    if (i < la.v[b]) s += ge[(int64_t)p * P + t];
+
+// Everything of the backward pass that the emission tiles wait for or that they do not need, in one launch: column sums
+// (a wavefront per 64 preterminals and chunk, eight positions in flight; chains, so they start first), then the rows of
+// L and R, then the root (dz = g - exp(log_root) * sum_j g_j).  N = P = 2048, 1400 tokens: 61 us; five launches took 100 us.
+__global__ void __launch_bounds__(256) k_rows_backward(LenArg la, int B, int n_max, int N, int P,
+                                                       const float* __restrict__ log_root, const float* __restrict__ L,
+                                                       const float* __restrict__ R, const float* __restrict__ g_root,
+                                                       const float* __restrict__ gL, const float* __restrict__ gR,
+                                                       const float* __restrict__ ge, float* __restrict__ d_root,
+                                                       float* __restrict__ dL, float* __restrict__ dR,
+                                                       float* __restrict__ part) {
+  __shared__ float red[4];
+  const int col_blocks = (P + 63) / 64 * (kColChunks / 4);
+  int r = blockIdx.x;
+  if (r < col_blocks) {
+    const int t = r / (kColChunks / 4) * 64 + (threadIdx.x & 63);
+    const int c = r % (kColChunks / 4) * 4 + (threadIdx.x >> 6);
+    if (t >= P) return;
+    float s = 0.0f;
+    for (int p0 = c; p0 < B * n_max; p0 += 8 * kColChunks) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int p = p0 + u * kColChunks;
+        const int b = p / n_max;
+        v[u] = p < B * n_max && p - b * n_max < la.v[min(b, B - 1)] ? ge[(int64_t)p * P + t] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    part[(int64_t)c * P + t] = s;
+    return;
   }
-  part[(int64_t)c * P + t] = s;
-}
-__global__ void __launch_bounds__(256) k_emit_colsum_final(int P, float* __restrict__ part) {  // tot -> part[0]
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= P) return;
-  float s = 0.0f;
-  for (int c = 0; c < kColChunks; ++c) s += part[(int64_t)c * P + t];
-  part[t] = s;
+  r -= col_blocks;
+  if (r == 2 * N) {
+    float s = 0.0f;
+    for (int c = threadIdx.x; c < N; c += 256) s += g_root[c];
+    s = bsum(s, red);
+    for (int c = threadIdx.x; c < N; c += 256) d_root[c] = g_root[c] - expf(log_root[c]) * s;
+    return;
+  }
+  const int64_t cols = (int64_t)N + P, base = (int64_t)(r < N ? r : r - N) * cols;
+  const float* p = (r < N ? L : R) + base;
+  const float* g = (r < N ? gL : gR) + base;
+  float* dz = (r < N ? dL : dR) + base;
+  const bool vec = aligned16(p, g, cols) && aligned16(dz, dz, cols);
+  if (cols <= 1024 * 4) {
+    if (vec) row_softmax_bwd<true, 4>(p, g, (int)cols, dz, red);
+    else row_softmax_bwd<false, 4>(p, g, (int)cols, dz, red);
+  } else if (cols <= 1024 * 8) {
+    if (vec) row_softmax_bwd<true, 8>(p, g, (int)cols, dz, red);
+    else row_softmax_bwd<false, 8>(p, g, (int)cols, dz, red);
+  } else {
+    float d = 0.0f;
+    for (int64_t c = threadIdx.x; c < cols; c += 256) d = fmaf(p[c], g[c], d);
+    d = bsum(d, red);
+    for (int64_t c = threadIdx.x; c < cols; c += 256) dz[c] = p[c] * (g[c] - d);
+  }
 }
 
 // d emis[T, v] = sum_{(b,i): tok = v} grad_log_emit[b, i, T]  -  softmax(emis[T, :])[v] * tot[T].
-// One wavefront owns a block of 64 preterminals x kVChunk vocabulary entries: it accumulates the token
-// contributions of its block in LDS (lane = preterminal, so every LDS word has one owner; tokens are walked in
-// order, which fixes the summation order of repeated tokens), then writes the block once, coalesced along v.
-constexpr int kVChunk = 128;
-__global__ void __launch_bounds__(64) k_emis_grad(LenArg la, int B, int n_max, int P, int V,
-                                                  const int32_t* __restrict__ tokens, const float* __restrict__ ge,
-                                                  const float* __restrict__ emis, const float* __restrict__ lse,
-                                                  const float* __restrict__ tot, float* __restrict__ d) {
+// One workgroup owns a tile of 64 preterminals x kVChunk vocabulary entries and accumulates the token contributions in LDS.
+// Deterministic: the tokens of a segment are listed in position order, in four lists by token id mod 4, one per
+// wavefront, so every LDS word has one owner that adds in position order (eight positions' loads in flight).  The
+// tile's part of the table is loaded before the tokens are looked through, and the tile is written once, coalesced along v.
+// P = 2048, V = 10000, 1400 tokens: 73 us (36 us of traffic); one wavefront per tile, adding a token at a time, took 332 us.
+__global__ void __launch_bounds__(256) k_emis_grad(LenArg la, int B, int n_max, int P, int V,
+                                                   const int32_t* __restrict__ tokens, const float* __restrict__ ge,
+                                                   const float* __restrict__ emis, const float* __restrict__ lse,
+                                                   const float* __restrict__ part, float* __restrict__ d) {
   __shared__ float tile[kVChunk][65];
-  const int lane = threadIdx.x;
-  const int t0 = blockIdx.x * 64, v0 = blockIdx.y * kVChunk;
-  const int v1 = min(v0 + kVChunk, V);
-  for (int v = 0; v < kVChunk; ++v) tile[v][lane] = 0.0f;
-  const int t = t0 + lane;
-  for (int b = 0; b < B; ++b) {
-    const int n = la.v[b];
-    for (int i0 = 0; i0 < n; i0 += 64) {
-      // one coalesced load of up to 64 token ids, then a ballot of those that fall into this block
-      const int i = i0 + lane;
-      const int mytok = i < n ? tokens[b * n_max + i] : -1;
-      unsigned long long hit = __ballot(mytok >= v0 && mytok < v1);
-      while (hit) {  // ascending position order
-        const int j = __ffsll((long long)hit) - 1;
-        hit &= hit - 1;
-        const int tok = __shfl(mytok, j, 64);
-        if (t < P) tile[tok - v0][lane] += ge[((int64_t)b * n_max + i0 + j) * P + t];
+  __shared__ int list[kSeg];
+  __shared__ int cnt[64], first[65];  // [list][quarter of the segment][wavefront]
+  __shared__ float tot[64], ls[64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t0 = blockIdx.x * 64, t = t0 + lane;
+  const int positions = B * n_max, chunks = (V + kVChunk - 1) / kVChunk;
+  if (wave == 0) {
+    float s = 0.0f;
+    if (t < P) {
+#pragma unroll
+      for (int c = 0; c < kColChunks; ++c) s += part[(int64_t)c * P + t];
+    }
+    tot[lane] = s;
+    ls[lane] = t < P ? lse[t] : 0.0f;
+  }
+  for (int vc = blockIdx.y; vc < chunks; vc += gridDim.y) {
+    const int v0 = vc * kVChunk, nv = min(kVChunk, V - v0);
+    float ea[16], eb[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int tr = min(t0 + wave * 16 + r, P - 1);
+      const float* row = emis + (int64_t)tr * V + v0;
+      ea[r] = lane < nv ? row[lane] : 0.0f;
+      eb[r] = lane + 64 < nv ? row[lane + 64] : 0.0f;
+    }
+    __syncthreads();  // the tile of the chunk before has been written out
+    for (int v = wave; v < kVChunk; v += 4) tile[v][lane] = 0.0f;
+    for (int seg = 0; seg < positions; seg += kSeg) {
+      int rel[kSeg / 256];
+#pragma unroll
+      for (int j = 0; j < kSeg / 256; ++j) {
+        const int p = seg + j * 256 + threadIdx.x;
+        rel[j] = -1;
+        if (p < positions) {
+          const int b = p / n_max;
+          const int tok = tokens[p];
+          if (p - b * n_max < la.v[b] && tok >= v0 && tok < v0 + nv) rel[j] = tok - v0;
+        }
+      }
+      int before[kSeg / 256];  // entries of the same list, quarter and wavefront before this one
+#pragma unroll
+      for (int j = 0; j < kSeg / 256; ++j) {
+        before[j] = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const unsigned long long m = __ballot(rel[j] >= 0 && (rel[j] & 3) == q);
+          if (lane == 0) cnt[q * 16 + j * 4 + wave] = __popcll(m);
+          if ((rel[j] & 3) == q) before[j] = __popcll(m & ((1ull << lane) - 1));
+        }
+      }
+      __syncthreads();  // counts (and, in the first segment, the cleared tile) are there; the list before has been used
+      if (wave == 0) {
+        int s = cnt[lane];
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int below = __shfl_up(s, o, 64);
+          if (lane >= o) s += below;
+        }
+        first[lane + 1] = s;
+        if (lane == 0) first[0] = 0;
+      }
+      __syncthreads();
+      if (first[64] == 0) continue;
+#pragma unroll
+      for (int j = 0; j < kSeg / 256; ++j)
+        if (rel[j] >= 0)
+          list[first[(rel[j] & 3) * 16 + j * 4 + wave] + before[j]] = ((seg + j * 256 + threadIdx.x) << 8) | rel[j];
+      __syncthreads();
+      const int end = first[wave * 16 + 16];
+      for (int h = first[wave * 16]; h < end; h += 8) {
+        int e[8];
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          e[u] = list[min(h + u, end - 1)];
+          v[u] = t < P ? ge[(int64_t)(e[u] >> 8) * P + t] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (h + u < end) tile[e[u] & 255][lane] += v[u];
       }
     }
-  }
-  __syncthreads();
-  // write-out: lanes along v (two columns per lane), eight preterminal rows in flight
-  const int va = v0 + lane, vb = v0 + 64 + lane;
-  const bool oka = va < v1, okb = vb < v1;
-  const int rows = min(64, P - t0);
-  for (int r0 = 0; r0 < rows; r0 += 8) {
-    float ea[8], eb[8], ls[8], ts[8];
+    __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int tr = t0 + min(r0 + u, rows - 1);
-      const int64_t base = (int64_t)tr * V;
-      ea[u] = oka ? emis[base + va] : 0.0f;
-      eb[u] = okb ? emis[base + vb] : 0.0f;
-      ls[u] = lse[tr];
-      ts[u] = tot[tr];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (r0 + u >= rows) break;
-      const int64_t base = (int64_t)(t0 + r0 + u) * V;
-      if (oka) d[base + va] = tile[va - v0][r0 + u] - expf(ea[u] - ls[u]) * ts[u];
-      if (okb) d[base + vb] = tile[vb - v0][r0 + u] - expf(eb[u] - ls[u]) * ts[u];
+    for (int r = 0; r < 16; ++r) {
+      const int row = wave * 16 + r;
+      if (t0 + row >= P) break;
+      float* o = d + (int64_t)(t0 + row) * V + v0;
+      if (lane < nv) o[lane] = tile[lane][row] - expf(ea[r] - ls[row]) * tot[row];
+      if (lane + 64 < nv) o[lane + 64] = tile[lane + 64][row] - expf(eb[r] - ls[row]) * tot[row];
     }
   }
 }
@@ -185,6 +389,11 @@ int check(int N, int P, int V, int B, int n_max, const int32_t* lengths, LenArg*
     la->v[b] = lengths[b];
   }
   return SPCFG_OK;
+}
+
+dim3 tile_grid(int P, int V) {
+  const int chunks = (V + kVChunk - 1) / kVChunk;
+  return dim3((P + 63) / 64, chunks < kMaxVBlocks ? chunks : kMaxVBlocks);
 }
 
 int status() { return hipGetLastError() == hipSuccess ? SPCFG_OK : SPCFG_ERR_HIP; }
@@ -207,13 +416,9 @@ int spcfg_rules_forward(int32_t N, int32_t P, int32_t V, const float* root_logit
       !emis_lse)
     return SPCFG_ERR_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
-  const int64_t M = (int64_t)N + P;
-  hipLaunchKernelGGL(k_row_softmax, dim3(1), dim3(256), 0, st, root_logits, (int64_t)N, log_root, 1);
-  hipLaunchKernelGGL(k_row_softmax, dim3(N), dim3(256), 0, st, L_logits, M, L, 0);
-  hipLaunchKernelGGL(k_row_softmax, dim3(N), dim3(256), 0, st, R_logits, M, R, 0);
-  hipLaunchKernelGGL(k_row_softmax, dim3(P), dim3(256), 0, st, emis_logits, (int64_t)V, emis_lse, 2);
-  hipLaunchKernelGGL(k_gather_emit, dim3(B * n_max), dim3(256), 0, st, la, n_max, P, V, emis_logits, emis_lse, tokens,
-                     log_emit);
+  hipLaunchKernelGGL(k_rows_forward, dim3(P + 2 * N + 1), dim3(256), 0, st, N, P, (int64_t)V, root_logits, L_logits, R_logits,
+                     emis_logits, log_root, L, R, emis_lse);
+  hipLaunchKernelGGL(k_gather_emit, dim3(B * n_max), dim3(256), 0, st, la, n_max, P, V, emis_logits, emis_lse, tokens, log_emit);
   return status();
 }
 
@@ -230,15 +435,11 @@ int spcfg_rules_backward(int32_t N, int32_t P, int32_t V, const float* log_root,
       !grad_log_emit || !grad_root_logits || !grad_L_logits || !grad_R_logits || !grad_emis_logits || !scratch)
     return SPCFG_ERR_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
-  const int64_t M = (int64_t)N + P;
-  hipLaunchKernelGGL(k_logsoftmax_bwd, dim3(1), dim3(256), 0, st, log_root, grad_log_root, N, grad_root_logits);
-  hipLaunchKernelGGL(k_softmax_bwd, dim3(N), dim3(256), 0, st, L, grad_L, M, grad_L_logits);
-  hipLaunchKernelGGL(k_softmax_bwd, dim3(N), dim3(256), 0, st, R, grad_R, M, grad_R_logits);
-  hipLaunchKernelGGL(k_emit_colsum_part, dim3((P + 63) / 64, kColChunks), dim3(64), 0, st, la, B, n_max, P,
-                     grad_log_emit, scratch);
-  hipLaunchKernelGGL(k_emit_colsum_final, dim3((P + 255) / 256), dim3(256), 0, st, P, scratch);
-  hipLaunchKernelGGL(k_emis_grad, dim3((P + 63) / 64, (V + kVChunk - 1) / kVChunk), dim3(64), 0, st, la, B, n_max, P, V,
-                     tokens, grad_log_emit, emis_logits, emis_lse, scratch, grad_emis_logits);
+  hipLaunchKernelGGL(k_rows_backward, dim3((P + 63) / 64 * (kColChunks / 4) + 2 * N + 1), dim3(256), 0, st, la, B, n_max, N, P,
+                     log_root, L, R, grad_log_root, grad_L, grad_R, grad_log_emit, grad_root_logits, grad_L_logits,
+                     grad_R_logits, scratch);
+  hipLaunchKernelGGL(k_emis_grad, tile_grid(P, V), dim3(256), 0, st, la, B, n_max, P, V, tokens, grad_log_emit, emis_logits,
+                     emis_lse, scratch, grad_emis_logits);
   return status();
 }
 
