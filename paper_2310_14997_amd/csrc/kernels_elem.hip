@@ -790,6 +790,135 @@ k_split_fwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   }
 }
 
+// Sentence and start of a workgroup's span: from the block index alone (starts > 0: a workgroup for every start of the longest
+// sentence, in every sentence), or from the row tables, one dependent load more and no workgroup without a span.
+__device__ __forceinline__ void few_span(int starts, int64_t row0, const int32_t* __restrict__ row_b,
+                                         const int32_t* __restrict__ row_i, int* b, int* i) {
+  if (starts > 0) {
+    *b = blockIdx.x / starts;
+    *i = blockIdx.x % starts;
+  } else {
+    *b = row_b[row0 + blockIdx.x];
+    *i = row_i[row0 + blockIdx.x];
+  }
+}
+
+// The same sum for launches with too few spans to fill the chip, where a launch costs its chain of dependent loads and not
+// its bytes: the split points of a (span, 256 nonterminals) are shared by the W wavefronts of one workgroup, U to each, and
+// all row loads of the span are in flight at once (W * U >= split points, at most 64).  The staging needs no LDS: in
+// every wavefront lane t holds split point t's rows and exponents, the row addresses go out (readlane) before the
+// exponents are looked up, and the partial sums meet in LDS in a fixed order.  Every dependent load costs most of a
+// microsecond here (what the launch before wrote is in no L2), so sentence and start come from the block index and row
+// tables are read for both cases that the sentence's length decides: three loads deep instead of six.
+template <int W, int U>
+__global__ void __launch_bounds__(64 * W)
+k_split_fwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row_b, const int32_t* __restrict__ row_i,
+                int B, int Np, int64_t S1, int stride, const int32_t* __restrict__ lens,
+                const int32_t* __restrict__ rowtab, const float* __restrict__ HZ,
+                float* __restrict__ T, int32_t* __restrict__ mexp, uint32_t* __restrict__ tmaxb, void* __restrict__ Tb,
+                int planes, int64_t plane_stride, int32_t* __restrict__ hmaxb, int32_t* __restrict__ zmaxb,
+                const float* __restrict__ colmax, int Pp, int per_sentence, int w0, const int32_t* __restrict__ bexp) {
+  static_assert(W * U <= 64, "one lane per split point");
+  __shared__ float4 s_part[W > 1 ? W - 1 : 1][64];
+  const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int b, i;
+  few_span(starts, row0, row_b, row_i, &b, &i);
+  const int n = lens[b];
+  // (row_of with the length's part left for later: children (i, i+k) never end the sentence, (i+k, i+w) never begin it)
+  const int* tab = rowtab + b;
+  const int own0 = tab[(i == 0 ? 0 : stride) + w * B] + (i == 0 ? 0 : i - 1), own2 = tab[2 * stride + w * B];
+  int lr = 0, rr = 0, rr2 = 0;
+  if (nk > 0) {
+    const int t = min(lane, nk - 1);
+    const int k = (w0 > 0 && t >= w - w0) ? t + 2 * w0 - w : t + 1;
+    lr = tab[(i == 0 ? 0 : stride) + k * B] + (i == 0 ? 0 : i - 1);
+    rr = tab[stride + (w - k) * B] + i + k - 1;
+    rr2 = tab[2 * stride + (w - k) * B];
+  }
+  if (i + w > n) return;  // (uniform over the workgroup: this sentence has fewer spans)
+  const int64_t r = i > 0 && i + w == n ? own2 : own0;
+  if (i + w == n) rr = rr2;
+  const int64_t ld = 2 * (int64_t)Np;
+  const int col = blockIdx.y * kChunk + lane * 4;
+  const int a = min(col, Np - 4);  // lanes past the end load the last columns and store nothing
+  float4 h[U], z[U];
+  const bool some = wave < nk;  // (a wavefront without a split point of its own)
+  if (some) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = min(wave + u * W, nk - 1);
+      h[u] = *reinterpret_cast<const float4*>(HZ + (int64_t)__builtin_amdgcn_readlane(lr, t) * ld + a);
+      z[u] = *reinterpret_cast<const float4*>(HZ + (int64_t)__builtin_amdgcn_readlane(rr, t) * ld + Np + a);
+    }
+  }
+  const int pe = w0 > 0 ? bexp[r] : kExpZero;
+  float4 first = make_float4(0.f, 0.f, 0.f, 0.f), wl = first, wr = first;
+  if (wave == 0) {
+    if (w0 > 0) first = *reinterpret_cast<const float4*>(T + (r - S1) * Np + a);
+    const float* cmL = colmax + (int64_t)(per_sentence ? b : 0) * 2 * (Np + Pp) + a;
+    wl = *reinterpret_cast<const float4*>(cmL);
+    wr = *reinterpret_cast<const float4*>(cmL + Np + Pp);
+  }
+  int d = kExpZero, gh = 0, gz = 0;
+  if (nk > 0) {
+    const uint32_t tl = tmaxb[lr], tr = tmaxb[rr];
+    const int hl = hmaxb[lr], zr = zmaxb[rr];
+    d = add_exp(proj_exp(mexp[lr], tl, hl), proj_exp(mexp[rr], tr, zr));
+    gh = proj_shift(tl, hl);
+    gz = proj_shift(tr, zr);
+  }
+  const int m = max(wave_max_i(d), pe);
+  const int c = __float_as_int(d == kExpZero ? 0.0f : pow2i(d - m - gh));
+  const int cz = __float_as_int(d == kExpZero ? 0.0f : pow2i(-gz));
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (wave == 0 && w0 > 0) {
+    const float cp = pe == kExpZero ? 0.0f : pow2i(pe - m);
+    acc = make_float4(cp * first.x, cp * first.y, cp * first.z, cp * first.w);
+  }
+  if (some) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = wave + u * W;
+      if (t < nk) {
+        const float ct = __int_as_float(__builtin_amdgcn_readlane(c, t)), czt = __int_as_float(__builtin_amdgcn_readlane(cz, t));
+        acc.x = fmaf(ct * h[u].x, czt * z[u].x, acc.x);
+        acc.y = fmaf(ct * h[u].y, czt * z[u].y, acc.y);
+        acc.z = fmaf(ct * h[u].z, czt * z[u].z, acc.z);
+        acc.w = fmaf(ct * h[u].w, czt * z[u].w, acc.w);
+      }
+    }
+  }
+  if (W > 1) {
+    if (wave > 0) s_part[wave - 1][lane] = acc;
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int q = 0; q < W - 1; ++q) {
+      const float4 o = s_part[q][lane];
+      acc.x += o.x; acc.y += o.y; acc.z += o.z; acc.w += o.w;
+    }
+  }
+  float tmax = 0.0f;
+  int hsum = 0, zsum = 0;
+  if (col < Np) {
+    *reinterpret_cast<float4*>(T + (r - S1) * Np + a) = acc;
+    if (Tb) store_planes4(Tb, planes, plane_stride, (r - S1) * Np + a, acc);
+    tmax = fmaxf(fmaxf(acc.x, acc.y), fmaxf(acc.z, acc.w));
+    hsum = max(max(bexp_sum(wl.x, acc.x), bexp_sum(wl.y, acc.y)), max(bexp_sum(wl.z, acc.z), bexp_sum(wl.w, acc.w)));
+    zsum = max(max(bexp_sum(wr.x, acc.x), bexp_sum(wr.y, acc.y)), max(bexp_sum(wr.z, acc.z), bexp_sum(wr.w, acc.w)));
+  }
+  tmax = wave_max(tmax);
+  hsum = wave_max_i(hsum);
+  zsum = wave_max_i(zsum);
+  if (lane == 0) {
+    if (tmax > 0.0f && m != kExpZero) atomicMax(&tmaxb[r], __float_as_uint(tmax));
+    if (hsum > 0 && m != kExpZero) atomicMax(&hmaxb[r], hsum);
+    if (zsum > 0 && m != kExpZero) atomicMax(&zmaxb[r], zsum);
+    if (blockIdx.y == 0) mexp[r] = m;
+  }
+}
+
 // ------------------------------------------------------------------------------------------ root
 // Z = sum_A pi(S->A) beta_0n[A] (rule S -> A, Sec. 2).
 __global__ void k_root_fwd(int B, int N, int Np, int64_t S1, const int32_t* __restrict__ lens,
@@ -1036,6 +1165,131 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   }
 }
 
+// The reverse sums for launches with few spans, shared by W wavefronts as in k_split_fwd_few: lane t of every wavefront
+// holds parent t (right-child roles first: their number does not depend on the sentence's length), wavefront q takes the
+// parents q, q + W, ...
+template <int W, int U>
+__global__ void __launch_bounds__(64 * W)
+k_split_bwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row_b, const int32_t* __restrict__ row_i,
+                int n_long, int B, int Np, int64_t S1, int stride, const int32_t* __restrict__ lens,
+                const int32_t* __restrict__ rowtab, const float* __restrict__ HZ, const float* __restrict__ BH, const int32_t* __restrict__ mexp,
+                const uint32_t* __restrict__ tmaxb, float* __restrict__ UV, int32_t* __restrict__ uexp,
+                uint32_t* __restrict__ umaxb, float* __restrict__ gsc, void* __restrict__ UVb, int planes,
+                int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb, int wt,
+                const int32_t* __restrict__ bexp, int64_t Sall) {
+  static_assert(W * U <= 64, "one lane per parent");
+  __shared__ float4 s_part[W > 1 ? W : 1][2][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int b, i;
+  few_span(starts, row0, row_b, row_i, &b, &i);
+  const int n = lens[b], j = i + w;
+  const int most = wt > 0 ? wt - 1 - w : n_long;
+  const int nr = min(i, most);  // parents (i', j), i' = i - nr .. i - 1; then the parents (i, j'), j' = j + 1 ..
+  // row_of for parent and sibling with the length's part left for later: row 2 is that of a span that ends the sentence
+  const int* tab = rowtab + b;
+  const int own0 = tab[(i == 0 ? 0 : stride) + w * B] + (i == 0 ? 0 : i - 1), own2 = tab[2 * stride + w * B];
+  const bool left = lane >= nr;
+  const int ip = i - nr + lane, jp = j + 1 + lane - nr;
+  const int p_at = left ? i : ip, p_w = min(left ? jp - i : j - ip, n_long);
+  const int s_at = left ? j : ip, s_w = min(left ? jp - j : i - ip, n_long);
+  int pr = tab[(p_at == 0 ? 0 : stride) + p_w * B] + (p_at == 0 ? 0 : p_at - 1);
+  int sr = tab[(s_at == 0 ? 0 : stride) + s_w * B] + (s_at == 0 ? 0 : s_at - 1);
+  const int pr2 = tab[2 * stride + p_w * B], sr2 = tab[2 * stride + s_w * B];
+  if (i + w > n || w == n) return;  // (uniform) no such span, or a root: it has no parent, its adjoint comes from k_root_bwd
+  const int64_t r = i > 0 && j == n ? own2 : own0;
+  const int nl = min(n - j, most), nt = nl + nr;
+  if (p_at > 0 && (left ? jp : j) == n) pr = pr2;
+  if (left && jp == n) sr = sr2;
+  if (lane >= nt) { pr = (int)S1; sr = 0; }
+  const int64_t ld = 2 * (int64_t)Np;
+  const int col = blockIdx.y * kChunk + lane * 4;
+  const int a = min(col, Np - 4);
+  float4 gq[U], sq[U];
+  const bool some = wave < nt;
+  if (some) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = min(wave + u * W, nt - 1);
+      gq[u] = *reinterpret_cast<const float4*>(BH + ((int64_t)__builtin_amdgcn_readlane(pr, t) - S1) * Np + a);
+      sq[u] = *reinterpret_cast<const float4*>(HZ + (int64_t)__builtin_amdgcn_readlane(sr, t) * ld + (t >= nr ? Np : 0) + a);
+    }
+  }
+  const int peu = wt > 0 ? bexp[r] : kExpZero, pev = wt > 0 ? bexp[Sall + r] : kExpZero;
+  float4 u0 = make_float4(0.f, 0.f, 0.f, 0.f), v0 = u0;
+  if (wave == 0 && wt > 0) {
+    u0 = *reinterpret_cast<const float4*>(UV + r * ld + a);
+    v0 = *reinterpret_cast<const float4*>(UV + r * ld + Np + a);
+  }
+  const int me = mexp[r];
+  int d = kExpZero;
+  float cs_lane = 0.0f;
+  if (lane < nt) {
+    const int sb = left ? zmaxb[sr] : hmaxb[sr];
+    const uint32_t tb = tmaxb[sr];
+    d = add_exp(norm_exp(uexp[pr], umaxb[pr]), proj_exp(mexp[sr], tb, sb));
+    cs_lane = d == kExpZero ? 0.0f : pow2i(-proj_shift(tb, sb));
+  }
+  const int m = max(wave_max_i(d), max(peu, pev));
+  const int c = __float_as_int(d == kExpZero ? 0.0f : pow2i(d - m)), cs = __float_as_int(cs_lane);
+  float4 x[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+  if (wave == 0 && wt > 0) {
+    const float cu = peu == kExpZero ? 0.0f : pow2i(peu - m), cv = pev == kExpZero ? 0.0f : pow2i(pev - m);
+    x[0] = make_float4(cu * u0.x, cu * u0.y, cu * u0.z, cu * u0.w);
+    x[1] = make_float4(cv * v0.x, cv * v0.y, cv * v0.z, cv * v0.w);
+  }
+  if (some) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = wave + u * W;
+      if (t < nt) {
+        const float ct = __int_as_float(__builtin_amdgcn_readlane(c, t)), cst = __int_as_float(__builtin_amdgcn_readlane(cs, t));
+        const float4 p = make_float4(ct * gq[u].x, ct * gq[u].y, ct * gq[u].z, ct * gq[u].w);
+        const float4 q = make_float4(cst * sq[u].x, cst * sq[u].y, cst * sq[u].z, cst * sq[u].w);
+        if (t >= nr) {
+          x[0].x = fmaf(p.x, q.x, x[0].x); x[0].y = fmaf(p.y, q.y, x[0].y);
+          x[0].z = fmaf(p.z, q.z, x[0].z); x[0].w = fmaf(p.w, q.w, x[0].w);
+        } else {
+          x[1].x = fmaf(p.x, q.x, x[1].x); x[1].y = fmaf(p.y, q.y, x[1].y);
+          x[1].z = fmaf(p.z, q.z, x[1].z); x[1].w = fmaf(p.w, q.w, x[1].w);
+        }
+      }
+    }
+  }
+  if (W > 1) {
+    s_part[wave][0][lane] = x[0];
+    s_part[wave][1][lane] = x[1];
+    __syncthreads();
+    if (wave > 1) return;
+  }
+  float amax = 0.0f;
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    if (W > 1 && half != wave) continue;  // with several wavefronts the first writes adj eta, the second adj zeta
+    float4 o = x[half];
+    if (W > 1) {
+      o = s_part[0][half][lane];
+#pragma unroll
+      for (int q = 1; q < W; ++q) {
+        const float4 y = s_part[q][half][lane];
+        o.x += y.x; o.y += y.y; o.z += y.z; o.w += y.w;
+      }
+    }
+    if (col < Np) {
+      *reinterpret_cast<float4*>(UV + r * ld + half * (int64_t)Np + a) = o;
+      if (UVb) store_planes4(UVb, planes, plane_stride, r * ld + half * (int64_t)Np + a, o);
+      amax = fmaxf(amax, fmaxf(fmaxf(fabsf(o.x), fabsf(o.y)), fmaxf(fabsf(o.z), fabsf(o.w))));
+    }
+  }
+  amax = wave_max(amax);
+  if (lane == 0) {
+    if (amax > 0.0f && m != kExpZero) atomicMax(&umaxb[r], __float_as_uint(amax));
+    if (blockIdx.y == 0 && wave == 0) {
+      uexp[r] = m;
+      gsc[r] = (m == kExpZero || me == kExpZero) ? 0.0f : pow2i(max(m + me, -160));
+    }
+  }
+}
+
 // grad_log_emit is zero at padded token positions.
 __global__ void k_zero_pad_emit(int P, int n_max, const int32_t* __restrict__ lens, float* __restrict__ g) {
   const int b = blockIdx.x;
@@ -1175,6 +1429,35 @@ void launch_leaf_prep(const Layout& ly, const Ptrs& p, const float* log_emit, bo
                      (int64_t)ly.S1 * ly.Pp, p.colmax, ly.Np, ly.G > 1 ? 1 : 0, p.hmaxb, p.zmaxb);
 }
 
+namespace {
+// Launches of up to one wavefront per SIMD in the plain form share each span among wavefronts: there a launch costs its chain of
+// dependent loads (B = 7, N = 141, n <= 37: 6.4 us a forward and 6.8 us a reverse launch plain, 4.7 and 5.1 us shared; B = 1,
+// N = 2048, n = 40: 7.2 and 5.4 us forward).  Limits from 512 to 4096 time alike within 0.5 % on whole calls: the plain
+// form has its loads in flight from 1024 wavefronts on as well.
+constexpr int64_t kFewWaves = 1024;
+// Spans by block index (see few_span) while the workgroups, with and without a span, are few enough to start at once.
+int few_starts(const Layout& ly, int w, int chunks) {
+  const int64_t starts = ly.n_long - w + 1;
+  return starts * ly.B * chunks <= kFewWaves ? (int)starts : 0;
+}
+template <typename... A>
+void launch_few_fwd(int terms, dim3 grid, hipStream_t st, A... args) {
+  if (terms <= 4) launch_k(k_split_fwd_few<1, 4>, grid, dim3(64), 0, st, args...);
+  else if (terms <= 8) launch_k(k_split_fwd_few<2, 4>, grid, dim3(128), 0, st, args...);
+  else if (terms <= 16) launch_k(k_split_fwd_few<4, 4>, grid, dim3(256), 0, st, args...);
+  else if (terms <= 32) launch_k(k_split_fwd_few<8, 4>, grid, dim3(512), 0, st, args...);
+  else launch_k(k_split_fwd_few<8, 8>, grid, dim3(512), 0, st, args...);
+}
+template <typename... A>
+void launch_few_bwd(int terms, dim3 grid, hipStream_t st, A... args) {
+  if (terms <= 4) launch_k(k_split_bwd_few<1, 4>, grid, dim3(64), 0, st, args...);
+  else if (terms <= 8) launch_k(k_split_bwd_few<2, 4>, grid, dim3(128), 0, st, args...);
+  else if (terms <= 16) launch_k(k_split_bwd_few<4, 4>, grid, dim3(256), 0, st, args...);
+  else if (terms <= 32) launch_k(k_split_bwd_few<8, 4>, grid, dim3(512), 0, st, args...);
+  else launch_k(k_split_bwd_few<8, 8>, grid, dim3(512), 0, st, args...);
+}
+}  // namespace
+
 void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int64_t rows, bool write_planes,
                       hipStream_t st) {
   void* Tb = write_planes ? p.Tb : nullptr;
@@ -1201,6 +1484,13 @@ void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
   const size_t sh = (size_t)nk * 16;
   const int chunks = (ly.Np + kChunk - 1) / kChunk;
+  const int starts = few_starts(ly, w, chunks);
+  if (rows * chunks <= kFewWaves && nk <= 64) {
+    launch_few_fwd(nk, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.B, ly.Np, ly.S1, stride, p.lens,
+                   p.rowbase, p.HZ, p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
+                   ly.G > 1 ? 1 : 0, w0, p.bexp);
+    return;
+  }
   if (rows * chunks < 1024 && nk >= 64) {  // fewer than one wavefront per SIMD, long chains of split points
     const dim3 grid((unsigned)rows, (unsigned)(ly.Np / 64));
     launch_k(k_split_fwd<4>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
@@ -1256,6 +1546,15 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
       launch_k(k_split_band_bwd<kBandShare>, dim3((unsigned)(ly.Np / 64), ti, z), dim3(kBandShare * 64), lds_sum, st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.BH, p.mexp,
              p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
     }
+  }
+  const int most = band ? 2 * (wt - 1 - w) : ly.n_long - w;  // parents of a span
+  const int chunks = (ly.Np + kChunk - 1) / kChunk;
+  const int starts = few_starts(ly, w, chunks);
+  if (rows * chunks <= kFewWaves && most <= 64) {
+    launch_few_bwd(most, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.n_long, ly.B, ly.Np, ly.S1, stride,
+                   p.lens, p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr,
+                   ly.planes_bwd, ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.bexp, ly.Sall);
+    return;
   }
   const size_t sh = (size_t)(band ? 2 * (wt - 1 - w) : ly.n_max) * 16;
   const dim3 grid((unsigned)rows, (unsigned)((ly.Np + kChunk - 1) / kChunk));
