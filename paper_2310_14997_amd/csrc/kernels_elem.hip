@@ -199,8 +199,12 @@ __global__ void k_plan_rows(int B, int stride, const int32_t* __restrict__ lens,
                             int32_t* __restrict__ row_b, int32_t* __restrict__ row_i,
                             int32_t* __restrict__ rootmask, uint32_t* __restrict__ tmaxb,
                             uint32_t* __restrict__ umaxb, int32_t* __restrict__ hmaxb,
-                            int32_t* __restrict__ zmaxb) {
+                            int32_t* __restrict__ zmaxb, uint32_t* __restrict__ colmax, int64_t n_colmax) {
   const int w = blockIdx.x + 1, b = blockIdx.y;
+  // (the weight packing takes column maxima into these)
+  for (int64_t c = ((int64_t)b * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; c < n_colmax;
+       c += (int64_t)gridDim.x * gridDim.y * blockDim.x)
+    colmax[c] = 0u;
   const int n = lens[b];
   if (w > n) return;
   for (int i = threadIdx.x; i <= n - w; i += blockDim.x) {
@@ -235,62 +239,86 @@ __global__ void k_plan_sentrows(int B, int stride, const int32_t* __restrict__ l
 // Stacks [L;R] (Sec. 3.2, kernel fusion: one matrix product for both projections) into zero-padded,
 // K-contiguous operands: Wn [2Np x Np] / Wp [2Np x Pp] for the forward products and their transposes
 // Wtn [Np x 2Np] / Wtp [Pp x 2Np] for the reverse products.
-// Element store of a packed panel: OutT float or __bf16 writes the value; uint16_t writes the first NPL bf16 pieces
-// of the cut (nt::Split3) into planes `stride` elements apart.  A null panel is skipped.
-template <int NPL, typename OutT> __device__ __forceinline__ void put_w(OutT* w, int64_t, int64_t at, float v) {
-  if (w != nullptr) w[at] = (OutT)v;
-}
-template <int NPL> __device__ __forceinline__ void put_w(uint16_t* w, int64_t stride, int64_t at, float v) {
-  if (w == nullptr) return;
+// The first NPL bf16 pieces of one value's cut (nt::Split3), into planes `stride` elements apart.
+template <int NPL> __device__ __forceinline__ void put_planes(uint16_t* w, int64_t stride, int64_t at, float v) {
   unsigned h, m, l;
   nt::Split3::cut2(v, 0.0f, h, m, l);
   w[at] = (uint16_t)h; w[stride + at] = (uint16_t)m;
   if (NPL == 3) w[2 * stride + at] = (uint16_t)l;
 }
-// OutT = uint16_t: NPL (2 or 3) bf16 planes per panel (plane strides 2Np*Np resp. 2Np*Pp elements; a grammar's
-// panel set is then NPL times as long)
-template <typename OutT, int NPL>
-__global__ void k_pack_weights(const float* __restrict__ L, const float* __restrict__ R, int N, int P, int Np,
-                               int Pp, OutT* __restrict__ Wn, OutT* __restrict__ Wp, OutT* __restrict__ Wtn,
-                               OutT* __restrict__ Wtp, uint32_t* __restrict__ colmax) {
-  const int64_t sn = 2 * (int64_t)Np * Np, sp = 2 * (int64_t)Np * Pp;
-  __shared__ float tile[32][33];
-  const int M = N + P;
+// One kernel writes every panel of a call, so L and R are read once: a 64 x 64 tile of a factor goes out as it lies and,
+// turned in LDS, transposed, four consecutive values per thread and store.  Panels of type FwdT / RevT (float or __bf16; the
+// values rounded to it) and NPLF / NPLR bf16 planes (the first pieces of the cut nt::Split3, 2Np*Np resp. 2Np*Pp
+// elements apart; shared grammars only); a null panel is left out.  Bound by HBM: N = P = 2048, fp32 panels and three planes
+// both ways: 76 us (400 MB, 5.3 TB/s); two kernels with 2- and 4-byte stores took 151 us.
+template <typename T> __device__ __forceinline__ void put_panel4(T* w, int64_t at, float4 v) {
+  if (w == nullptr) return;
+  if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(w + at) = v;
+  else store_bf16x4(w, at, v);
+}
+template <typename FwdT, int NPLF, typename RevT, int NPLR>
+__global__ void __launch_bounds__(256)
+k_pack_weights(const float* __restrict__ L, const float* __restrict__ R, int N, int P, int Np, int Pp, FwdT* __restrict__ Wn,
+               FwdT* __restrict__ Wp, RevT* __restrict__ Wtn, RevT* __restrict__ Wtp, void* __restrict__ Wn3,
+               void* __restrict__ Wp3, void* __restrict__ Wtn3, void* __restrict__ Wtp3, uint32_t* __restrict__ colmax) {
+  __shared__ float tile[64][65];
+  const int64_t M = (int64_t)N + P;
   const int gi = blockIdx.z >> 1, lr = blockIdx.z & 1;  // grammar, left / right factor
   const float* src = (lr ? R : L) + (int64_t)gi * N * M;
-  if (Wn) Wn += (int64_t)gi * NPL * sn;
-  if (Wtn) Wtn += (int64_t)gi * NPL * sn;
-  if (Wp) Wp += (int64_t)gi * NPL * sp;
-  if (Wtp) Wtp += (int64_t)gi * NPL * sp;
-  const int half = lr * Np;
-  const int c0 = blockIdx.x * 32;  // padded column: [0,Np) nonterminal part, [Np, Np+Pp) preterminal part
-  const int a0 = blockIdx.y * 32;
-  const bool ppart = c0 >= Np;
-  const int cc0 = ppart ? c0 - Np : c0;
-  const int tx = threadIdx.x, ty = threadIdx.y;  // 32 x 8
+  const bool ppart = (int)blockIdx.x * 64 >= Np;  // padded columns: [0, Np) nonterminals, [Np, Np + Pp) preterminals
+  const int K = ppart ? Pp : Np, cols = ppart ? P : N;
+  const int c0 = (int)blockIdx.x * 64 - (ppart ? Np : 0), a0 = blockIdx.y * 64;
+  const int64_t plane = 2 * (int64_t)Np * K, half = (int64_t)lr * Np;
+  FwdT* W = ppart ? Wp : Wn;
+  RevT* Wt = ppart ? Wtp : Wtn;
+  if (W != nullptr) W += gi * plane;
+  if (Wt != nullptr) Wt += gi * plane;
+  const int x = (threadIdx.x & 15) * 4, y = threadIdx.x >> 4;
+  if (ppart) src += N;
+  const bool vec = ((uintptr_t)src & 15) == 0 && (M & 3) == 0;
+  float4 v[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int a = a0 + ty + 8 * q, c = cc0 + tx;
-    float v = 0.0f;
-    if (a < N && c < (ppart ? P : N)) v = src[(int64_t)a * M + (ppart ? N + c : c)];
-    tile[ty + 8 * q][tx] = v;
-    if (ppart) put_w<NPL>(Wp, sp, (int64_t)(half + a) * Pp + c, v); else put_w<NPL>(Wn, sn, (int64_t)(half + a) * Np + c, v);
+    const int a = a0 + y + 16 * q, c = c0 + x;
+    const float* s = src + a * M + c;
+    v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (a < N) {
+      if (vec && c + 4 <= cols) {
+        v[q] = *reinterpret_cast<const float4*>(s);
+      } else {
+        if (c < cols) v[q].x = s[0];
+        if (c + 1 < cols) v[q].y = s[1];
+        if (c + 2 < cols) v[q].z = s[2];
+        if (c + 3 < cols) v[q].w = s[3];
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = y + 16 * q;
+    tile[r][x] = v[q].x; tile[r][x + 1] = v[q].y; tile[r][x + 2] = v[q].z; tile[r][x + 3] = v[q].w;
+    const int64_t at = (half + a0 + r) * K + c0 + x;
+    put_panel4(W, at, v[q]);
+    if (NPLF > 0) store_planes4(ppart ? Wp3 : Wn3, NPLF, plane, at, v[q]);
   }
   __syncthreads();
-  if (colmax != nullptr && ty == 0) {
+  if (threadIdx.x < 64) {
     // colmax[(g * 2 + lr) * (Np + Pp) + c] = max_A W[A, c] over the padded columns c (nonterminals [0, Np), then
     // preterminals): feeds the exponent bounds of the projections (see proj_shift).  Weights are non-negative, so the
-    // maximum of the bit patterns is the maximum of the values; the array is zeroed before this kernel.
+    // maximum of the bit patterns is the maximum of the values; the array is zeroed by the span plan.
     float m = 0.0f;
-#pragma unroll
-    for (int q = 0; q < 32; ++q) m = fmaxf(m, tile[q][tx]);
-    if (m > 0.0f) atomicMax(colmax + (int64_t)blockIdx.z * (Np + Pp) + c0 + tx, __float_as_uint(m));
+#pragma unroll 16
+    for (int q = 0; q < 64; ++q) m = fmaxf(m, tile[q][threadIdx.x]);
+    if (m > 0.0f)
+      atomicMax(colmax + (int64_t)blockIdx.z * (Np + Pp) + (int64_t)blockIdx.x * 64 + threadIdx.x, __float_as_uint(m));
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int c = cc0 + ty + 8 * q, a = a0 + tx;
-    const float v = tile[tx][ty + 8 * q];
-    if (ppart) put_w<NPL>(Wtp, sp, (int64_t)c * (2 * Np) + half + a, v); else put_w<NPL>(Wtn, sn, (int64_t)c * (2 * Np) + half + a, v);
+    const int c = y + 16 * q;
+    const float4 t = make_float4(tile[x][c], tile[x + 1][c], tile[x + 2][c], tile[x + 3][c]);
+    const int64_t at = (int64_t)(c0 + c) * (2 * Np) + half + a0 + x;
+    put_panel4(Wt, at, t);
+    if (NPLR > 0) store_planes4(ppart ? Wtp3 : Wtn3, NPLR, plane, at, t);
   }
 }
 
@@ -314,10 +342,6 @@ __global__ void k_zero_plane_rows(uint16_t* __restrict__ planes, int64_t plane_s
   uint16_t* p = planes + (int64_t)blockIdx.y * plane_stride + first;
   for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8; i < count; i += (int64_t)gridDim.x * blockDim.x * 8)
     *reinterpret_cast<uint4*>(p + i) = uint4{0u, 0u, 0u, 0u};  // count and first are multiples of 8 elements
-}
-
-__global__ void k_zero_u32(uint32_t* __restrict__ p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
 // Xt[c][s] = bf16(sc[s] * X[s][c]) for s < S, 0 for S <= s < Spad: the reduction-major operands of the
@@ -370,8 +394,8 @@ __global__ void k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, i
     hs = max(hs, bexp_sum(cmL[t], v));
     zs = max(zs, bexp_sum(cmR[t], v));
     if (leafEb) {
-      if (planes == 3) put_w<3>(leafEb, plane_stride, (int64_t)r * Pp + t, v);
-      else if (planes == 2) put_w<2>(leafEb, plane_stride, (int64_t)r * Pp + t, v);
+      if (planes == 3) put_planes<3>(leafEb, plane_stride, (int64_t)r * Pp + t, v);
+      else if (planes == 2) put_planes<2>(leafEb, plane_stride, (int64_t)r * Pp + t, v);
       else reinterpret_cast<__bf16*>(leafEb)[(int64_t)r * Pp + t] = (__bf16)v;
     }
   }
@@ -1366,7 +1390,8 @@ void launch_plan(const Layout& ly, const Ptrs& p, const LenArg& lens, hipStream_
            p.rootrow,
                      p.counters, ly.n_counters);
   launch_k(k_plan_rows, dim3(ly.n_max, ly.B), dim3(64), 0, st, ly.B, (ly.n_max + 1) * ly.B, p.lens, p.rowbase, p.row_b, p.row_i,
-                     p.rootmask, p.tmaxb, p.umaxb, p.hmaxb, p.zmaxb);
+                     p.rootmask, p.tmaxb, p.umaxb, p.hmaxb, p.zmaxb, reinterpret_cast<uint32_t*>(p.colmax),
+                     2 * (int64_t)(ly.Np + ly.Pp) * ly.G);
 }
 
 void launch_plan_sentrows(const Layout& ly, const Ptrs& p, hipStream_t st) {
@@ -1376,32 +1401,26 @@ void launch_plan_sentrows(const Layout& ly, const Ptrs& p, hipStream_t st) {
 }
 
 void launch_pack_weights(const Layout& ly, const Ptrs& p, const float* L, const float* R, hipStream_t st) {
-  dim3 grid((ly.Np + ly.Pp) / 32, ly.Np / 32, 2 * ly.G);
+  const dim3 grid((ly.Np + ly.Pp) / 64, ly.Np / 64, 2 * ly.G), block(256);
   uint32_t* cm = reinterpret_cast<uint32_t*>(p.colmax);
-  const int64_t ncm = 2 * (int64_t)(ly.Np + ly.Pp) * ly.G;
-  launch_k(k_zero_u32, dim3((unsigned)((ncm + 255) / 256 < 1024 ? (ncm + 255) / 256 : 1024)), dim3(256), 0, st, cm, ncm);
-  if (ly.planes == 3)  // the panels once more as three bf16 planes
-    launch_k(k_pack_weights<uint16_t, 3>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp,
-                       (uint16_t*)p.Wn3, (uint16_t*)p.Wp3, (uint16_t*)p.Wtn3, (uint16_t*)p.Wtp3, (uint32_t*)nullptr);
-  if (ly.planes == 2)  // the panels of the forward products as two bf16 planes
-    launch_k(k_pack_weights<uint16_t, 2>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp,
-                       (uint16_t*)p.Wn3, (uint16_t*)p.Wp3, (uint16_t*)nullptr, (uint16_t*)nullptr, (uint32_t*)nullptr);
-  if (ly.fwd_fp32) {  // fp32 panels for the forward products, bf16 panels for the reverse ones
-    launch_k(k_pack_weights<float, 1>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp, p.Wn, p.Wp,
-                       (float*)nullptr, (float*)nullptr, cm);
-    launch_k(k_pack_weights<__bf16, 1>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp,
-                       (__bf16*)nullptr, (__bf16*)nullptr, (__bf16*)p.Wtn, (__bf16*)p.Wtp, (uint32_t*)nullptr);
-    return;
-  }
-  if (ly.planes == 2)  // single bf16 panels of the reverse products only
-    launch_k(k_pack_weights<__bf16, 1>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp,
-                       (__bf16*)nullptr, (__bf16*)nullptr, (__bf16*)p.Wtn, (__bf16*)p.Wtp, cm);
+  void* none = nullptr;
+  float *Wn = p.Wn, *Wp = p.Wp, *Wtn = p.Wtn, *Wtp = p.Wtp;
+  __bf16 *Wtn_b = reinterpret_cast<__bf16*>(Wtn), *Wtp_b = reinterpret_cast<__bf16*>(Wtp);
+  if (ly.planes == 3)  // fp32 panels, and once more as three bf16 planes
+    launch_k(k_pack_weights<float, 3, float, 3>, grid, block, 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp, Wn, Wp, Wtn, Wtp, p.Wn3,
+             p.Wp3, p.Wtn3, p.Wtp3, cm);
+  else if (ly.fwd_fp32)  // fp32 panels for the forward products, bf16 panels for the reverse ones
+    launch_k(k_pack_weights<float, 0, __bf16, 0>, grid, block, 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp, Wn, Wp, Wtn_b, Wtp_b, none,
+             none, none, none, cm);
+  else if (ly.planes == 2)  // two bf16 planes for the forward products, single bf16 panels for the reverse ones
+    launch_k(k_pack_weights<__bf16, 2, __bf16, 0>, grid, block, 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp, (__bf16*)nullptr,
+             (__bf16*)nullptr, Wtn_b, Wtp_b, p.Wn3, p.Wp3, none, none, cm);
   else if (ly.bf16)
-    launch_k(k_pack_weights<__bf16, 1>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp,
-                       (__bf16*)p.Wn, (__bf16*)p.Wp, (__bf16*)p.Wtn, (__bf16*)p.Wtp, cm);
+    launch_k(k_pack_weights<__bf16, 0, __bf16, 0>, grid, block, 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp,
+             reinterpret_cast<__bf16*>(Wn), reinterpret_cast<__bf16*>(Wp), Wtn_b, Wtp_b, none, none, none, none, cm);
   else
-    launch_k(k_pack_weights<float, 1>, grid, dim3(32, 8), 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp, p.Wn, p.Wp,
-                       p.Wtn, p.Wtp, cm);
+    launch_k(k_pack_weights<float, 0, float, 0>, grid, block, 0, st, L, R, ly.N, ly.P, ly.Np, ly.Pp, Wn, Wp, Wtn, Wtp, none, none,
+             none, none, cm);
 }
 
 void launch_scaled_planes(const float* X, int64_t ld, const float* sc, int64_t S, int64_t Srows, void* planes,
