@@ -292,6 +292,10 @@ void launch_gemm_tn3(const Tn3Args& a, hipStream_t st) {
   if (Gn > a.max_wgs) Gn = a.max_wgs;  // the partial-tile scratch holds 2 * max_wgs slots
   if (Gn > total / 2) Gn = total / 2 > 0 ? total / 2 : 1;
   int ipw = (total + Gn - 1) / Gn;
+  // A tile costs its share's steps in a row, then the last workgroup adds up KT / ipw partial tiles at about half a step's time
+  // each: shares of at least sqrt(KT / 2) steps balance the two when few tiles would be cut for the whole chip.
+  // B = 7, N = 141, n <= 37 (6 tiles of 66 steps): whole call 638 -> 620 us; larger outputs have longer shares anyway.
+  while (2 * (int64_t)ipw * ipw < a.KT) ++ipw;
   Gn = (total + ipw - 1) / ipw;
   launch_k(k_gemm_tn3, dim3(Gn), dim3(256), kLdsTn3, st, a, ipw, total);
 }
