@@ -1,7 +1,7 @@
 """Split-point sums of launches with few spans (k_split_fwd_few / k_split_bwd_few in csrc/kernels_elem.hip): the terms of a
 span shared by the wavefronts of one workgroup.  Against the CPU oracle, with the tolerances of tests/parity_util.py: every
-number of terms from 1 to 47 (all five shapes, with and without idle wavefronts), the last lanes of a block of nonterminals,
-both forms within one pass, bands, one grammar per sentence, bf16 operands."""
+number of terms from 1 to 46 (all five shapes, with and without idle wavefronts), the last lanes of a block of nonterminals,
+both forms within one pass, bands, one grammar per sentence."""
 import numpy as np
 import pytest
 
