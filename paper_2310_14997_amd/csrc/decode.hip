@@ -8,7 +8,11 @@
 // scratch otherwise, and the integer split table likewise (three tables fit up to n_max = 73, two up to 90).
 // Bound by chains, not bytes: the widths follow each other, and so do the steps of the read-out, which one thread walks.
 // So no step waits for memory where the tables are in LDS: the scores are in the chart before the first width, split
-// points and the read-out stack stay in LDS (the by-end chart, which is dead by then): 79 -> 70 us for 64 sentences, n <= 40.
+// points and the read-out stack stay in LDS (the by-end chart, which is dead by then).  A chart in the scratch gains nothing
+// from a copy of the scores.  Where the tables lie is a template parameter (chosen at run time, they would be read through
+// flat addresses), and the maximum over the lanes has no branches (six steps a span; with branches a width took a fifth longer).
+// 64 sentences of 40 / 90 / 100 / 200 words: 57 / 221 / 297 / 1127 us; with tables chosen at run time, branches and
+// no scores in LDS 74 / 275 / 358 / 1371 us.
 #include "spcfg_internal.h"
 
 namespace spcfg {
@@ -17,8 +21,10 @@ namespace {
 constexpr int kDecodeThreads = 1024;
 constexpr size_t kDecodeLdsMax = 64 * 1024;
 
+// kTables: tables in LDS (0 none, 2 the chart, 3 the chart and the split points)
+template <int kTables>
 __global__ void __launch_bounds__(kDecodeThreads)
-k_mbr_decode(LenArg la, int n_max, int use_lds, const float* __restrict__ mu, float* __restrict__ gchart,
+k_mbr_decode(LenArg la, int n_max, const float* __restrict__ mu, float* __restrict__ gchart,
              int32_t* __restrict__ gsplit, int32_t* __restrict__ tree_spans, float* __restrict__ tree_score) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int b = blockIdx.x;
@@ -26,14 +32,16 @@ k_mbr_decode(LenArg la, int n_max, int use_lds, const float* __restrict__ mu, fl
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
   const int64_t nn = (int64_t)n_max * n_max;
   // byS[i * n_max + (k-1)] = best(i,k); byE[(j-1) * n_max + k] = best(k,j)
-  float* byS = use_lds ? reinterpret_cast<float*>(smem) : gchart + (int64_t)b * 2 * nn;
+  float* byS = kTables >= 2 ? reinterpret_cast<float*>(smem) : gchart + (int64_t)b * 2 * nn;
   float* byE = byS + nn;
-  int32_t* split = use_lds == 2 ? reinterpret_cast<int32_t*>(byE + nn) : gsplit + (int64_t)b * nn;
+  int32_t* split = kTables == 3 ? reinterpret_cast<int32_t*>(byE + nn) : gsplit + (int64_t)b * nn;
   const float* m = mu + (int64_t)b * nn;
 
-  for (int e = tid; e < n * n_max; e += blockDim.x) {  // best(i,j) starts as mu(i,j)
-    const int i = e / n_max, j = e - i * n_max + 1;
-    if (j >= i + 2 && j <= n) byS[e] = m[e];
+  if (kTables >= 2) {  // best(i,j) starts as mu(i,j)
+    for (int e = tid; e < n * n_max; e += blockDim.x) {
+      const int i = e / n_max, j = e - i * n_max + 1;
+      if (j >= i + 2 && j <= n) byS[e] = m[e];
+    }
   }
   for (int i = tid; i < n; i += blockDim.x) {  // width 1
     byS[i * n_max + i] = 0.0f;
@@ -55,13 +63,15 @@ k_mbr_decode(LenArg la, int n_max, int use_lds, const float* __restrict__ mu, fl
       for (int o = 32; o > 0; o >>= 1) {
         const float ov = __shfl_xor(bv, o, 64);
         const int ok = __shfl_xor(bk, o, 64);
-        if (ov > bv || (ov == bv && ok < bk)) { bv = ov; bk = ok; }
+        const bool take = (ov > bv) | ((ov == bv) & (ok < bk));  // (no branches in the chain)
+        bv = take ? ov : bv;
+        bk = take ? ok : bk;
       }
       // No candidate compares greater than -inf when every sum is -inf or NaN (scores are the caller's data): the
       // split then defaults to the smallest one, so the table only ever holds split points inside the span.
       if (bk <= i || bk >= j) bk = i + 1;
       if (lane == 0) {
-        const float v = byS[(int64_t)i * n_max + (j - 1)] + bv;
+        const float v = (kTables >= 2 ? byS[(int64_t)i * n_max + (j - 1)] : m[(int64_t)i * n_max + (j - 1)]) + bv;
         byS[(int64_t)i * n_max + (j - 1)] = v;
         byE[(int64_t)(j - 1) * n_max + i] = v;
         split[(int64_t)i * n_max + (j - 1)] = bk;
@@ -115,12 +125,19 @@ int spcfg_mbr_decode(const float* span_post, const int32_t* lengths, int32_t B, 
     la.v[b] = lengths[b];
   }
   const size_t nn = (size_t)n_max * n_max;
-  const int use_lds = 3 * nn * sizeof(float) <= kDecodeLdsMax ? 2 : (2 * nn * sizeof(float) <= kDecodeLdsMax ? 1 : 0);
-  const size_t lds = (size_t)(use_lds + 1) * nn * sizeof(float);
+  const size_t table = nn * sizeof(float);
   float* gchart = static_cast<float*>(scratch);
   int32_t* gsplit = reinterpret_cast<int32_t*>(gchart + 2 * nn * B);
-  hipLaunchKernelGGL(k_mbr_decode, dim3(B), dim3(kDecodeThreads), use_lds ? lds : 0, (hipStream_t)hip_stream, la, n_max,
-                     use_lds, span_post, gchart, gsplit, tree_spans, tree_score);
+  hipStream_t st = (hipStream_t)hip_stream;
+  if (3 * table <= kDecodeLdsMax)
+    hipLaunchKernelGGL(k_mbr_decode<3>, dim3(B), dim3(kDecodeThreads), 3 * table, st, la, n_max, span_post, gchart, gsplit,
+                       tree_spans, tree_score);
+  else if (2 * table <= kDecodeLdsMax)
+    hipLaunchKernelGGL(k_mbr_decode<2>, dim3(B), dim3(kDecodeThreads), 2 * table, st, la, n_max, span_post, gchart, gsplit,
+                       tree_spans, tree_score);
+  else
+    hipLaunchKernelGGL(k_mbr_decode<0>, dim3(B), dim3(kDecodeThreads), 0, st, la, n_max, span_post, gchart, gsplit, tree_spans,
+                       tree_score);
   return hipGetLastError() == hipSuccess ? SPCFG_OK : SPCFG_ERR_HIP;
 }
 
