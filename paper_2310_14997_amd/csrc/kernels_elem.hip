@@ -1449,11 +1449,22 @@ void launch_leaf_prep(const Layout& ly, const Ptrs& p, const float* log_emit, bo
 }
 
 namespace {
-// Launches of up to one wavefront per SIMD in the plain form share each span among wavefronts: there a launch costs its chain of
-// dependent loads (B = 7, N = 141, n <= 37: 6.4 us a forward and 6.8 us a reverse launch plain, 4.7 and 5.1 us shared; B = 1,
-// N = 2048, n = 40: 7.2 and 5.4 us forward).  Limits from 512 to 4096 time alike within 0.5 % on whole calls: the plain
-// form has its loads in flight from 1024 wavefronts on as well.
+// Launches of few wavefronts (in the plain form) share each span among several: there a launch costs its chain of dependent
+// loads (B = 7, N = 141, n <= 37: 6.4 us a forward and 6.8 us a reverse launch plain, 4.7 and 5.1 us shared; B = 1, N = 2048,
+// n = 40: 7.2 and 5.4 us forward).  Every sharing wavefront looks all terms of the span up and keeps its rows in flight, so the
+// form pays while few rows are requested in all: kFewLoads counts them as wavefronts times the form's terms.  Split sums
+// of a pass in us, plain / up to this limit / up to twice as many / with a limit on wavefronts alone: forward B = 8, N = 64,
+// n = 60 428 / 314 / 312 / 315; B = 4, N = 2048, n = 60 689 / 668 / 731 / 793; B = 1, N = 4096, n = 60 579 / 544 / 606 / 607.
+// The reverse form pays up to 1024 nonterminals: B = 1, n = 60 with N = 64 426 / 310 / 316 / 317, N = 1024 488 / 404 / 383 /
+// 393, but N = 2048 484 / 474 / 563 / 566 (B = 2: 640 / 649 / 651 / 825) and N = 4096 687 / 728 / 737 / 1073.
 constexpr int64_t kFewWaves = 1024;
+constexpr int64_t kFewLoads = 16384;
+constexpr int kFewChunksBwd = 4;
+// Terms that the form with room for `terms` has room for (launch_few_fwd, launch_few_bwd)
+int few_slots(int terms) { return terms <= 4 ? 4 : (terms <= 8 ? 8 : (terms <= 16 ? 16 : (terms <= 32 ? 32 : 64))); }
+bool few_pays(int64_t waves, int terms) {
+  return terms <= 64 && waves <= kFewWaves && waves * few_slots(terms) <= kFewLoads;
+}
 // Spans by block index (see few_span) while the workgroups, with and without a span, are few enough to start at once.
 int few_starts(const Layout& ly, int w, int chunks) {
   const int64_t starts = ly.n_long - w + 1;
@@ -1504,7 +1515,7 @@ void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   const size_t sh = (size_t)nk * 16;
   const int chunks = (ly.Np + kChunk - 1) / kChunk;
   const int starts = few_starts(ly, w, chunks);
-  if (rows * chunks <= kFewWaves && nk <= 64) {
+  if (few_pays(rows * chunks, nk)) {
     launch_few_fwd(nk, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.B, ly.Np, ly.S1, stride, p.lens,
                    p.rowbase, p.HZ, p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
                    ly.G > 1 ? 1 : 0, w0, p.bexp);
@@ -1569,7 +1580,7 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   const int most = band ? 2 * (wt - 1 - w) : ly.n_long - w;  // parents of a span
   const int chunks = (ly.Np + kChunk - 1) / kChunk;
   const int starts = few_starts(ly, w, chunks);
-  if (rows * chunks <= kFewWaves && most <= 64) {
+  if (chunks <= kFewChunksBwd && few_pays(rows * chunks, most)) {
     launch_few_bwd(most, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.n_long, ly.B, ly.Np, ly.S1, stride,
                    p.lens, p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr,
                    ly.planes_bwd, ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.bexp, ly.Sall);

@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (300, 20, [35, 2, 18]),     # the second block of nonterminals is nearly empty
     (65, 33, [66, 65, 3]),      # bands late: sums that go on from a partial one, with 0 to 6 terms
     (70, 30, [28] * 90),        # about 2400 spans in the shortest widths, 90 in the last: both forms
+    (20, 10, [60] * 8),         # reverse widths 16 to 27 request too many rows and take the plain form, wider ones do not
+    (1100, 12, [9, 4]),         # five blocks of nonterminals: the reverse sums stay in the plain form
 ])
 def test_shared_grammar(N, P, lens):
     d = synth.make_inputs("tiny", seed=4400 + N, pad_value=np.nan, N=N, P=P, B=len(lens), lengths=lens, V=300)
