@@ -434,7 +434,7 @@ __global__ void k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, i
 // tables are built once for four blocks of nonterminals (60 against 85 us there).
 constexpr int kBandI = 4;
 constexpr int kBandQ = kBandI + kBandW - 1;  // ends of the tile's spans
-constexpr int kBandWaves = 4;    // wavefronts of a workgroup with 64 nonterminals each
+constexpr int kBandWaves = 4;    // wavefronts of a workgroup with 64 nonterminals each, at most
 constexpr int kBandShare = 16;   // wavefronts of a workgroup that share 64 nonterminals
 constexpr int kBandMinWaves = 1536;
 enum { BAND_FWD = 0, BAND_ETA = 1, BAND_ZETA = 2 };
@@ -454,7 +454,8 @@ __device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np,
                                            int64_t out_row0, int32_t* __restrict__ bexp, int32_t* lds, int32_t* s_m) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // KS == 1: every wavefront has 64 nonterminals of its own; KS > 1: KS of them share 64 and take turns in s
-  const int a = (KS > 1 ? (int)blockIdx.x : (int)blockIdx.x * kBandWaves + wave) * 64 + lane;
+  const int waves = KS > 1 ? KS : (int)(blockDim.x >> 6);
+  const int a = (KS > 1 ? (int)blockIdx.x : (int)blockIdx.x * waves + wave) * 64 + lane;
   const int al = min(a, Np - 1);  // (a last workgroup may have wavefronts past the end: they load, and store nothing)
   const int wt = w0 + kBandW;
   // the values of s that some span of the tile uses
@@ -537,7 +538,7 @@ __device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np,
       y_sc[q * S_max + k] = ok[u] ? sc[u] : 0.0f;
     }
   };
-  for (int pq = wave; pq < kBandI + kBandQ; pq += band_threads(KS) / 64) {
+  for (int pq = wave; pq < kBandI + kBandQ; pq += waves) {
     if (S4 <= 64) {
       if (pq < kBandI) fill_x(pq, lane, std::integral_constant<int, 1>{});
       else fill_y(pq - kBandI, lane, std::integral_constant<int, 1>{});
@@ -549,13 +550,13 @@ __device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np,
     }
   }
   __syncthreads();
-  {  // largest exponent of every span's sum: sixteen threads a span
-    const int pair = (tid >> 4) % (kBandI * kBandW), p = pair / kBandW, q = p + pair % kBandW;
+  for (int pair = tid >> 4; pair < kBandI * kBandW; pair += waves * 4) {  // largest exponent of a span's sum: sixteen threads
+    const int p = pair / kBandW, q = p + pair % kBandW;
     int m = kExpZero;
     for (int k = tid & 15; k < S4; k += 16) m = max(m, add_exp(x_max[p * S_max + k], y_exp[q * S_max + k]));
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    if ((tid & 15) == 0 && tid < 16 * kBandI * kBandW) s_m[pair] = m;
+    if ((tid & 15) == 0) s_m[pair] = m;
   }
   __syncthreads();
 
@@ -1488,28 +1489,55 @@ void launch_few_bwd(int terms, dim3 grid, hipStream_t st, A... args) {
 }
 }  // namespace
 
+namespace {
+// The launch of one band: a grid of every tile of the longest sentence, in every sentence.  With enough tiles a wavefront
+// per 64 nonterminals, up to four a workgroup and evenly dealt to the workgroups (at most one of these has a wavefront without
+// nonterminals of its own: with four in each, B = 960, N = 64, n <= 40 spent 831 + 1443 us forward + reverse on split sums, and
+// 694 + 989 us so); otherwise kBandShare wavefronts per 64.  What counts is the tiles that there are, not those of the grid:
+// by the grid's, late bands of mixed lengths took the first form (B = 64, N = 512, n = 2 .. 100: 2187 us forward, 1875 us so).
+struct BandGrid {
+  bool share;
+  dim3 grid, block;
+  size_t lds;
+  int S_max;
+};
+BandGrid band_grid(const Layout& ly, int w0, int S, int roles) {
+  BandGrid g;
+  const int blocks = ly.Np / 64, groups = (blocks + kBandWaves - 1) / kBandWaves;
+  g.share = (int64_t)roles * ly.band_tiles[w0 / kBandW] * blocks < kBandMinWaves;
+  g.grid = dim3((unsigned)(g.share ? blocks : groups), (unsigned)((ly.n_long - w0 + kBandI) / kBandI), (unsigned)(roles * ly.B));
+  g.block = dim3(64u * (unsigned)(g.share ? kBandShare : (blocks + groups - 1) / groups));
+  g.S_max = round_up(S, 4);
+  g.lds = sizeof(int32_t) * (size_t)band_words(g.S_max);
+  const size_t sums = sizeof(float) * (size_t)kBandSumWords;
+  if (g.share && g.lds < sums) g.lds = sums;
+  return g;
+}
+template <int KS>
+void launch_band_fwd(const BandGrid& g, const Layout& ly, const Ptrs& p, int w0, hipStream_t st) {
+  static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_fwd<KS>));
+  (void)attr;
+  launch_k(k_split_band_fwd<KS>, g.grid, g.block, g.lds, st, w0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, g.S_max, p.lens,
+           p.rowbase, p.HZ, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.T, p.bexp);
+}
+template <int KS>
+void launch_band_bwd(const BandGrid& g, const Layout& ly, const Ptrs& p, int w0, hipStream_t st) {
+  static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<KS>));
+  (void)attr;
+  launch_k(k_split_band_bwd<KS>, g.grid, g.block, g.lds, st, w0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, g.S_max, p.lens,
+           p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
+}
+}  // namespace
+
 void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int64_t rows, bool write_planes,
                       hipStream_t st) {
   void* Tb = write_planes ? p.Tb : nullptr;
   const int stride = (ly.n_max + 1) * ly.B;
   const int w0 = ly.band_fwd[w / kBandW] ? w / kBandW * kBandW : 0;
   if (w == w0) {  // the first width of a band: all that its widths can do together
-    const int S_max = round_up(w0 + kBandI, 4);
-    const size_t lds = sizeof(int32_t) * (size_t)band_words(S_max), sums = sizeof(float) * (size_t)kBandSumWords;
-    const size_t lds_sum = lds > sums ? lds : sums;
-    const unsigned ti = (unsigned)((ly.n_long - w0 + kBandI) / kBandI), z = (unsigned)ly.B;
-    if ((int64_t)ti * z * (ly.Np / 64) >= kBandMinWaves) {
-      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_fwd<1>));
-      (void)attr;
-      launch_k(k_split_band_fwd<1>, dim3((unsigned)((ly.Np / 64 + kBandWaves - 1) / kBandWaves), ti, z), dim3(kBandWaves * 64), lds,
-               st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.mexp, p.tmaxb,
-             p.hmaxb, p.zmaxb, p.T, p.bexp);
-    } else {
-      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_fwd<kBandShare>));
-      (void)attr;
-      launch_k(k_split_band_fwd<kBandShare>, dim3((unsigned)(ly.Np / 64), ti, z), dim3(kBandShare * 64), lds_sum, st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.mexp, p.tmaxb,
-             p.hmaxb, p.zmaxb, p.T, p.bexp);
-    }
+    const BandGrid g = band_grid(ly, w0, w0 + kBandI, 1);
+    if (g.share) launch_band_fwd<kBandShare>(g, ly, p, w0, st);
+    else launch_band_fwd<1>(g, ly, p, w0, st);
   }
   const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
   const size_t sh = (size_t)nk * 16;
@@ -1560,22 +1588,9 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   int top = wt - 1 < ly.n_long ? wt - 1 : ly.n_long;
   if (top > ly.n_max - 1) top = ly.n_max - 1;
   if (band && w == top) {
-    const int S_max = round_up(ly.n_long - w0 + kBandI, 4);  // (adj eta: n - wt + 1, adj zeta: n - w0 + 3)
-    const size_t lds = sizeof(int32_t) * (size_t)band_words(S_max), sums = sizeof(float) * (size_t)kBandSumWords;
-    const size_t lds_sum = lds > sums ? lds : sums;
-    const unsigned ti = (unsigned)((ly.n_long - w0 + kBandI) / kBandI), z = (unsigned)(2 * ly.B);
-    if ((int64_t)ti * z * (ly.Np / 64) >= kBandMinWaves) {
-      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<1>));
-      (void)attr;
-      launch_k(k_split_band_bwd<1>, dim3((unsigned)((ly.Np / 64 + kBandWaves - 1) / kBandWaves), ti, z), dim3(kBandWaves * 64), lds,
-               st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.BH, p.mexp,
-             p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
-    } else {
-      static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<kBandShare>));
-      (void)attr;
-      launch_k(k_split_band_bwd<kBandShare>, dim3((unsigned)(ly.Np / 64), ti, z), dim3(kBandShare * 64), lds_sum, st, w0, ly.B, ly.Np, ly.S1, stride, S_max, p.lens, p.rowbase, p.HZ, p.BH, p.mexp,
-             p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
-    }
+    const BandGrid g = band_grid(ly, w0, ly.n_long - w0 + kBandI, 2);  // (adj eta: n - wt + 1 values of s, adj zeta: n - w0 + 3)
+    if (g.share) launch_band_bwd<kBandShare>(g, ly, p, w0, st);
+    else launch_band_bwd<1>(g, ly, p, w0, st);
   }
   const int most = band ? 2 * (wt - 1 - w) : ly.n_long - w;  // parents of a span
   const int chunks = (ly.Np + kChunk - 1) / kChunk;

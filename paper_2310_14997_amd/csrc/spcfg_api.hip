@@ -172,9 +172,10 @@ void choose_bands(const Plan& plan, Layout* ly) {
     for (int b = 0; b < ly->B; ++b) {
       const int n = plan.lens.v[b];
       if (n < w0 || n < 2) continue;
-      const double tiles = (n - w0 + kBandW) / kBandW;
-      fwd -= tiles * (2 * kBandW + 3) * (w0 + 2);
-      bwd -= tiles * (2 * kBandW + 3) * (n - w0);
+      const int tiles = (n - w0 + kBandW) / kBandW;
+      ly->band_tiles[k] += tiles;
+      fwd -= (double)tiles * (2 * kBandW + 3) * (w0 + 2);
+      bwd -= (double)tiles * (2 * kBandW + 3) * (n - w0);
       for (int w = w0 > 0 ? w0 : 1; w < wt && w <= n; ++w) {
         const double spans = n - w + 1;
         fwd += spans * (2.0 * (w - 1) - 4.0 * (w - w0) - 2.0);

@@ -74,6 +74,7 @@ struct Layout {
   // bands: widths kBandW * k .. + kBandW - 1 take their split-point sums (reverse: parent sums) partly in one pass
   int n_long;                   // longest sentence of the batch (n_max may be larger)
   uint8_t band_fwd[kMaxLen / kBandW + 1], band_bwd[kMaxLen / kBandW + 1];
+  int32_t band_tiles[kMaxLen / kBandW + 1];  // its tiles of kBandW starts, over all sentences
   int n_counters;
   int gemm_wgs;          // workgroups the partial-tile scratch is sized for (kGemmWgs, fewer for the static scratch)
   size_t total;

@@ -8,7 +8,7 @@ import torch
 from oracle import spcfg_oracle as O
 from paper_2310_14997_amd import binding as bd
 from paper_2310_14997_amd import synth
-from parity_util import check_all, check_grad, check_logZ
+from parity_util import check_all, check_grad, check_logZ, oracle_batch_parallel
 
 pytestmark = pytest.mark.gpu
 
@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
     (7, 9, [52, 51, 50, 53], 60),            # band ends inside the longest sentence; padding beyond it
     (65, 20, [63, 17, 64, 3, 62], None),     # two blocks of nonterminals; sentences shorter than every band
     (200, 33, [57], 58),                     # one sentence; n_max one above it
-    (300, 65, [14] * 24 + [40] * 20, None),  # enough terms for bands at every width; a wavefront per 64 nonterminals
+    (300, 65, [14] * 24 + [40] * 20, None),  # reverse bands of the shortest widths; a wavefront per 64 nonterminals
+    (310, 20, [48] * 60, None),              # the same forward: five blocks of nonterminals dealt to six wavefronts
+    (180, 12, [60] * 70, None),              # three wavefronts a workgroup; late bands with sixteen that share a block
 ])
 def test_shared_grammar(N, P, lens, n_max):
     d = synth.make_inputs("tiny", seed=4200 + N, pad_value=np.nan, N=N, P=P, B=len(lens), lengths=lens, V=300)
@@ -31,7 +33,9 @@ def test_shared_grammar(N, P, lens, n_max):
     wl.workspace.fill_(255)  # nothing is read before it is written
     g = np.linspace(-1.0, 2.0, len(lens)).astype(np.float32)
     wl.forward_backward(torch.tensor(g, device="cuda:0"))
-    check_all(wl.results(), O.inside_backward(d["log_root"], d["L"], d["R"], d["log_emit"], d["lengths"], g))
+    many = len(lens) >= 60
+    ref = oracle_batch_parallel(d, g) if many else O.inside_backward(d["log_root"], d["L"], d["R"], d["log_emit"], d["lengths"], g)
+    check_all(wl.results(), ref)
 
 
 def test_one_grammar_per_sentence():
