@@ -22,10 +22,19 @@ struct Plan {            // host-side copy of the span schedule
   LenArg lens;
 };
 
-// 50 MB are about 10 us, the cost of one more dependent launch with its tables: with bands from 25 MB on, the forward pass at
-// B = 64, N = 2048, n <= 40 lost 3 % instead of gaining 1 %
-constexpr double kBandBytes = 50e6;
+// When a band of widths pays (choose_bands): bytes of row reads saved, less kBandTables for every tile and value of s (its
+// tables take eleven dependent lookups, whatever N is), against what another dependent launch costs.  Fitted to 1006 bands a
+// direction timed with and without, N = 64 .. 2048, B = 8 .. 960, n = 36 .. 100: with this rule no batch's split sums take more
+// than 2.3 % longer than without bands.  With 50 MB and no charge for the tables, which is right for N >= 512, batches of small
+// grammars lost up to 17 % (B = 128, N = 128, n = 10 .. 60 forward: 568 us without bands, 662 us with, 562 us by this rule;
+// B = 960, N = 64, n <= 40 reverse: 893, 1007 and 893 us); from kBandManyWaves wavefronts on (N = 2048, B = 64) 50 MB pay.
+constexpr double kBandTables = 3072;
+constexpr double kBandBytes = 100e6, kBandBytesMany = 50e6;
+constexpr int64_t kBandManyWaves = 16384;
+// Long chains of few spans are latency, not bytes: from this many split points (parents) on they pay while the band has fewer
+// wavefronts than kBandFewWaves in the form with 64 nonterminals a wavefront.
 constexpr int kBandChain = 48;
+constexpr int64_t kBandFewWaves = 768;
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -160,22 +169,22 @@ Ptrs resolve(const Layout& ly, void* ws) {
 }
 
 // Which bands of widths sum together (k_split_band_fwd / _bwd).  A band saves rows read (of Np floats) and costs a launch
-// of its own, the partial sums' rows written and read, and rows read for spans that a tile lacks; counted exactly here,
-// per tile of four starts.  It pays from kBandBytes saved on (see there); long chains of few spans are latency, not
-// bytes, and pay from 48 split points (or parents) on.
+// of its own, the partial sums' rows written and read, rows read for spans that a tile lacks, and its tables; counted exactly
+// here, per tile of four starts.
 void choose_bands(const Plan& plan, Layout* ly) {
   ly->n_long = 2;
   for (int b = 0; b < ly->B; ++b) ly->n_long = plan.lens.v[b] > ly->n_long ? plan.lens.v[b] : ly->n_long;
   for (int k = 0; k * kBandW < ly->n_long; ++k) {
     const int w0 = k * kBandW, wt = w0 + kBandW;
-    double fwd = 0, bwd = 0;  // rows saved
+    double fwd = 0, bwd = 0;              // rows saved
+    double fwd_steps = 0, bwd_steps = 0;  // values of s, over all tiles
     for (int b = 0; b < ly->B; ++b) {
       const int n = plan.lens.v[b];
       if (n < w0 || n < 2) continue;
       const int tiles = (n - w0 + kBandW) / kBandW;
       ly->band_tiles[k] += tiles;
-      fwd -= (double)tiles * (2 * kBandW + 3) * (w0 + 2);
-      bwd -= (double)tiles * (2 * kBandW + 3) * (n - w0);
+      fwd_steps += (double)tiles * (w0 + 2);
+      bwd_steps += (double)tiles * (n - w0);
       for (int w = w0 > 0 ? w0 : 1; w < wt && w <= n; ++w) {
         const double spans = n - w + 1;
         fwd += spans * (2.0 * (w - 1) - 4.0 * (w - w0) - 2.0);
@@ -183,9 +192,16 @@ void choose_bands(const Plan& plan, Layout* ly) {
         bwd += spans * (2.0 * (n - w) - 4.0 * near - 4.0);
       }
     }
+    fwd -= (2 * kBandW + 3) * fwd_steps;
+    bwd -= (2 * kBandW + 3) * bwd_steps;
+    const int64_t waves = (int64_t)ly->band_tiles[k] * (ly->Np / 64);
+    auto pays = [&](double rows, double steps, int64_t launch_waves, bool chain) {
+      return 4.0 * ly->Np * rows - kBandTables * steps >= (launch_waves >= kBandManyWaves ? kBandBytesMany : kBandBytes) ||
+             (chain && launch_waves < kBandFewWaves);
+    };
     // (below width 8 most split points have a child inside the band)
-    ly->band_fwd[k] = w0 >= 2 * kBandW && (4.0 * ly->Np * fwd >= kBandBytes || w0 >= kBandChain);
-    ly->band_bwd[k] = 4.0 * ly->Np * bwd >= kBandBytes || ly->n_long - w0 >= kBandChain;
+    ly->band_fwd[k] = w0 >= 2 * kBandW && pays(fwd, fwd_steps, waves, w0 >= kBandChain);
+    ly->band_bwd[k] = pays(bwd, bwd_steps, 2 * waves, ly->n_long - w0 >= kBandChain);
   }
 }
 

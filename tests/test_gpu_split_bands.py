@@ -1,10 +1,11 @@
 """Bands of widths (k_split_band_fwd / k_split_band_bwd in csrc/kernels_elem.hip): partial split-point sums of four
 widths in one pass, the rest by the launch of each width.  Against the CPU oracle, with the tolerances of
-tests/parity_util.py, at the sizes where the bands' tables, tiles and ranges end."""
+tests/parity_util.py, at the sizes where the bands' tables, tiles and ranges end; every case asserts which forms it reaches."""
 import numpy as np
 import pytest
 import torch
 
+import band_rule
 from oracle import spcfg_oracle as O
 from paper_2310_14997_amd import binding as bd
 from paper_2310_14997_amd import synth
@@ -13,17 +14,19 @@ from parity_util import check_all, check_grad, check_logZ, oracle_batch_parallel
 pytestmark = pytest.mark.gpu
 
 
-# sentences of 48 words and more take their late widths in bands whatever the grammar's size
-@pytest.mark.parametrize("N,P,lens,n_max", [
-    (7, 9, [49, 48, 2], None),               # one band forward: its first width only, and only in one sentence
-    (7, 9, [52, 51, 50, 53], 60),            # band ends inside the longest sentence; padding beyond it
-    (65, 20, [63, 17, 64, 3, 62], None),     # two blocks of nonterminals; sentences shorter than every band
-    (200, 33, [57], 58),                     # one sentence; n_max one above it
-    (300, 65, [14] * 24 + [40] * 20, None),  # reverse bands of the shortest widths; a wavefront per 64 nonterminals
-    (310, 20, [48] * 60, None),              # the same forward: five blocks of nonterminals dealt to six wavefronts
-    (180, 12, [60] * 70, None),              # three wavefronts a workgroup; late bands with sixteen that share a block
+# forms: wavefronts that share 64 nonterminals in the case's forward and reverse bands.  Sentences of 48 words and more take
+# their late widths in bands whatever the grammar's size.
+@pytest.mark.parametrize("N,P,lens,n_max,forms", [
+    (7, 9, [49, 48, 2], None, ({16}, {16})),                # one band forward: its first width only, and only in one sentence
+    (7, 9, [52, 51, 50, 53], 60, ({16}, {16})),             # band ends inside the longest sentence; padding beyond it
+    (65, 20, [63, 17, 64, 3, 62], None, ({16}, {16})),      # two blocks of nonterminals; sentences shorter than every band
+    (200, 33, [57], 58, ({16}, {16})),                      # one sentence; n_max one above it
+    (300, 65, [14] * 24 + [40] * 20, None, (set(), set())),  # too few rows saved for any band
+    (310, 20, [48] * 60 + [21, 5], None, ({1}, {1})),       # five blocks of nonterminals dealt to six wavefronts; short sentences
+    (180, 12, [60] * 70, None, ({1, 16}, {1})),             # three wavefronts a workgroup; late bands with sixteen that share a block
 ])
-def test_shared_grammar(N, P, lens, n_max):
+def test_shared_grammar(N, P, lens, n_max, forms):
+    assert tuple(set(x.values()) for x in band_rule.choose(N, lens)) == forms
     d = synth.make_inputs("tiny", seed=4200 + N, pad_value=np.nan, N=N, P=P, B=len(lens), lengths=lens, V=300)
     if n_max is not None:
         more = np.full((d["B"], n_max - d["n_max"], P), np.nan, dtype=np.float32)
