@@ -411,6 +411,18 @@ __global__ void k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, i
 }
 
 // ------------------------------------------------------------------------------------------ bands of widths
+// Where the exponents of row r's partial sums of the reverse pass lie (which: 0 adjoint of eta, 1 of zeta): in the row's place
+// of BH until its reverse product, for leaf rows in two arrays that the reverse pass does not read.
+struct BwdPartExp {
+  float* BH;
+  float* xs;
+  int32_t* rootmask;
+  __device__ __forceinline__ int32_t* at(int which, int64_t r, int64_t S1, int Np) const {
+    if (r >= S1) return reinterpret_cast<int32_t*>(BH + (r - S1) * Np) + which;
+    return which ? rootmask + r : reinterpret_cast<int32_t*>(xs) + r;
+  }
+};
+
 // Most of the split-point sums of kBandW consecutive widths w0 .. w0 + kBandW - 1 in one pass, before the first of them
 // (forward), resp. before the last of them (reverse), is finished.  A launch per width reads two rows per term: span
 // (i, j) needs the rows eta(i, .) and zeta(., j), and no other span of its width shares one.  Spans of neighbouring
@@ -421,7 +433,7 @@ __global__ void k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, i
 // so for each s the wavefront loads 4 rows X(i, s) and 7 rows Y(s, j) and uses them for 16 terms: 0.69 rows a term
 // instead of 2.  The few terms that touch the band itself (at most 2 * (w - w0) forward, w0 + kBandW - 1 - w a side
 // in reverse) are left to the kernel of their width, which adds them to this partial sum; the partial sum lies in the row's
-// place in T (UV) with an exponent of its own (bexp).  Every term is scaled by an exact power of two against the largest
+// place in T (UV) with an exponent of its own.  Every term is scaled by an exact power of two against the largest
 // exponent of its own sum, as in the kernels of one width.
 // A workgroup is one tile; with enough of them its four wavefronts have 64 nonterminals each, with few of them (late
 // widths of small batches) they share 64 nonterminals, take every fourth group of four s and meet in LDS in wavefront
@@ -451,7 +463,8 @@ __device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np,
                                            const uint32_t* __restrict__ tmaxb, const int32_t* __restrict__ hmaxb,
                                            const int32_t* __restrict__ zmaxb, const int32_t* __restrict__ uexp,
                                            const uint32_t* __restrict__ umaxb, float* __restrict__ out, int64_t out_ld,
-                                           int64_t out_row0, int32_t* __restrict__ bexp, int32_t* lds, int32_t* s_m) {
+                                           int64_t out_row0, int32_t* __restrict__ fwd_exp, const BwdPartExp& bwd_exp, int32_t* lds,
+                                           int32_t* s_m) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // KS == 1: every wavefront has 64 nonterminals of its own; KS > 1: KS of them share 64 and take turns in s
   const int waves = KS > 1 ? KS : (int)(blockDim.x >> 6);
@@ -638,7 +651,8 @@ __device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np,
       if (w == 0 || i + w > n || (ROLE != BAND_FWD && w == n)) continue;
       const int r = row_of(rowtab, stride, B, w, b, i, n);
       if (a < Np) out[(r - out_row0) * out_ld + a] = acc[p][d];
-      if (blockIdx.x == 0 && lane == 0 && (KS > 1 || wave == 0)) bexp[r] = s_m[p * kBandW + d];
+      if (blockIdx.x == 0 && lane == 0 && (KS > 1 || wave == 0))
+        *(ROLE == BAND_FWD ? fwd_exp + r : bwd_exp.at(ROLE == BAND_ZETA, r, S1, Np)) = s_m[p * kBandW + d];
     }
 }
 
@@ -647,13 +661,13 @@ __global__ void __launch_bounds__(band_threads(KS))
 k_split_band_fwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const int32_t* __restrict__ lens,
                  const int32_t* __restrict__ rowtab, const float* __restrict__ HZ, const int32_t* __restrict__ mexp,
                  const uint32_t* __restrict__ tmaxb, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb,
-                 float* __restrict__ T, int32_t* __restrict__ bexp) {
+                 float* __restrict__ T, int32_t* __restrict__ part_exp) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t s_m[kBandI * kBandW];
   const int b = blockIdx.z, n = lens[b], i0 = blockIdx.y * kBandI;
   if (i0 + w0 > n) return;
   split_band<BAND_FWD, KS>(w0, b, i0, B, Np, S1, stride, n, S_max, rowtab, HZ, nullptr, mexp,
-                       tmaxb, hmaxb, zmaxb, nullptr, nullptr, T, Np, S1, bexp, reinterpret_cast<int32_t*>(smem), s_m);
+                       tmaxb, hmaxb, zmaxb, nullptr, nullptr, T, Np, S1, part_exp, BwdPartExp{}, reinterpret_cast<int32_t*>(smem), s_m);
 }
 
 // blockIdx.z: sentence, and which of the two adjoints
@@ -663,17 +677,17 @@ k_split_band_bwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const
                  const int32_t* __restrict__ rowtab, const float* __restrict__ HZ, const float* __restrict__ BH,
                  const int32_t* __restrict__ mexp, const uint32_t* __restrict__ tmaxb, const int32_t* __restrict__ hmaxb,
                  const int32_t* __restrict__ zmaxb, const int32_t* __restrict__ uexp, const uint32_t* __restrict__ umaxb,
-                 float* __restrict__ UV, int32_t* __restrict__ bexp, int64_t Sall) {
+                 float* __restrict__ UV, BwdPartExp part_exp) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int32_t s_m[kBandI * kBandW];
   const int b = blockIdx.z >> 1, n = lens[b], i0 = blockIdx.y * kBandI;
   if (i0 + w0 > n) return;
   if ((blockIdx.z & 1) == 0)
     split_band<BAND_ETA, KS>(w0, b, i0, B, Np, S1, stride, n, S_max, rowtab, HZ, BH, mexp, tmaxb, hmaxb, zmaxb, uexp, umaxb, UV,
-                         2 * (int64_t)Np, 0, bexp, reinterpret_cast<int32_t*>(smem), s_m);
+                         2 * (int64_t)Np, 0, nullptr, part_exp, reinterpret_cast<int32_t*>(smem), s_m);
   else
     split_band<BAND_ZETA, KS>(w0, b, i0, B, Np, S1, stride, n, S_max, rowtab, HZ, BH, mexp, tmaxb, hmaxb, zmaxb, uexp, umaxb,
-                          UV + Np, 2 * (int64_t)Np, 0, bexp + Sall, reinterpret_cast<int32_t*>(smem), s_m);
+                          UV + Np, 2 * (int64_t)Np, 0, nullptr, part_exp, reinterpret_cast<int32_t*>(smem), s_m);
 }
 
 // ------------------------------------------------------------------------------------------ forward split
@@ -695,7 +709,7 @@ k_split_fwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
             const int32_t* __restrict__ row_i, const float* __restrict__ HZ,
             float* __restrict__ T, int32_t* __restrict__ mexp, uint32_t* __restrict__ tmaxb, void* __restrict__ Tb,
             int planes, int64_t plane_stride, int32_t* __restrict__ hmaxb, int32_t* __restrict__ zmaxb,
-            const float* __restrict__ colmax, int Pp, int per_sentence, int w0, const int32_t* __restrict__ bexp) {
+            const float* __restrict__ colmax, int Pp, int per_sentence, int w0, const int32_t* __restrict__ part_exp) {
   extern __shared__ __align__(16) unsigned char smem[];
   // split points of this launch: all w - 1, or (w0 > 0) those with a child of width w0 or more, the rest lies summed in T
   const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
@@ -707,7 +721,7 @@ k_split_fwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   const int64_t r = row0 + blockIdx.x;
   const int b = row_b[r], i = row_i[r];
   const int n = lens[b];
-  const int pe = w0 > 0 ? bexp[r] : kExpZero;
+  const int pe = w0 > 0 ? part_exp[r] : kExpZero;
   int dmax = pe;
   for (int t = lane; t < nk; t += 64) {
     const int k = (w0 > 0 && t >= w - w0) ? t + 2 * w0 - w : t + 1;
@@ -842,7 +856,7 @@ k_split_fwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
                 const int32_t* __restrict__ rowtab, const float* __restrict__ HZ,
                 float* __restrict__ T, int32_t* __restrict__ mexp, uint32_t* __restrict__ tmaxb, void* __restrict__ Tb,
                 int planes, int64_t plane_stride, int32_t* __restrict__ hmaxb, int32_t* __restrict__ zmaxb,
-                const float* __restrict__ colmax, int Pp, int per_sentence, int w0, const int32_t* __restrict__ bexp) {
+                const float* __restrict__ colmax, int Pp, int per_sentence, int w0, const int32_t* __restrict__ part_exp) {
   static_assert(W * U <= 64, "one lane per split point");
   __shared__ float4 s_part[W > 1 ? W - 1 : 1][64];
   const int nk = w0 > 0 ? 2 * (w - w0) : w - 1;
@@ -877,7 +891,7 @@ k_split_fwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
       z[u] = *reinterpret_cast<const float4*>(HZ + (int64_t)__builtin_amdgcn_readlane(rr, t) * ld + Np + a);
     }
   }
-  const int pe = w0 > 0 ? bexp[r] : kExpZero;
+  const int pe = w0 > 0 ? part_exp[r] : kExpZero;
   float4 first = make_float4(0.f, 0.f, 0.f, 0.f), wl = first, wr = first;
   if (wave == 0) {
     if (w0 > 0) first = *reinterpret_cast<const float4*>(T + (r - S1) * Np + a);
@@ -1068,11 +1082,11 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
             const uint32_t* __restrict__ tmaxb, float* __restrict__ UV, int32_t* __restrict__ uexp,
             uint32_t* __restrict__ umaxb, float* __restrict__ gsc, void* __restrict__ UVb, int planes,
             int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb, int wt,
-            const int32_t* __restrict__ bexp, int64_t Sall) {
+            BwdPartExp part_exp) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
   const int64_t r = row0 + blockIdx.x;
-  if (rootmask[r]) return;  // the root span has no parent; its adjoint comes from k_root_bwd
+  if (w > 1 && rootmask[r]) return;  // the root span has no parent; its adjoint comes from k_root_bwd (no leaf is a root)
   const int b = row_b[r], i = row_i[r];
   const int n = lens[b];
   const int j = i + w;
@@ -1086,7 +1100,7 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   int32_t* s_p = reinterpret_cast<int32_t*>(s_cs + nt);    // [nt] parent row (index into BH: row - S1)
   int32_t* s_s = s_p + nt;                                 // [nt] sibling row
 
-  const int peu = wt > 0 ? bexp[r] : kExpZero, pev = wt > 0 ? bexp[Sall + r] : kExpZero;
+  const int peu = wt > 0 ? *part_exp.at(0, r, S1, Np) : kExpZero, pev = wt > 0 ? *part_exp.at(1, r, S1, Np) : kExpZero;
   int dmax = max(peu, pev);
   for (int t = lane; t < nt; t += 64) {
     int pr, sr;
@@ -1201,7 +1215,7 @@ k_split_bwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
                 const uint32_t* __restrict__ tmaxb, float* __restrict__ UV, int32_t* __restrict__ uexp,
                 uint32_t* __restrict__ umaxb, float* __restrict__ gsc, void* __restrict__ UVb, int planes,
                 int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb, int wt,
-                const int32_t* __restrict__ bexp, int64_t Sall) {
+                BwdPartExp part_exp) {
   static_assert(W * U <= 64, "one lane per parent");
   __shared__ float4 s_part[W > 1 ? W : 1][2][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1239,7 +1253,7 @@ k_split_bwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
       sq[u] = *reinterpret_cast<const float4*>(HZ + (int64_t)__builtin_amdgcn_readlane(sr, t) * ld + (t >= nr ? Np : 0) + a);
     }
   }
-  const int peu = wt > 0 ? bexp[r] : kExpZero, pev = wt > 0 ? bexp[Sall + r] : kExpZero;
+  const int peu = wt > 0 ? *part_exp.at(0, r, S1, Np) : kExpZero, pev = wt > 0 ? *part_exp.at(1, r, S1, Np) : kExpZero;
   float4 u0 = make_float4(0.f, 0.f, 0.f, 0.f), v0 = u0;
   if (wave == 0 && wt > 0) {
     u0 = *reinterpret_cast<const float4*>(UV + r * ld + a);
@@ -1490,6 +1504,8 @@ void launch_few_bwd(int terms, dim3 grid, hipStream_t st, A... args) {
 }  // namespace
 
 namespace {
+BwdPartExp bwd_part_exp(const Ptrs& p) { return BwdPartExp{p.BH, p.xs, p.rootmask}; }
+
 // The launch of one band: a grid of every tile of the longest sentence, in every sentence.  With enough tiles a wavefront
 // per 64 nonterminals, up to four a workgroup and evenly dealt to the workgroups (at most one of these has a wavefront without
 // nonterminals of its own: with four in each, B = 960, N = 64, n <= 40 spent 831 + 1443 us forward + reverse on split sums, and
@@ -1518,14 +1534,14 @@ void launch_band_fwd(const BandGrid& g, const Layout& ly, const Ptrs& p, int w0,
   static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_fwd<KS>));
   (void)attr;
   launch_k(k_split_band_fwd<KS>, g.grid, g.block, g.lds, st, w0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, g.S_max, p.lens,
-           p.rowbase, p.HZ, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.T, p.bexp);
+           p.rowbase, p.HZ, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.T, p.uexp);
 }
 template <int KS>
 void launch_band_bwd(const BandGrid& g, const Layout& ly, const Ptrs& p, int w0, hipStream_t st) {
   static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<KS>));
   (void)attr;
   launch_k(k_split_band_bwd<KS>, g.grid, g.block, g.lds, st, w0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, g.S_max, p.lens,
-           p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, p.bexp, ly.Sall);
+           p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, bwd_part_exp(p));
 }
 }  // namespace
 
@@ -1546,20 +1562,20 @@ void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   if (few_pays(rows * chunks, nk)) {
     launch_few_fwd(nk, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.B, ly.Np, ly.S1, stride, p.lens,
                    p.rowbase, p.HZ, p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
-                   ly.G > 1 ? 1 : 0, w0, p.bexp);
+                   ly.G > 1 ? 1 : 0, w0, p.uexp);
     return;
   }
   if (rows * chunks < 1024 && nk >= 64) {  // fewer than one wavefront per SIMD, long chains of split points
     const dim3 grid((unsigned)rows, (unsigned)(ly.Np / 64));
     launch_k(k_split_fwd<4>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
              p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
-             ly.G > 1 ? 1 : 0, w0, p.bexp);
+             ly.G > 1 ? 1 : 0, w0, p.uexp);
     return;
   }
   const dim3 grid((unsigned)rows, (unsigned)chunks);
   launch_k(k_split_fwd<1>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
            p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,
-           ly.G > 1 ? 1 : 0, w0, p.bexp);
+           ly.G > 1 ? 1 : 0, w0, p.uexp);
 }
 
 void launch_root_fwd(const Layout& ly, const Ptrs& p, const float* log_root, float* logZ, hipStream_t st) {
@@ -1598,14 +1614,14 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   if (chunks <= kFewChunksBwd && few_pays(rows * chunks, most)) {
     launch_few_bwd(most, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.n_long, ly.B, ly.Np, ly.S1, stride,
                    p.lens, p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr,
-                   ly.planes_bwd, ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.bexp, ly.Sall);
+                   ly.planes_bwd, ly.uvb_plane, p.hmaxb, p.zmaxb, wt, bwd_part_exp(p));
     return;
   }
   const size_t sh = (size_t)(band ? 2 * (wt - 1 - w) : ly.n_max) * 16;
   const dim3 grid((unsigned)rows, (unsigned)((ly.Np + kChunk - 1) / kChunk));
   launch_k(k_split_bwd, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b,
                      p.row_i, p.rootmask, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr, ly.planes_bwd,
-                     ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.bexp, ly.Sall);
+                     ly.uvb_plane, p.hmaxb, p.zmaxb, wt, bwd_part_exp(p));
 }
 
 void launch_zero_pad_emit(const Layout& ly, const Ptrs& p, float* grad_log_emit, hipStream_t st) {

@@ -87,7 +87,6 @@ Layout make_layout(int N, int P, int B, int n_max, int64_t S1, int64_t S2, int b
   ly.hmaxb = take(i4 * ly.Sall);
   ly.zmaxb = take(i4 * ly.Sall);
   ly.colmax = take(f4 * 2 * (size_t)(ly.Np + ly.Pp) * ly.G);
-  ly.bexp = take(i4 * 2 * ly.Sall);
   ly.gsc = take(f4 * ly.Sall);
   ly.xs = take(f4 * S1);
   // One arrival counter per output tile of the largest launch: at most max(S1, S2) rows (one width; grouped
@@ -158,7 +157,6 @@ Ptrs resolve(const Layout& ly, void* ws) {
   p.leafE = (float*)(b + ly.leafE); p.T = (float*)(b + ly.T); p.HZ = (float*)(b + ly.HZ);
   p.UV = (float*)(b + ly.UV); p.BH = (float*)(b + ly.BH);
   p.partial = (float*)(b + ly.partial); p.counters = (int32_t*)(b + ly.counters);
-  p.bexp = (int32_t*)(b + ly.bexp);
   p.sentrows = (int32_t*)(b + ly.sentrows); p.sentoff = (int32_t*)(b + ly.sentoff);
   p.Tb = ly.planes ? b + ly.Tb : nullptr; p.UVb = ly.planes_bwd ? b + ly.UVb : nullptr; p.leafEb = ly.planes ? b + ly.leafEb : nullptr;
   p.UVt_n = b + ly.UVt_n; p.Tt = b + ly.Tt; p.UVt_p = b + ly.UVt_p; p.Et = b + ly.Et;

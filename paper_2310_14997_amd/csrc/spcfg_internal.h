@@ -19,6 +19,10 @@
 //                      workspace pre-filled with 0xFF bytes to catch a read of such a half.
 //   reverse pass:      UV[r]    = unnormalised adjoints of [eta | zeta]                   (exponent uexp[r])
 //                      BH[r]    = 2^-f' * UV[r] * [L;R]  = scaled adjoint of beta         (exponent uexp[r] + f')
+// A band of widths leaves partial split-point sums in T (UV), each with an exponent of its own, until the launch of the row's
+// width.  These have no arrays: the forward one lies in uexp[r], which the reverse pass has not written yet; the reverse
+// two (adjoints of eta and zeta) in the first two words of BH[r], which the reverse product of the width has not written yet,
+// and for leaf rows, which have no BH, in xs[r] and rootmask[r] (read by the root of the forward pass, resp. for w >= 2 only).
 // f (f') is the shift that brings the largest magnitude of T[r] (UV[r]) into [0.5, 1).  The split kernels
 // record that magnitude's bit pattern in tmaxb[r] (umaxb[r]) with an integer atomicMax; the GEMM epilogue
 // applies 2^-f, and every consumer derives the exponent from (mexp, tmaxb) or (uexp, umaxb).
@@ -70,7 +74,6 @@ struct Layout {
   size_t Tg3, Eg3;              // tn3: three bf16 planes of gsc[s] * T[s] ([3][S2p32][Np]) and of gsc[s] * leafE[s] ([3][S1p32][Pp])
   size_t Tb, UVb, leafEb;       // planes > 0: bf16 planes of T, UV, leafE ([planes][rows][cols]), written by their producers
   size_t sentrows, sentoff;     // per-sentence grammars only: rows of width >= 2 listed sentence by sentence, first entry of each
-  size_t bexp;                  // [2][Sall] exponents of the partial split-point sums (forward: the first half)
   // bands: widths kBandW * k .. + kBandW - 1 take their split-point sums (reverse: parent sums) partly in one pass
   int n_long;                   // longest sentence of the batch (n_max may be larger)
   uint8_t band_fwd[kMaxLen / kBandW + 1], band_bwd[kMaxLen / kBandW + 1];
@@ -92,7 +95,6 @@ struct Ptrs {  // device pointers resolved from a Layout
   void *Tb, *UVb, *leafEb;  // null when the layout has no planes
   void *Wn3, *Wp3, *Wtn3, *Wtp3;
   int32_t* counters;
-  int32_t* bexp;
   int32_t* sentrows; int32_t* sentoff;
 };
 

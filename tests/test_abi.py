@@ -32,6 +32,35 @@ def test_strerror_is_total():
         assert isinstance(lib.spcfg_strerror(code), bytes) and len(lib.spcfg_strerror(code)) > 0
 
 
+# bytes of spcfg_workspace_bytes_for (N, P, lengths, precision, flags): callers keep buffers and sizes between versions
+WORKSPACE_BYTES = [
+    (30, 60, [14] * 180, 0, 0, 125688320),
+    (30, 60, [16] * 139, 0, 0, 125781760),
+    (30, 60, [25] * 58, 0, 0, 125792256),
+    (30, 60, [44] * 19, 0, 0, 125817088),
+    (2048, 2048, [40] * 64, 0, 0, 5543836672),
+    (4096, 4096, [40] * 32, 1, 0, 4668549120),
+    (512, 300, [30, 7, 2], 0, bd.FLAG_PER_SENTENCE_GRAMMAR, 93587200),
+    (512, 300, [30, 7, 2], 1, bd.FLAG_PER_SENTENCE_GRAMMAR, 91236096),
+    (141, 333, [37, 2, 9], 0, bd.FLAG_FP32_MFMA, 72377600),
+    (4, 7, [1024], 0, 0, 1700460800),
+]
+
+
+@pytest.mark.parametrize("N,P,lens,precision,flags,most", WORKSPACE_BYTES)
+def test_workspaces_do_not_grow(N, P, lens, precision, flags, most):
+    cfg = bd.make_config(N, P, len(lens), max(lens), precision, flags)
+    assert bd.spcfg_workspace_bytes_for(cfg, lens, max(lens)) <= most
+
+
+@pytest.mark.parametrize("lens", [[14] * 180, [16] * 139, [25] * 58, [44] * 19], ids=lambda x: f"{len(x)}x{x[0]}")
+def test_batches_that_just_fit_the_static_buffer(lens):
+    """spcfg_inside_static needs what spcfg_inside does, with partial tiles (two of 64 KiB each) for 64 workgroups, not 512."""
+    cfg = bd.make_config(30, 60, len(lens), max(lens))
+    need = bd.spcfg_workspace_bytes_for(cfg, lens, max(lens)) - (512 - 64) * 2 * 64 * 1024
+    assert 66.9e6 < need <= 64 * 1024 * 1024
+
+
 def test_workspace_query_and_monotonicity():
     cfg = bd.make_config(30, 60, 4, 10)
     exact = bd.spcfg_workspace_bytes_for(cfg, [10, 10, 10, 10], 10)

@@ -41,6 +41,20 @@ def test_shared_grammar(N, P, lens, n_max, forms):
     check_all(wl.results(), ref)
 
 
+def test_backward_twice_on_one_forward():
+    """The exponents of partial sums lie where the pass has not written yet; none of it is needed by another reverse pass."""
+    d = synth.make_inputs("tiny", seed=4299, pad_value=np.nan, N=65, P=20, B=3, lengths=[63, 17, 52], V=300)
+    print("case two reverse passes", flush=True)
+    wl = bd.Workload(d)
+    wl.workspace.fill_(255)
+    wl.forward()
+    g = np.array([0.5, -1.0, 2.0], dtype=np.float32)
+    for grad in (None, torch.tensor(g, device="cuda:0")):
+        wl.backward(grad)
+        check_all(wl.results(), O.inside_backward(d["log_root"], d["L"], d["R"], d["log_emit"], d["lengths"],
+                                                  np.ones(3) if grad is None else g))
+
+
 def test_one_grammar_per_sentence():
     d = synth.make_inputs_per_sentence("tiny", seed=4300, pad_value=np.nan, N=40, P=24, B=3, lengths=[50, 2, 61])
     print("case per-sentence bands", flush=True)

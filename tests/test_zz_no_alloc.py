@@ -37,6 +37,17 @@ def test_static_scratch_entry_point_matches_the_workspace_one_twice_in_a_row():
         check_logZ(got, O.inside(d["log_root"], d["L"], d["R"], d["log_emit"], d["lengths"]))
 
 
+def test_static_scratch_entry_point_at_its_capacity():
+    """Batches of which one more sentence would not fit; the last one's late widths are summed in bands."""
+    from oracle import spcfg_oracle as O
+    for seed, lens in ((4714, [14] * 180), (4715, [53] * 13)):
+        d = synth.make_inputs("tiny", seed=seed, pad_value=np.nan, B=len(lens), lengths=lens)
+        print("case static scratch, full:", len(lens), "x", lens[0], flush=True)
+        got, ref = run_both(d)
+        check_logZ(got, ref)
+        check_logZ(got, O.inside(d["log_root"], d["L"], d["R"], d["log_emit"], d["lengths"]))
+
+
 def test_static_scratch_entry_point_refuses_what_does_not_fit():
     import torch
     d = synth.make_inputs("tiny", seed=4713, pad_value=np.nan, B=2, lengths=[4, 3])
