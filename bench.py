@@ -156,8 +156,8 @@ def measure(d, bf16, fp32_mfma, steps, warmup, profile_steps, graph=False, extra
     elif fp32_mfma:
         kernel_name, mfma = "k_gemm_nt (fp32 MFMA", "f32"
     else:
-        kernel_name, mfma = ("k_gemm_nt3 / k_gemm_nt (fp32 operands as 3 bf16 pieces, 6 bf16 MFMA products per fp32 "
-                             "product; pre-cut planes for 128-row tiles, cut in the kernel for shorter ones"), "bf16 x6"
+        kernel_name, mfma = ("k_gemm_nt3 / k_gemm_nt / k_gemm_short (fp32 operands as 3 bf16 pieces, 6 bf16 MFMA products "
+                             "per fp32 product; pre-cut planes for 128-row tiles, cut in the kernel for shorter ones"), "bf16 x6"
     wc = synth.work_counts(d["lengths"], d["N"], d["P"])
     stream = torch.cuda.current_stream()
     step = wl.forward_backward
@@ -214,6 +214,8 @@ def measure(d, bf16, fp32_mfma, steps, warmup, profile_steps, graph=False, extra
     res["gemm_grad"] = {"bound": "mfma", "kernel": "rule-gradient product (fp32 mode: k_gemm_tn3 on pre-cut bf16 planes incl. the kernel that scales and cuts the inside vectors; fp32 matrix instructions or per-sentence grammars: k_gemm_tn; bf16 mode: transposes + k_gemm_nt16)",
                         "mfma": mfma, "achieved": gg_tflops, "peak": peak, "unit": "TFLOP/s", "frac": gg_tflops / peak,
                         "ms_per_step": gg["ms_per_step"]}
+    # chart rows that the launches read and write; rows that several workgroups read count for each, so part of them is
+    # served by the caches
     res["split_reduction"] = {"bound": "hbm", "achieved": split_bytes / (split_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
                               "unit": "GB/s", "frac": split_bytes / (split_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                               "ms_per_step": split_ms}

@@ -165,8 +165,9 @@ const char* spcfg_last_hip_error(void);
  * (this perturbs the schedule slightly, so whole-step timing should be taken with profiling disabled).
  * spcfg_profile_read synchronises the recorded events, then fills, for class c in [0, SPCFG_PROF_CLASSES):
  *   ms[c]      total device time of the class since spcfg_profile_enable(1)
- *   launches[c] number of launches
- *   work[c]    algorithmic work enqueued: flop for the GEMM classes, bytes for the others
+ *   launches[c] number of kernel launches
+ *   work[c]    work enqueued: flop for the GEMM classes, bytes for the others (split classes: chart rows that the
+ *              launches read and write; a row that several workgroups read counts for each, whatever cache it comes from)
  * and resets the counters.  Arrays must hold SPCFG_PROF_CLASSES entries.  The counters are the library's only state:
  * process-wide and guarded by a mutex; launches of all threads made while profiling is enabled add up.
  */

@@ -444,8 +444,6 @@ struct BwdPartExp {
 // 2.7 -> 1.8 ms.  kBandShare wavefronts per 64 nonterminals: at n = 200 the launches of the last widths fall from 62 us (four
 // wavefronts) to 25 us; above kBandMinWaves wavefronts in all a wavefront per 64 nonterminals is the faster form, because the
 // tables are built once for four blocks of nonterminals (60 against 85 us there).
-constexpr int kBandI = 4;
-constexpr int kBandQ = kBandI + kBandW - 1;  // ends of the tile's spans
 constexpr int kBandWaves = 4;    // wavefronts of a workgroup with 64 nonterminals each, at most
 constexpr int kBandShare = 16;   // wavefronts of a workgroup that share 64 nonterminals
 constexpr int kBandMinWaves = 1536;
@@ -1600,10 +1598,7 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   const int stride = (ly.n_max + 1) * ly.B;
   const bool band = ly.band_bwd[w / kBandW] != 0;
   const int w0 = w / kBandW * kBandW, wt = band ? w0 + kBandW : 0;
-  // the widest launch of the band (the reverse pass starts one width below n_max, where all spans are roots)
-  int top = wt - 1 < ly.n_long ? wt - 1 : ly.n_long;
-  if (top > ly.n_max - 1) top = ly.n_max - 1;
-  if (band && w == top) {
+  if (band && w == band_top(ly, w0)) {
     const BandGrid g = band_grid(ly, w0, ly.n_long - w0 + kBandI, 2);  // (adj eta: n - wt + 1 values of s, adj zeta: n - w0 + 3)
     if (g.share) launch_band_bwd<kBandShare>(g, ly, p, w0, st);
     else launch_band_bwd<1>(g, ly, p, w0, st);

@@ -179,7 +179,7 @@ void choose_bands(const Plan& plan, Layout* ly) {
     for (int b = 0; b < ly->B; ++b) {
       const int n = plan.lens.v[b];
       if (n < w0 || n < 2) continue;
-      const int tiles = (n - w0 + kBandW) / kBandW;
+      const int tiles = (n - w0 + kBandI) / kBandI;
       ly->band_tiles[k] += tiles;
       fwd_steps += (double)tiles * (w0 + 2);
       bwd_steps += (double)tiles * (n - w0);
@@ -190,8 +190,8 @@ void choose_bands(const Plan& plan, Layout* ly) {
         bwd += spans * (2.0 * (n - w) - 4.0 * near - 4.0);
       }
     }
-    fwd -= (2 * kBandW + 3) * fwd_steps;
-    bwd -= (2 * kBandW + 3) * bwd_steps;
+    fwd -= (kBandI + kBandQ) * fwd_steps;
+    bwd -= (kBandI + kBandQ) * bwd_steps;
     const int64_t waves = (int64_t)ly->band_tiles[k] * (ly->Np / 64);
     auto pays = [&](double rows, double steps, int64_t launch_waves, bool chain) {
       return 4.0 * ly->Np * rows - kBandTables * steps >= (launch_waves >= kBandManyWaves ? kBandBytesMany : kBandBytes) ||
@@ -201,6 +201,45 @@ void choose_bands(const Plan& plan, Layout* ly) {
     ly->band_fwd[k] = w0 >= 2 * kBandW && pays(fwd, fwd_steps, waves, w0 >= kBandChain);
     ly->band_bwd[k] = pays(bwd, bwd_steps, 2 * waves, ly->n_long - w0 >= kBandChain);
   }
+}
+
+// Bytes of chart rows (N floats) that the split launches of a width read and write, for the profile: two rows a term and
+// the sum's own row; with a band the terms inside it, the partial sum read and written once more, and at its first launch
+// eleven rows for every tile and value of s.  (Rows that tiles have in common are counted for each: they may come from a cache.)
+double split_fwd_bytes(const Plan& plan, const Layout& ly, int w) {
+  const bool band = ly.band_fwd[w / kBandW] != 0;
+  const int w0 = w / kBandW * kBandW;
+  double rows = 0;
+  for (int b = 0; b < ly.B; ++b) {
+    const int n = plan.lens.v[b];
+    if (n < w) continue;
+    rows += (n - w + 1) * (band ? 4.0 * (w - w0) + 2.0 : 2.0 * (w - 1) + 1.0);
+    if (!band || w != w0) continue;
+    for (int i0 = 0; i0 + w0 <= n; i0 += kBandI) {
+      const int last = i0 + kBandI + w0 - 2 < n - 1 ? i0 + kBandI + w0 - 2 : n - 1;
+      rows += (double)(kBandI + kBandQ) * (last > i0 ? last - i0 : 0);
+    }
+    for (int v = w0; v < w0 + kBandW && v <= n; ++v) rows += n - v + 1;
+  }
+  return 4.0 * ly.N * rows;
+}
+double split_bwd_bytes(const Plan& plan, const Layout& ly, int w) {
+  const bool band = ly.band_bwd[w / kBandW] != 0;
+  const int w0 = w / kBandW * kBandW, wt = w0 + kBandW;
+  double rows = 0;
+  for (int b = 0; b < ly.B; ++b) {
+    const int n = plan.lens.v[b];
+    if (n > w) {  // (a root has no parents and no sums)
+      const int most = band ? wt - 1 - w : n;
+      for (int i = 0; i <= n - w; ++i) rows += 2.0 * ((n - w - i < most ? n - w - i : most) + (i < most ? i : most));
+      rows += (band ? 4.0 : 2.0) * (n - w + 1);
+    }
+    if (!band || w != band_top(ly, w0)) continue;
+    for (int i0 = 0; i0 + w0 <= n; i0 += kBandI)
+      rows += (double)(kBandI + kBandQ) * ((n - i0 - wt >= 0 ? n - i0 - wt + 1 : 0) + i0 + kBandI - 1);
+    for (int v = w0 > 0 ? w0 : 1; v < wt && v < n; ++v) rows += 2.0 * (n - v + 1);
+  }
+  return 4.0 * ly.N * rows;
 }
 
 int make_plan(const spcfg_config* cfg, const int32_t* lengths, int B, int n_max, Plan* plan, Layout* ly,
@@ -257,12 +296,11 @@ struct Prof {
 
 struct Scope {
   int prev;
-  Scope(hipStream_t, int c, double work, int nlaunch = 1) : prev(t_cur_cls) {
+  Scope(int c, double work) : prev(t_cur_cls) {
     if (!g_prof.on) return;
     t_cur_cls = c;
     std::lock_guard<std::mutex> lock(g_prof.mu);
     g_prof.work[c] += work;
-    g_prof.launches[c] += nlaunch;
   }
   ~Scope() { t_cur_cls = prev; }
 };
@@ -275,6 +313,7 @@ LaunchEvents prof_launch_events() {
   LaunchEvents ev;
   if (!g_prof.on || t_cur_cls < 0) return ev;
   std::lock_guard<std::mutex> lock(g_prof.mu);
+  ++g_prof.launches[t_cur_cls];
   ev.start = g_prof.get();
   ev.stop = g_prof.get();
   if (!ev.start || !ev.stop) {
@@ -363,7 +402,7 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
   leaf.epilogue = NT_EPI_ROWSCALE; leaf.rowmaxb = p.tmaxb;
   set_groups(leaf, plan, ly, p, 1, 0, 2 * Np * Pp);
   {
-    Scope s(st, SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * 3 + 8.0 * ly.S1 * ly.P, 4);
+    Scope s(SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * 3 + 8.0 * ly.S1 * ly.P);
     launch_plan(ly, p, plan.lens, st);
     if (ly.G > 1) launch_plan_sentrows(ly, p, st);
     launch_pack_weights(ly, p, L, R, st);
@@ -371,15 +410,15 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
     launch_leaf_prep(ly, p, log_emit, (ly.bf16 && !ly.fwd_fp32) || gemm_nt_reads_planes(leaf), st);
   }
   {
-    Scope s(st, SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.P * ly.S1);
+    Scope s(SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.P * ly.S1);
     launch_gemm_nt(leaf, st);
   }
   for (int w = 2; w <= n_max; ++w) {
     const int64_t row0 = plan.off[w], rows = plan.cnt[w];
     if (rows == 0) continue;
-    const double split_bytes = 4.0 * ly.N * (double)rows * (2.0 * (w - 1) + 1.0);
+    const double split_bytes = g_prof.on ? split_fwd_bytes(plan, ly, w) : 0.0;
     if (w == n_max) {  // every span of the largest width is a root span: never a child, not projected
-      Scope s(st, SPCFG_PROF_SPLIT_FWD, split_bytes);
+      Scope s(SPCFG_PROF_SPLIT_FWD, split_bytes);
       launch_split_fwd(ly, p, w, row0, rows, false, st);
       break;
     }
@@ -409,14 +448,14 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
     }
     set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
     {
-      Scope s(st, SPCFG_PROF_SPLIT_FWD, split_bytes);
+      Scope s(SPCFG_PROF_SPLIT_FWD, split_bytes);
       launch_split_fwd(ly, p, w, row0, rows, (ly.bf16 && !ly.fwd_fp32) || gemm_nt_reads_planes(a), st);
     }
-    Scope s(st, SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.N * rows - skipped);
+    Scope s(SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.N * rows - skipped);
     launch_gemm_nt(a, st);
   }
   {
-    Scope s(st, SPCFG_PROF_ROOT, 8.0 * ly.N * ly.B);
+    Scope s(SPCFG_PROF_ROOT, 8.0 * ly.N * ly.B);
     launch_root_fwd(ly, p, log_root, logZ, st);
   }
   (void)cfg;
@@ -431,20 +470,14 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
   const int fp32_mfma = (cfg->flags & SPCFG_FLAG_FP32_MFMA) ? 1 : 0;
   const int acc = (cfg->flags & SPCFG_FLAG_ACCUMULATE_GRADS) ? 1 : 0;
   {
-    Scope s(st, SPCFG_PROF_ROOT, 16.0 * ly.N * ly.B, 3);
+    Scope s(SPCFG_PROF_ROOT, 16.0 * ly.N * ly.B);
     launch_root_bwd(ly, p, log_root, grad_logZ, grad_log_root, acc, st);
     launch_zero_pad_emit(ly, p, grad_log_emit, st);
   }
   for (int w = n_max - 1; w >= 1; --w) {  // spans of width n_max are all roots
     const int64_t row0 = plan.off[w], rows = plan.cnt[w];
     if (rows == 0) continue;
-    // per span: (n - w) terms, two vector reads each, plus the two output vectors
-    double terms = 0;
-    for (int b = 0; b < ly.B; ++b) {
-      const int n = plan.lens.v[b];
-      if (n > w) terms += (double)(n - w + 1) * (n - w);
-    }
-    const double split_bytes = 4.0 * ly.N * (2.0 * terms + 2.0 * rows);  // reads + the two output vectors
+    const double split_bytes = g_prof.on ? split_bwd_bytes(plan, ly, w) : 0.0;
     NtArgs a{};
     double gemm_flop;
     a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.b_bf16 = ly.bf16; a.fp32_mfma = fp32_mfma;
@@ -477,19 +510,17 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
       set_groups(a, plan, ly, p, 1, 0, 2 * Np * Pp);
     }
     {
-      Scope s(st, SPCFG_PROF_SPLIT_BWD, split_bytes);
+      Scope s(SPCFG_PROF_SPLIT_BWD, split_bytes);
       // (the rule-gradient product on planes reads the adjoint planes of every row)
       launch_split_bwd(ly, p, w, row0, rows, ly.bf16 || (ly.tn3 && !fp32_mfma) || gemm_nt_reads_planes(a), st);
     }
     {
-      Scope s(st, SPCFG_PROF_GEMM_BWD, gemm_flop);
+      Scope s(SPCFG_PROF_GEMM_BWD, gemm_flop);
       launch_gemm_nt(a, st);
     }
   }
   {
-    // (launches of the class: the two products, plus what prepares their operands: planes or transposes)
-    Scope s(st, SPCFG_PROF_GEMM_GRAD, 4.0 * ly.N * ((double)ly.N * ly.S2 + (double)ly.P * ly.S1),
-            (ly.tn3 && !fp32_mfma && ly.G == 1) ? 5 : ((ly.bf16 && ly.G == 1) ? 6 : 2));
+    Scope s(SPCFG_PROF_GEMM_GRAD, 4.0 * ly.N * ((double)ly.N * ly.S2 + (double)ly.P * ly.S1));
     if (ly.G > 1) {
       // one reduction per sentence over its own spans of width >= 2 (listed in sentrows), one over its leaves
       int n_longest = 2;

@@ -45,7 +45,10 @@ constexpr int kExpZero = -(1 << 24);     // exponent marking an all-zero vector
 constexpr int kMaxB = 960;               // lengths travel as one kernel argument
 constexpr int kMaxLen = 1024;
 
-constexpr int kBandW = 4;                // widths whose split-point sums share row reads (see k_split_band_fwd)
+// widths whose split-point sums share row reads, and starts of a tile (see k_split_band_fwd)
+constexpr int kBandW = 4;
+constexpr int kBandI = 4;
+constexpr int kBandQ = kBandI + kBandW - 1;  // ends of the tile's spans
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
@@ -77,11 +80,17 @@ struct Layout {
   // bands: widths kBandW * k .. + kBandW - 1 take their split-point sums (reverse: parent sums) partly in one pass
   int n_long;                   // longest sentence of the batch (n_max may be larger)
   uint8_t band_fwd[kMaxLen / kBandW + 1], band_bwd[kMaxLen / kBandW + 1];
-  int32_t band_tiles[kMaxLen / kBandW + 1];  // its tiles of kBandW starts, over all sentences
+  int32_t band_tiles[kMaxLen / kBandW + 1];  // its tiles, over all sentences
   int n_counters;
   int gemm_wgs;          // workgroups the partial-tile scratch is sized for (kGemmWgs, fewer for the static scratch)
   size_t total;
 };
+
+// The widest launch of the reverse band of first width w0 (the pass starts one width below n_max, where all spans are roots)
+inline int band_top(const Layout& ly, int w0) {
+  const int top = w0 + kBandW - 1 < ly.n_long ? w0 + kBandW - 1 : ly.n_long;
+  return top < ly.n_max - 1 ? top : ly.n_max - 1;
+}
 
 struct Ptrs {  // device pointers resolved from a Layout
   int32_t *lens, *rowbase, *row_b, *row_i, *rootmask, *rootrow, *mexp, *uexp;
