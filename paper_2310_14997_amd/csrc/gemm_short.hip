@@ -12,8 +12,8 @@
 //    load), so the 16-byte operand reads of 16 consecutive rows touch every bank equally.
 //  * Every operand value is cut into its three bf16 pieces (nt::Split3) by the one lane that multiplies it; fp32 matrix
 //    instructions instead of the cut were 5 % faster on 16 x 16 tiles and 10-60 % slower on all larger ones.
-//  * blockIdx.x is the column tile: workgroups go to the XCDs in turn, so the row tiles of one column tile read their
-//    share of the panel through the same L2.
+//  * blockIdx.x is the column tile: workgroups go to the eight XCDs in turn, so where the columns are a multiple of 128 * NI
+//    the row tiles of one column tile read their share of the panel through the same L2; elsewhere through several.
 // Measured against gemm_nt.hip (us per launch, N = 1024, forward shape 2N columns, K = N / reverse shape N columns, K = 2N):
 // 16 rows 11.5 -> 4.1 / 13.3 -> 6.0; 64 rows 13.1 -> 5.8 / 16.4 -> 8.0; 200 rows 20.3 -> 10.4 / 21.8 -> 11.3;
 // 600 rows 32.8 -> 26.7 / 31.6 -> 26.2.  N = 2048: 16 rows 15.7 -> 6.7 / 18.9 -> 10.2; 200 rows 37.1 -> 28.4 / 41.7 -> 30.9;

@@ -435,11 +435,12 @@ struct BwdPartExp {
 // in reverse) are left to the kernel of their width, which adds them to this partial sum; the partial sum lies in the row's
 // place in T (UV) with an exponent of its own.  Every term is scaled by an exact power of two against the largest
 // exponent of its own sum, as in the kernels of one width.
-// A workgroup is one tile; with enough of them its four wavefronts have 64 nonterminals each, with few of them (late
-// widths of small batches) they share 64 nonterminals, take every fourth group of four s and meet in LDS in wavefront
-// order.  blockIdx.x is the block of nonterminals: the XCD that a tile's neighbours run on is the same, and three of
-// their seven Y rows are shared in its L2.
-// Bound by reading rows (6-8 TB/s through the L2s at the large launches).  Split-point sums of a whole pass before and
+// A workgroup is one tile; with enough of them each of its up to four wavefronts has 64 nonterminals, with few of them (late
+// widths of small batches) sixteen share 64 nonterminals, take every sixteenth group of four s and meet in LDS in wavefront
+// order.  blockIdx.x is the block of nonterminals.  A tile shares three of its seven Y rows with its neighbour in blockIdx.y;
+// both run on the same XCD, and find them in one L2, only where the grid is a multiple of eight wide (Np a multiple of 2048,
+// in the shared form of 512); elsewhere those rows are read from the Infinity Cache or HBM by several XCDs.
+// Bound by reading rows (6-8 TB/s of rows asked for at the large launches).  Split-point sums of a whole pass before and
 // after: B = 4, N = 1024, n <= 200: reverse 10.1 -> 6.2 ms, forward 5.6 -> 4.0 ms; B = 32, N = 4096, n = 40: 4.2 -> 2.7 and
 // 2.7 -> 1.8 ms.  kBandShare wavefronts per 64 nonterminals: at n = 200 the launches of the last widths fall from 62 us (four
 // wavefronts) to 25 us; above kBandMinWaves wavefronts in all a wavefront per 64 nonterminals is the faster form, because the
@@ -695,9 +696,11 @@ k_split_band_bwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const
 // LDS, eight split points (16 row loads) are in flight per lane, the per-span maximum that drives the
 // rescaling of Sec. 3.2 is a wavefront reduction followed by one integer atomicMax, and nothing per split
 // point goes to HBM.  The normalisation itself is applied by the projection GEMM's epilogue.
-// KG = 4 is the shape for launches with few spans and many split points (the late widths), which would leave
-// most of the chip idle: the wavefront covers 64 nonterminals and its four groups of 16 lanes take every fourth
-// split point, so four times as many wavefronts run and each walks a quarter of the split points.
+// KG = 4 is the shape for launches with few spans and more than 64 split points, which would leave most of the chip idle: the
+// wavefront covers 64 nonterminals and its four groups of 16 lanes take every fourth split point, so four times as many
+// wavefronts run and each walks a quarter of the split points.  Nearly all such widths lie in bands; what is left is the last
+// width of a batch whose longest sentence has a multiple of four words (choose_bands ends below it).  A band for that one
+// width costs a launch more: one sentence of 72 words scored in 593 instead of 586 us at N = 64, 1447 instead of 1403 at 2048.
 constexpr int kChunk = 256;  // nonterminals per wavefront (4 per lane) when KG = 1
 
 template <int KG>
@@ -1563,7 +1566,7 @@ void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
                    ly.G > 1 ? 1 : 0, w0, p.uexp);
     return;
   }
-  if (rows * chunks < 1024 && nk >= 64) {  // fewer than one wavefront per SIMD, long chains of split points
+  if (rows * chunks < 1024 && nk >= 64) {  // fewer than one wavefront per SIMD, long chains of split points (see k_split_fwd)
     const dim3 grid((unsigned)rows, (unsigned)(ly.Np / 64));
     launch_k(k_split_fwd<4>, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b, p.row_i, p.HZ,
              p.T, p.mexp, p.tmaxb, Tb, ly.planes, (int64_t)ly.S2 * ly.Np, p.hmaxb, p.zmaxb, p.colmax, ly.Pp,

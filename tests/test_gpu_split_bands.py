@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (7, 9, [49, 48, 2], None, ({16}, {16})),                # one band forward: its first width only, and only in one sentence
     (7, 9, [52, 51, 50, 53], 60, ({16}, {16})),             # band ends inside the longest sentence; padding beyond it
     (65, 20, [63, 17, 64, 3, 62], None, ({16}, {16})),      # two blocks of nonterminals; sentences shorter than every band
+    (33, 10, [72, 68, 5], None, ({16}, {16})),              # the longest sentence's last width is in no band (k_split_fwd<4>)
     (200, 33, [57], 58, ({16}, {16})),                      # one sentence; n_max one above it
     (300, 65, [14] * 24 + [40] * 20, None, (set(), set())),  # too few rows saved for any band
     (310, 20, [48] * 60 + [21, 5], None, ({1}, {1})),       # five blocks of nonterminals dealt to six wavefronts; short sentences
