@@ -417,11 +417,18 @@ struct BwdPartExp {
   float* BH;
   float* xs;
   int32_t* rootmask;
-  __device__ __forceinline__ int32_t* at(int which, int64_t r, int64_t S1, int Np) const {
-    if (r >= S1) return reinterpret_cast<int32_t*>(BH + (r - S1) * Np) + which;
-    return which ? rootmask + r : reinterpret_cast<int32_t*>(xs) + r;
+  __device__ __forceinline__ void put(int which, int64_t r, int64_t S1, int Np, int32_t e) const {
+    if (r >= S1) BH[(r - S1) * Np + which] = __int_as_float(e);
+    else if (which == 0) xs[r] = __int_as_float(e);
+    else rootmask[r] = e;
   }
 };
+// (through the launches' own pointers: a uniform load, which goes through the scalar cache)
+__device__ __forceinline__ int2 bwd_part_exp(int w, int64_t r, int64_t S1, int Np, const float* __restrict__ BH,
+                                             const float* __restrict__ xs, const int32_t* __restrict__ rootmask) {
+  if (w == 1) return make_int2(__float_as_int(xs[r]), rootmask[r]);
+  return make_int2(__float_as_int(BH[(r - S1) * Np]), __float_as_int(BH[(r - S1) * Np + 1]));
+}
 
 // Most of the split-point sums of kBandW consecutive widths w0 .. w0 + kBandW - 1 in one pass, before the first of them
 // (forward), resp. before the last of them (reverse), is finished.  A launch per width reads two rows per term: span
@@ -650,8 +657,10 @@ __device__ __forceinline__ void split_band(int w0, int b, int i0, int B, int Np,
       if (w == 0 || i + w > n || (ROLE != BAND_FWD && w == n)) continue;
       const int r = row_of(rowtab, stride, B, w, b, i, n);
       if (a < Np) out[(r - out_row0) * out_ld + a] = acc[p][d];
-      if (blockIdx.x == 0 && lane == 0 && (KS > 1 || wave == 0))
-        *(ROLE == BAND_FWD ? fwd_exp + r : bwd_exp.at(ROLE == BAND_ZETA, r, S1, Np)) = s_m[p * kBandW + d];
+      if (blockIdx.x == 0 && lane == 0 && (KS > 1 || wave == 0)) {
+        if (ROLE == BAND_FWD) fwd_exp[r] = s_m[p * kBandW + d];
+        else bwd_exp.put(ROLE == BAND_ZETA, r, S1, Np, s_m[p * kBandW + d]);
+      }
     }
 }
 
@@ -700,7 +709,7 @@ k_split_band_bwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const
 // wavefront covers 64 nonterminals and its four groups of 16 lanes take every fourth split point, so four times as many
 // wavefronts run and each walks a quarter of the split points.  Nearly all such widths lie in bands; what is left is the last
 // width of a batch whose longest sentence has a multiple of four words (choose_bands ends below it).  A band for that one
-// width costs a launch more: one sentence of 72 words scored in 593 instead of 586 us at N = 64, 1447 instead of 1403 at 2048.
+// width costs a launch more: split sums of one sentence of 72 words 371 instead of 362 us at N = 64, 501 instead of 491 at 2048.
 constexpr int kChunk = 256;  // nonterminals per wavefront (4 per lane) when KG = 1
 
 template <int KG>
@@ -1083,7 +1092,7 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
             const uint32_t* __restrict__ tmaxb, float* __restrict__ UV, int32_t* __restrict__ uexp,
             uint32_t* __restrict__ umaxb, float* __restrict__ gsc, void* __restrict__ UVb, int planes,
             int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb, int wt,
-            BwdPartExp part_exp) {
+            const float* __restrict__ xs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
   const int64_t r = row0 + blockIdx.x;
@@ -1101,7 +1110,8 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   int32_t* s_p = reinterpret_cast<int32_t*>(s_cs + nt);    // [nt] parent row (index into BH: row - S1)
   int32_t* s_s = s_p + nt;                                 // [nt] sibling row
 
-  const int peu = wt > 0 ? *part_exp.at(0, r, S1, Np) : kExpZero, pev = wt > 0 ? *part_exp.at(1, r, S1, Np) : kExpZero;
+  const int2 pe = wt > 0 ? bwd_part_exp(w, r, S1, Np, BH, xs, rootmask) : make_int2(kExpZero, kExpZero);
+  const int peu = pe.x, pev = pe.y;
   int dmax = max(peu, pev);
   for (int t = lane; t < nt; t += 64) {
     int pr, sr;
@@ -1216,7 +1226,7 @@ k_split_bwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
                 const uint32_t* __restrict__ tmaxb, float* __restrict__ UV, int32_t* __restrict__ uexp,
                 uint32_t* __restrict__ umaxb, float* __restrict__ gsc, void* __restrict__ UVb, int planes,
                 int64_t plane_stride, const int32_t* __restrict__ hmaxb, const int32_t* __restrict__ zmaxb, int wt,
-                BwdPartExp part_exp) {
+                const float* __restrict__ xs, const int32_t* __restrict__ rootmask) {
   static_assert(W * U <= 64, "one lane per parent");
   __shared__ float4 s_part[W > 1 ? W : 1][2][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1254,7 +1264,8 @@ k_split_bwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
       sq[u] = *reinterpret_cast<const float4*>(HZ + (int64_t)__builtin_amdgcn_readlane(sr, t) * ld + (t >= nr ? Np : 0) + a);
     }
   }
-  const int peu = wt > 0 ? *part_exp.at(0, r, S1, Np) : kExpZero, pev = wt > 0 ? *part_exp.at(1, r, S1, Np) : kExpZero;
+  const int2 pe = wt > 0 ? bwd_part_exp(w, r, S1, Np, BH, xs, rootmask) : make_int2(kExpZero, kExpZero);
+  const int peu = pe.x, pev = pe.y;
   float4 u0 = make_float4(0.f, 0.f, 0.f, 0.f), v0 = u0;
   if (wave == 0 && wt > 0) {
     u0 = *reinterpret_cast<const float4*>(UV + r * ld + a);
@@ -1505,8 +1516,6 @@ void launch_few_bwd(int terms, dim3 grid, hipStream_t st, A... args) {
 }  // namespace
 
 namespace {
-BwdPartExp bwd_part_exp(const Ptrs& p) { return BwdPartExp{p.BH, p.xs, p.rootmask}; }
-
 // The launch of one band: a grid of every tile of the longest sentence, in every sentence.  With enough tiles a wavefront
 // per 64 nonterminals, up to four a workgroup and evenly dealt to the workgroups (at most one of these has a wavefront without
 // nonterminals of its own: with four in each, B = 960, N = 64, n <= 40 spent 831 + 1443 us forward + reverse on split sums, and
@@ -1542,7 +1551,7 @@ void launch_band_bwd(const BandGrid& g, const Layout& ly, const Ptrs& p, int w0,
   static const bool attr = set_band_lds(reinterpret_cast<const void*>(&k_split_band_bwd<KS>));
   (void)attr;
   launch_k(k_split_band_bwd<KS>, g.grid, g.block, g.lds, st, w0, ly.B, ly.Np, ly.S1, (ly.n_max + 1) * ly.B, g.S_max, p.lens,
-           p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, bwd_part_exp(p));
+           p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.hmaxb, p.zmaxb, p.uexp, p.umaxb, p.UV, BwdPartExp{p.BH, p.xs, p.rootmask});
 }
 }  // namespace
 
@@ -1612,14 +1621,14 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
   if (chunks <= kFewChunksBwd && few_pays(rows * chunks, most)) {
     launch_few_bwd(most, dim3((unsigned)(starts > 0 ? starts * ly.B : rows), (unsigned)chunks), st, w, starts, row0, p.row_b, p.row_i, ly.n_long, ly.B, ly.Np, ly.S1, stride,
                    p.lens, p.rowbase, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr,
-                   ly.planes_bwd, ly.uvb_plane, p.hmaxb, p.zmaxb, wt, bwd_part_exp(p));
+                   ly.planes_bwd, ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.xs, p.rootmask);
     return;
   }
   const size_t sh = (size_t)(band ? 2 * (wt - 1 - w) : ly.n_max) * 16;
   const dim3 grid((unsigned)rows, (unsigned)((ly.Np + kChunk - 1) / kChunk));
   launch_k(k_split_bwd, grid, dim3(64), sh, st, w, row0, ly.B, ly.Np, ly.S1, stride, p.lens, p.rowbase, p.row_b,
                      p.row_i, p.rootmask, p.HZ, p.BH, p.mexp, p.tmaxb, p.UV, p.uexp, p.umaxb, p.gsc, write_planes ? p.UVb : nullptr, ly.planes_bwd,
-                     ly.uvb_plane, p.hmaxb, p.zmaxb, wt, bwd_part_exp(p));
+                     ly.uvb_plane, p.hmaxb, p.zmaxb, wt, p.xs);
 }
 
 void launch_zero_pad_emit(const Layout& ly, const Ptrs& p, float* grad_log_emit, hipStream_t st) {
