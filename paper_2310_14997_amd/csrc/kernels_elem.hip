@@ -1096,6 +1096,8 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   extern __shared__ __align__(16) unsigned char smem[];
   const int lane = threadIdx.x;
   const int64_t r = row0 + blockIdx.x;
+  // (asked for with the row's indices: the row's place in BH is in no cache yet)
+  const int2 pe = wt > 0 ? bwd_part_exp(w, r, S1, Np, BH, xs, rootmask) : make_int2(kExpZero, kExpZero);
   if (w > 1 && rootmask[r]) return;  // the root span has no parent; its adjoint comes from k_root_bwd (no leaf is a root)
   const int b = row_b[r], i = row_i[r];
   const int n = lens[b];
@@ -1110,7 +1112,6 @@ k_split_bwd(int w, int64_t row0, int B, int Np, int64_t S1, int stride, const in
   int32_t* s_p = reinterpret_cast<int32_t*>(s_cs + nt);    // [nt] parent row (index into BH: row - S1)
   int32_t* s_s = s_p + nt;                                 // [nt] sibling row
 
-  const int2 pe = wt > 0 ? bwd_part_exp(w, r, S1, Np, BH, xs, rootmask) : make_int2(kExpZero, kExpZero);
   const int peu = pe.x, pev = pe.y;
   int dmax = max(peu, pev);
   for (int t = lane; t < nt; t += 64) {
