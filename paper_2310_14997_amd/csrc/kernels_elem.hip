@@ -707,8 +707,8 @@ k_split_band_bwd(int w0, int B, int Np, int64_t S1, int stride, int S_max, const
 // point goes to HBM.  The normalisation itself is applied by the projection GEMM's epilogue.
 // KG = 4 is the shape for launches with few spans and more than 64 split points, which would leave most of the chip idle: the
 // wavefront covers 64 nonterminals and its four groups of 16 lanes take every fourth split point, so four times as many
-// wavefronts run and each walks a quarter of the split points.  Nearly all such widths lie in bands; what is left is the last
-// width of a batch whose longest sentence has a multiple of four words (choose_bands ends below it).  A band for that one
+// wavefronts run and each walks a quarter of the split points.  Nearly all such widths lie in bands; what is left is mostly the
+// last width of a batch whose longest sentence has a multiple of four words (choose_bands ends below it).  A band for that one
 // width costs a launch more: split sums of one sentence of 72 words 371 instead of 362 us at N = 64, 501 instead of 491 at 2048.
 constexpr int kChunk = 256;  // nonterminals per wavefront (4 per lane) when KG = 1
 
