@@ -23,8 +23,8 @@ struct Plan {            // host-side copy of the span schedule
 };
 
 // When a band of widths pays (choose_bands): bytes of row reads saved, less kBandTables for every tile and value of s (its
-// tables take eleven dependent lookups, whatever N is), against what another dependent launch costs.  Fitted to 1006 bands a
-// direction timed with and without, N = 64 .. 2048, B = 8 .. 960, n = 36 .. 100: with this rule no batch's split sums take more
+// tables take eleven dependent lookups, whatever N is), against what another dependent launch costs.  Fitted to 930 forward and
+// 1082 reverse bands timed with and without, N = 64 .. 2048, B = 8 .. 960, n = 36 .. 100: with this rule no batch's split sums take more
 // than 2.3 % longer than without bands.  With 50 MB and no charge for the tables, which is right for N >= 512, batches of small
 // grammars lost up to 17 % (B = 128, N = 128, n = 10 .. 60 forward: 568 us without bands, 662 us with, 562 us by this rule;
 // B = 960, N = 64, n <= 40 reverse: 893, 1007 and 893 us); from kBandManyWaves wavefronts on (N = 2048, B = 64) 50 MB pay.
