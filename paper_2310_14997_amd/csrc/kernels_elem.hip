@@ -135,63 +135,78 @@ __device__ __forceinline__ int row_of(const int32_t* __restrict__ rowtab, int st
   return rowtab[which * stride + w * B + b] + (which == 1 ? i - 1 : 0);
 }
 
-__global__ void k_plan_rowbase(LenArg la, int B, int n_max, int by_sentence, int32_t* __restrict__ lens,
-                               int32_t* __restrict__ rowtab, int32_t* __restrict__ rootrow,
-                               int32_t* __restrict__ counters, int n_counters) {
-  __shared__ int s_w[kMaxLen + 2];
+// One workgroup per width, four sentences per thread: the first row of a width is a closed sum over the sentences, the places
+// within it four scans.  (One workgroup with a thread per width that walked the sentences took 22 us at B = 64, n_max = 40 and
+// 4.8 us at B = 1; this one 3.8 and 3.2.)
+constexpr int kPlanThreads = 256;
+static_assert(4 * kPlanThreads >= kMaxB, "four sentences per thread");
+__global__ void __launch_bounds__(kPlanThreads)
+k_plan_rowbase(LenArg la, int B, int n_max, int by_sentence, int32_t* __restrict__ lens, int32_t* __restrict__ rowtab,
+               int32_t* __restrict__ rootrow, int32_t* __restrict__ counters, int n_counters) {
+  __shared__ int4 s_sum[kPlanThreads / 64];
+  __shared__ int s_below[kPlanThreads / 64];
+  const int w = blockIdx.x + 1, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int stride = (n_max + 1) * B;
-  for (int t = threadIdx.x; t < n_counters; t += blockDim.x) counters[t] = 0;  // GEMM arrival counters
-  for (int b = threadIdx.x; b < B; b += blockDim.x) lens[b] = la.v[b];
-  for (int w = 1 + threadIdx.x; w <= n_max; w += blockDim.x) {
-    int s = 0;
-    for (int b = 0; b < B; ++b) s += max(0, la.v[b] - w + 1);
-    s_w[w] = s;
+  for (int t = blockIdx.x * kPlanThreads + tid; t < n_counters; t += gridDim.x * kPlanThreads) counters[t] = 0;  // GEMM arrival counters
+  int cnt[4];
+  int4 own = make_int4(0, 0, 0, 0);  // of this thread's sentences: spans, prefix spans, middle spans, suffix spans
+  int below = 0;                     // their spans of smaller widths
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int b = 4 * tid + q;
+    const int n = b < B ? la.v[b] : 0;
+    if (b < B && blockIdx.x == 0) lens[b] = n;
+    cnt[q] = max(0, n - w + 1);
+    own.x += cnt[q];
+    own.y += cnt[q] >= 1 ? 1 : 0;
+    own.z += max(0, cnt[q] - 2);
+    own.w += cnt[q] >= 2 ? 1 : 0;
+    const int v = min(w - 1, n);  // sum of n - u + 1 over the widths u = 1 .. v
+    below += v * n - v * (v - 1) / 2;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int w = 1; w <= n_max; ++w) {
-      int s = s_w[w];
-      s_w[w] = run;
-      run += s;
-    }
+  int4 x = own;  // inclusive scan over the wavefront, then over the workgroup
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int4 y = make_int4(__shfl_up(x.x, o, 64), __shfl_up(x.y, o, 64), __shfl_up(x.z, o, 64), __shfl_up(x.w, o, 64));
+    if (lane >= o) x = make_int4(x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w);
+    below += __shfl_xor(below, o, 64);
   }
+  if (lane == 63) { s_sum[wave] = x; s_below[wave] = below; }
   __syncthreads();
-  for (int w = 1 + threadIdx.x; w <= n_max; w += blockDim.x) {
-    const int base = s_w[w];
-    int* tp = rowtab + w * B;
-    int* tm = rowtab + stride + w * B;
-    int* ts = rowtab + 2 * stride + w * B;
+  int base = 0;
+  int4 at = make_int4(x.x - own.x, x.y - own.y, x.z - own.z, x.w - own.w), all = make_int4(0, 0, 0, 0);
+#pragma unroll
+  for (int q = 0; q < kPlanThreads / 64; ++q) {
+    const int4 y = s_sum[q];
+    base += s_below[q];
+    if (q < wave) at = make_int4(at.x + y.x, at.y + y.y, at.z + y.z, at.w + y.w);
+    all = make_int4(all.x + y.x, all.y + y.y, all.z + y.z, all.w + y.w);
+  }
+  int* tp = rowtab + w * B;
+  int* tm = rowtab + stride + w * B;
+  int* ts = rowtab + 2 * stride + w * B;
+  // first rows of this thread's next sentence: plain order, or prefix, middle and suffix blocks
+  int run = base + at.x, rp = base + at.y, rm = base + all.y + at.z, rs = base + all.y + all.z + at.w;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int b = 4 * tid + q;
+    if (b >= B) break;
+    const bool any = cnt[q] > 0;
     if (by_sentence || w == 1) {
-      int run = base;
-      for (int b = 0; b < B; ++b) {
-        const int cnt = la.v[b] - w + 1;
-        tp[b] = cnt > 0 ? run : -1;
-        tm[b] = cnt > 0 ? run + 1 : -1;
-        ts[b] = cnt > 0 ? run + cnt - 1 : -1;
-        if (cnt == 1) rootrow[b] = run;
-        run += max(0, cnt);
-      }
+      tp[b] = any ? run : -1;
+      tm[b] = any ? run + 1 : -1;
+      ts[b] = any ? run + cnt[q] - 1 : -1;
+      if (cnt[q] == 1) rootrow[b] = run;
     } else {
-      int n_pre = 0, n_mid = 0;
-      for (int b = 0; b < B; ++b) {
-        const int cnt = la.v[b] - w + 1;
-        n_pre += cnt > 0 ? 1 : 0;
-        n_mid += max(0, cnt - 2);
-      }
-      int rp = base, rm = base + n_pre, rs = base + n_pre + n_mid;
-      for (int b = 0; b < B; ++b) {
-        const int cnt = la.v[b] - w + 1;
-        if (cnt <= 0) { tp[b] = tm[b] = ts[b] = -1; continue; }
-        tp[b] = rp;
-        tm[b] = rm;
-        ts[b] = cnt >= 2 ? rs : rp;  // a span that is the whole sentence is both: it sits in the prefix block
-        if (cnt == 1) rootrow[b] = rp;
-        rp += 1;
-        rm += max(0, cnt - 2);
-        rs += cnt >= 2 ? 1 : 0;
-      }
+      tp[b] = any ? rp : -1;
+      tm[b] = any ? rm : -1;
+      ts[b] = any ? (cnt[q] >= 2 ? rs : rp) : -1;  // a span that is the whole sentence is both: it sits in the prefix block
+      if (cnt[q] == 1) rootrow[b] = rp;
     }
+    run += cnt[q];
+    rp += any ? 1 : 0;
+    rm += max(0, cnt[q] - 2);
+    rs += cnt[q] >= 2 ? 1 : 0;
   }
 }
 
@@ -369,36 +384,65 @@ __global__ void k_transpose_bf16(const float* __restrict__ X, int64_t ldx, const
 // ------------------------------------------------------------------------------------------ leaves
 // Base case (Sec. 3.1): the inside vector of token i is its emission vector; it is stored as
 // exp(e - max e) with the maximum kept aside (it re-enters only in log Z).
-__global__ void k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, int n_max,
-                            const int32_t* __restrict__ row_b, const int32_t* __restrict__ row_i,
-                            float* __restrict__ leafE, float* __restrict__ xs, int32_t* __restrict__ mexp,
-                            uint32_t* __restrict__ tmaxb, uint16_t* __restrict__ leafEb, int planes,
-                            int64_t plane_stride, const float* __restrict__ colmax, int Np, int per_sentence,
-                            int32_t* __restrict__ hmaxb, int32_t* __restrict__ zmaxb) {
+// One workgroup per token.  Bound by its chain (indices, row, two block reductions): up to kLeafHeld * 1024 values stay in registers
+// between the maximum and the exponentials, four consecutive ones a thread (P = 2048: 1442 tokens 14 us, 40 tokens
+// 6.3 us; two passes over memory with 4-byte loads and 2-byte plane stores took 20 and 11).
+constexpr int kLeafHeld = 4;
+__device__ __forceinline__ float4 load_upto4(const float* p, int left, bool vec, float fill) {
+  if (vec && left >= 4) return *reinterpret_cast<const float4*>(p);
+  return make_float4(left > 0 ? p[0] : fill, left > 1 ? p[1] : fill, left > 2 ? p[2] : fill, left > 3 ? p[3] : fill);
+}
+__global__ void __launch_bounds__(256)
+k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, int n_max, const int32_t* __restrict__ row_b,
+            const int32_t* __restrict__ row_i, float* __restrict__ leafE, float* __restrict__ xs,
+            int32_t* __restrict__ mexp, uint32_t* __restrict__ tmaxb, uint16_t* __restrict__ leafEb, int planes,
+            int64_t plane_stride, const float* __restrict__ colmax, int Np, int per_sentence,
+            int32_t* __restrict__ hmaxb, int32_t* __restrict__ zmaxb) {
   __shared__ float red[16];
   __shared__ int redi[16];
-  const int r = blockIdx.x;
+  const int r = blockIdx.x, t0 = threadIdx.x * 4;
   const float* e = log_emit + ((int64_t)row_b[r] * n_max + row_i[r]) * P;
+  const bool vec = ((uintptr_t)e & 15) == 0;
+  const float* cmL = colmax + (int64_t)(per_sentence ? row_b[r] : 0) * 2 * (Np + Pp) + Np;  // preterminal columns of L
+  const float* cmR = cmL + (Np + Pp);
+  float4 held[kLeafHeld], wl[kLeafHeld], wr[kLeafHeld];
   float mx = -INFINITY;
-  for (int t = threadIdx.x; t < P; t += blockDim.x) mx = fmaxf(mx, e[t]);
+#pragma unroll
+  for (int q = 0; q < kLeafHeld; ++q) {
+    const int t = t0 + q * 1024;
+    if (t >= Pp) continue;
+    held[q] = load_upto4(e + t, P - t, vec, -INFINITY);
+    wl[q] = *reinterpret_cast<const float4*>(cmL + t);
+    wr[q] = *reinterpret_cast<const float4*>(cmR + t);
+    mx = fmaxf(fmaxf(fmaxf(mx, held[q].x), fmaxf(held[q].y, held[q].z)), held[q].w);
+  }
+  for (int t = t0 + kLeafHeld * 1024; t < Pp; t += 1024) {
+    const float4 x = load_upto4(e + t, P - t, vec, -INFINITY);
+    mx = fmaxf(fmaxf(fmaxf(mx, x.x), fmaxf(x.y, x.z)), x.w);
+  }
   mx = block_max(mx, red);
   const bool dead = !(mx > -INFINITY);
   const float x = dead ? 0.0f : mx;
-  float* out = leafE + (int64_t)r * Pp;
-  const float* cmL = colmax + (int64_t)(per_sentence ? row_b[r] : 0) * 2 * (Np + Pp) + Np;  // preterminal columns of L
-  const float* cmR = cmL + (Np + Pp);
   int hs = 0, zs = 0;
-  for (int t = threadIdx.x; t < Pp; t += blockDim.x) {
-    const float v = (t < P && !dead) ? expf(e[t] - x) : 0.0f;
-    out[t] = v;
-    hs = max(hs, bexp_sum(cmL[t], v));
-    zs = max(zs, bexp_sum(cmR[t], v));
-    if (leafEb) {
-      if (planes == 3) put_planes<3>(leafEb, plane_stride, (int64_t)r * Pp + t, v);
-      else if (planes == 2) put_planes<2>(leafEb, plane_stride, (int64_t)r * Pp + t, v);
-      else reinterpret_cast<__bf16*>(leafEb)[(int64_t)r * Pp + t] = (__bf16)v;
+  auto finish = [&](int t, const float4& l, const float4& a, const float4& b) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!dead) {
+      if (t < P) v.x = expf(l.x - x);
+      if (t + 1 < P) v.y = expf(l.y - x);
+      if (t + 2 < P) v.z = expf(l.z - x);
+      if (t + 3 < P) v.w = expf(l.w - x);
     }
-  }
+    *reinterpret_cast<float4*>(leafE + (int64_t)r * Pp + t) = v;
+    hs = max(hs, max(max(bexp_sum(a.x, v.x), bexp_sum(a.y, v.y)), max(bexp_sum(a.z, v.z), bexp_sum(a.w, v.w))));
+    zs = max(zs, max(max(bexp_sum(b.x, v.x), bexp_sum(b.y, v.y)), max(bexp_sum(b.z, v.z), bexp_sum(b.w, v.w))));
+    if (leafEb) store_planes4(leafEb, planes, plane_stride, (int64_t)r * Pp + t, v);
+  };
+#pragma unroll
+  for (int q = 0; q < kLeafHeld; ++q)
+    if (t0 + q * 1024 < Pp) finish(t0 + q * 1024, held[q], wl[q], wr[q]);
+  for (int t = t0 + kLeafHeld * 1024; t < Pp; t += 1024)
+    finish(t, load_upto4(e + t, P - t, vec, -INFINITY), *reinterpret_cast<const float4*>(cmL + t),
+           *reinterpret_cast<const float4*>(cmR + t));
   hs = block_max_i(hs, redi);
   zs = block_max_i(zs, redi);
   if (threadIdx.x == 0) {
@@ -970,34 +1014,50 @@ k_split_fwd_few(int w, int starts, int64_t row0, const int32_t* __restrict__ row
 
 // ------------------------------------------------------------------------------------------ root
 // Z = sum_A pi(S->A) beta_0n[A] (rule S -> A, Sec. 2).
-__global__ void k_root_fwd(int B, int N, int Np, int64_t S1, const int32_t* __restrict__ lens,
-                           const int32_t* __restrict__ rowbase, const int32_t* __restrict__ rootrow,
-                           const float* __restrict__ log_root, const float* __restrict__ T,
-                           const int32_t* __restrict__ mexp, const uint32_t* __restrict__ tmaxb,
-                           const float* __restrict__ xs, float* __restrict__ logZ, float* __restrict__ ztil,
-                           float* __restrict__ rmaxs, int64_t root_stride) {
+// Bound by its chain of lookups: up to kRootHeld * 256 values of the row and of the root's scores are asked for before the
+// maximum of the scores is known (N = 2048: 5.3 us for 64 sentences, 4.1 for one; two loops one after the other took 15 and 9.8).
+constexpr int kRootHeld = 8;
+__global__ void __launch_bounds__(256)
+k_root_fwd(int B, int N, int Np, int64_t S1, const int32_t* __restrict__ lens, const int32_t* __restrict__ rowbase,
+           const int32_t* __restrict__ rootrow, const float* __restrict__ log_root, const float* __restrict__ T,
+           const int32_t* __restrict__ mexp, const uint32_t* __restrict__ tmaxb, const float* __restrict__ xs,
+           float* __restrict__ logZ, float* __restrict__ ztil, float* __restrict__ rmaxs, int64_t root_stride) {
   __shared__ float redf[16];
-  __shared__ double redd[16];
-  const int b = blockIdx.x;
+  __shared__ double redd[16], redx[16];
+  const int b = blockIdx.x, tid = threadIdx.x;
   log_root += b * root_stride;
   const int64_t r = rootrow[b];
+  const int n = lens[b];
+  const int leaf0 = rowbase[1 * B + b];  // width 1 keeps the (sentence, start) order
+  float lr[kRootHeld], th[kRootHeld];
   float rm = -INFINITY;
-  for (int a = threadIdx.x; a < N; a += blockDim.x) rm = fmaxf(rm, log_root[a]);
+#pragma unroll
+  for (int q = 0; q < kRootHeld; ++q) {
+    const int a = tid + q * 256;
+    lr[q] = a < N ? log_root[a] : -INFINITY;
+    rm = fmaxf(rm, lr[q]);
+  }
+  for (int a = tid + kRootHeld * 256; a < N; a += 256) rm = fmaxf(rm, log_root[a]);
+  const float* t = T + (r - S1) * Np;
+#pragma unroll
+  for (int q = 0; q < kRootHeld; ++q) th[q] = tid + q * 256 < N ? t[tid + q * 256] : 0.0f;
+  const uint32_t tb = tmaxb[r];
+  const int me = mexp[r];
+  double sx = 0.0;
+  for (int i = tid; i < n; i += 256) sx += (double)xs[leaf0 + i];
   rm = block_max(rm, redf);
   const bool deadroot = !(rm > -INFINITY);
   const float rmx = deadroot ? 0.0f : rm;
-  const float* t = T + (r - S1) * Np;
-  const float fs = norm_scale(tmaxb[r]);
+  const float fs = norm_scale(tb);
   double z = 0.0;
-  for (int a = threadIdx.x; a < N; a += blockDim.x) z += (double)expf(log_root[a] - rmx) * (double)(t[a] * fs);
+#pragma unroll
+  for (int q = 0; q < kRootHeld; ++q)
+    if (tid + q * 256 < N) z += (double)expf(lr[q] - rmx) * (double)(th[q] * fs);
+  for (int a = tid + kRootHeld * 256; a < N; a += 256) z += (double)expf(log_root[a] - rmx) * (double)(t[a] * fs);
   z = block_sum_d(z, redd);
-  double sx = 0.0;
-  const int n = lens[b];
-  const int leaf0 = rowbase[1 * B + b];  // width 1 keeps the (sentence, start) order
-  for (int i = threadIdx.x; i < n; i += blockDim.x) sx += (double)xs[leaf0 + i];
-  sx = block_sum_d(sx, redd);
-  if (threadIdx.x == 0) {
-    const int e = norm_exp(mexp[r], tmaxb[r]);
+  sx = block_sum_d(sx, redx);
+  if (tid == 0) {
+    const int e = norm_exp(me, tb);
     const bool dead = deadroot || e == kExpZero || !(z > 0.0);
     logZ[b] = dead ? -INFINITY : (float)((double)rmx + log(z) + (double)e * 0.6931471805599453094 + sx);
     ztil[b] = dead ? 0.0f : (float)z;
@@ -1414,9 +1474,8 @@ bool set_band_lds(const void* kernel) {
 }  // namespace
 
 void launch_plan(const Layout& ly, const Ptrs& p, const LenArg& lens, hipStream_t st) {
-  launch_k(k_plan_rowbase, dim3(1), dim3(256), 0, st, lens, ly.B, ly.n_max, ly.G > 1 ? 1 : 0, p.lens, p.rowbase,
-           p.rootrow,
-                     p.counters, ly.n_counters);
+  launch_k(k_plan_rowbase, dim3((unsigned)ly.n_max), dim3(kPlanThreads), 0, st, lens, ly.B, ly.n_max, ly.G > 1 ? 1 : 0, p.lens,
+           p.rowbase, p.rootrow, p.counters, ly.n_counters);
   launch_k(k_plan_rows, dim3(ly.n_max, ly.B), dim3(64), 0, st, ly.B, (ly.n_max + 1) * ly.B, p.lens, p.rowbase, p.row_b, p.row_i,
                      p.rootmask, p.tmaxb, p.umaxb, p.hmaxb, p.zmaxb, reinterpret_cast<uint32_t*>(p.colmax),
                      2 * (int64_t)(ly.Np + ly.Pp) * ly.G);
