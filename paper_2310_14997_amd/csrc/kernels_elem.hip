@@ -254,18 +254,12 @@ __global__ void k_plan_sentrows(int B, int stride, const int32_t* __restrict__ l
 // Stacks [L;R] (Sec. 3.2, kernel fusion: one matrix product for both projections) into zero-padded,
 // K-contiguous operands: Wn [2Np x Np] / Wp [2Np x Pp] for the forward products and their transposes
 // Wtn [Np x 2Np] / Wtp [Pp x 2Np] for the reverse products.
-// The first NPL bf16 pieces of one value's cut (nt::Split3), into planes `stride` elements apart.
-template <int NPL> __device__ __forceinline__ void put_planes(uint16_t* w, int64_t stride, int64_t at, float v) {
-  unsigned h, m, l;
-  nt::Split3::cut2(v, 0.0f, h, m, l);
-  w[at] = (uint16_t)h; w[stride + at] = (uint16_t)m;
-  if (NPL == 3) w[2 * stride + at] = (uint16_t)l;
-}
 // One kernel writes every panel of a call, so L and R are read once: a 64 x 64 tile of a factor goes out as it lies and,
 // turned in LDS, transposed, four consecutive values per thread and store.  Panels of type FwdT / RevT (float or __bf16; the
 // values rounded to it) and NPLF / NPLR bf16 planes (the first pieces of the cut nt::Split3, 2Np*Np resp. 2Np*Pp
 // elements apart; shared grammars only); a null panel is left out.  Bound by HBM: N = P = 2048, fp32 panels and three planes
-// both ways: 76 us (400 MB, 5.3 TB/s); two kernels with 2- and 4-byte stores took 151 us.
+// both ways: 76 us (400 MB, 5.3 TB/s; two kernels with 2- and 4-byte stores took 151 us); the forward ones alone 41 us, without
+// planes 22 us.
 template <typename T> __device__ __forceinline__ void put_panel4(T* w, int64_t at, float4 v) {
   if (w == nullptr) return;
   if constexpr (sizeof(T) == 4) *reinterpret_cast<float4*>(w + at) = v;
@@ -314,10 +308,14 @@ k_pack_weights(const float* __restrict__ L, const float* __restrict__ R, int N, 
     tile[r][x] = v[q].x; tile[r][x + 1] = v[q].y; tile[r][x + 2] = v[q].z; tile[r][x + 3] = v[q].w;
     const int64_t at = (half + a0 + r) * K + c0 + x;
     put_panel4(W, at, v[q]);
-    if (NPLF > 0) store_planes4(ppart ? Wp3 : Wn3, NPLF, plane, at, v[q]);
+    void* W3 = ppart ? Wp3 : Wn3;
+    if (NPLF > 0 && W3 != nullptr) store_planes4(W3, NPLF, plane, at, v[q]);
   }
+  void* Wt3 = ppart ? Wtp3 : Wtn3;
+  const bool turned = Wt != nullptr || (NPLR > 0 && Wt3 != nullptr);
+  if (!turned && colmax == nullptr) return;
   __syncthreads();
-  if (threadIdx.x < 64) {
+  if (threadIdx.x < 64 && colmax != nullptr) {
     // colmax[(g * 2 + lr) * (Np + Pp) + c] = max_A W[A, c] over the padded columns c (nonterminals [0, Np), then
     // preterminals): feeds the exponent bounds of the projections (see proj_shift).  Weights are non-negative, so the
     // maximum of the bit patterns is the maximum of the values; the array is zeroed by the span plan.
@@ -327,13 +325,14 @@ k_pack_weights(const float* __restrict__ L, const float* __restrict__ R, int N, 
     if (m > 0.0f)
       atomicMax(colmax + (int64_t)blockIdx.z * (Np + Pp) + (int64_t)blockIdx.x * 64 + threadIdx.x, __float_as_uint(m));
   }
+  if (!turned) return;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int c = y + 16 * q;
     const float4 t = make_float4(tile[x][c], tile[x + 1][c], tile[x + 2][c], tile[x + 3][c]);
     const int64_t at = (int64_t)(c0 + c) * (2 * Np) + half + a0 + x;
     put_panel4(Wt, at, t);
-    if (NPLR > 0) store_planes4(ppart ? Wtp3 : Wtn3, NPLR, plane, at, t);
+    if (NPLR > 0 && Wt3 != nullptr) store_planes4(Wt3, NPLR, plane, at, t);
   }
 }
 

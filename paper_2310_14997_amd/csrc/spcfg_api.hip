@@ -384,28 +384,131 @@ void set_groups(NtArgs& a, const Plan& plan, const Layout& ly, const Ptrs& p, in
   }
 }
 
-int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const Ptrs& p, const float* log_root,
-            const float* L, const float* R, const float* log_emit, float* logZ, hipStream_t st) {
-  const int n_max = ly.n_max;
+// The forward product of width w: [eta | zeta] = [L;R] * inside vectors (width 1: [L_P ; R_P] * emission vectors).
+// *skipped: flop of the projections that the launch leaves out (w >= 2).
+NtArgs forward_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfma, int w, double* skipped) {
   const int64_t Np = ly.Np, Pp = ly.Pp;
-  const int fp32_mfma = (cfg->flags & SPCFG_FLAG_FP32_MFMA) ? 1 : 0;
-  // width 1: [eta | zeta] = [L_P ; R_P] * emission vector
-  NtArgs leaf{};
-  leaf.partial = p.partial; leaf.counters = p.counters; leaf.max_wgs = ly.gemm_wgs; leaf.n_counters = ly.n_counters; leaf.b_bf16 = ly.bf16 && !ly.fwd_fp32; leaf.fp32_mfma = fp32_mfma;
-  leaf.A = p.leafE; leaf.lda = Pp; leaf.Bm = p.Wp; leaf.ldb = Pp; leaf.C = p.HZ; leaf.ldc = 2 * Np;
-  if (ly.bf16 && !ly.fwd_fp32) { leaf.A = p.leafEb; leaf.a_bf16 = 1; }
-  if (ly.planes >= 2) {
-    leaf.A3 = p.leafEb; leaf.Bm3 = p.Wp3; leaf.planes3 = ly.planes; leaf.a_plane = ly.S1 * Pp; leaf.b_plane = 2 * Np * Pp;
-    leaf.a_bf16 = 0; leaf.b_bf16 = 0;
+  NtArgs a{};
+  if (w == 1) {
+    a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.b_bf16 = ly.bf16 && !ly.fwd_fp32; a.fp32_mfma = fp32_mfma;
+    a.A = p.leafE; a.lda = Pp; a.Bm = p.Wp; a.ldb = Pp; a.C = p.HZ; a.ldc = 2 * Np;
+    if (ly.bf16 && !ly.fwd_fp32) { a.A = p.leafEb; a.a_bf16 = 1; }
+    if (ly.planes >= 2) {
+      a.A3 = p.leafEb; a.Bm3 = p.Wp3; a.planes3 = ly.planes; a.a_plane = ly.S1 * Pp; a.b_plane = 2 * Np * Pp;
+      a.a_bf16 = 0; a.b_bf16 = 0;
+    }
+    a.rows = (int)ly.S1; a.cols = (int)(2 * Np); a.K = (int)Pp;
+    a.epilogue = NT_EPI_ROWSCALE; a.rowmaxb = p.tmaxb;
+    set_groups(a, plan, ly, p, 1, 0, 2 * Np * Pp);
+    return a;
   }
-  leaf.rows = (int)ly.S1; leaf.cols = (int)(2 * Np); leaf.K = (int)Pp;
-  leaf.epilogue = NT_EPI_ROWSCALE; leaf.rowmaxb = p.tmaxb;
-  set_groups(leaf, plan, ly, p, 1, 0, 2 * Np * Pp);
+  const int64_t row0 = plan.off[w], rows = plan.cnt[w];
+  a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.b_bf16 = ly.bf16 && !ly.fwd_fp32; a.fp32_mfma = fp32_mfma;
+  a.A = p.T + (row0 - ly.S1) * Np; a.lda = Np; a.Bm = p.Wn; a.ldb = Np;
+  if (ly.bf16 && !ly.fwd_fp32) { a.A = static_cast<const uint16_t*>(p.Tb) + (row0 - ly.S1) * Np; a.a_bf16 = 1; }
+  if (ly.planes >= 2) {
+    a.A3 = static_cast<const uint16_t*>(p.Tb) + (row0 - ly.S1) * Np; a.Bm3 = p.Wn3;
+    a.planes3 = ly.planes; a.a_plane = ly.S2 * Np; a.b_plane = 2 * Np * Np;
+    a.a_bf16 = 0; a.b_bf16 = 0;
+  }
+  a.C = p.HZ + row0 * 2 * Np; a.ldc = 2 * Np;
+  a.rows = (int)rows; a.cols = (int)(2 * Np); a.K = (int)Np;
+  a.epilogue = NT_EPI_ROWSCALE; a.rowmaxb = p.tmaxb + row0;
+  // eta for the prefix and middle rows, zeta for the middle and suffix rows (when Np is not a whole number of
+  // 128-column tiles the two column blocks would each pad their last tile: one product of 2Np columns then)
+  if (use_parts(ly, w, true) && Np % 128 == 0) {
+    const WidthBlocks k = width_blocks(plan, ly, w);
+    const int kt = (int)(Np / 32);
+    // the profile counts the executed flop: one of the two projections is left out for k.nP + k.nS rows
+    *skipped = 2.0 * ly.N * (double)ly.N * (k.nP + k.nS);
+    a.parts = 2; a.cols = (int)Np;
+    set_part(a, 0, 0, k.nP + k.nM, 0, 0, kt);
+    set_part(a, 1, k.nP, k.nM + k.nS, (int)Np, 0, kt);
+  }
+  set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
+  return a;
+}
+
+// The reverse product of width w; *flop: what it executes.
+NtArgs reverse_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfma, int w, float* grad_log_emit,
+                       double* flop) {
+  const int64_t Np = ly.Np, Pp = ly.Pp, row0 = plan.off[w], rows = plan.cnt[w];
+  NtArgs a{};
+  a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.b_bf16 = ly.bf16; a.fp32_mfma = fp32_mfma;
+  a.A = p.UV + row0 * 2 * Np; a.lda = 2 * Np; a.K = (int)(2 * Np); a.rows = (int)rows;
+  if (ly.bf16) { a.A = static_cast<const uint16_t*>(p.UVb) + row0 * 2 * Np; a.a_bf16 = 1; }
+  if (ly.planes_bwd == 3) {
+    a.A3 = static_cast<const uint16_t*>(p.UVb) + row0 * 2 * Np; a.Bm3 = w >= 2 ? p.Wtn3 : p.Wtp3;
+    a.planes3 = 3; a.a_plane = ly.uvb_plane; a.b_plane = 2 * Np * (w >= 2 ? Np : Pp);
+  }
+  if (w >= 2) {
+    *flop = 4.0 * ly.N * (double)ly.N * rows;
+    a.Bm = p.Wtn; a.ldb = 2 * Np; a.C = p.BH + (row0 - ly.S1) * Np; a.ldc = Np; a.cols = (int)Np;
+    a.epilogue = NT_EPI_MASKROWS; a.rowmask = p.rootmask + row0; a.rowmaxb = p.umaxb + row0;
+    if (use_parts(ly, w, false)) {  // prefix rows: only the eta adjoint (first half of K); suffix rows: only zeta's
+      const WidthBlocks k = width_blocks(plan, ly, w);
+      const int kt = (int)(Np / 32);
+      a.parts = 3;
+      set_part(a, 0, 0, k.nP, 0, 0, kt);
+      set_part(a, 1, k.nP, k.nM, 0, 0, 2 * kt);
+      set_part(a, 2, k.nP + k.nM, k.nS, 0, kt, kt);
+      // (the profile counts the executed flop)
+      if (gemm_nt_keep_parts(a)) *flop -= 2.0 * ly.N * (double)ly.N * (k.nP + k.nS);
+    }
+    set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
+  } else {
+    *flop = 4.0 * ly.N * (double)ly.P * rows;
+    a.Bm = p.Wtp; a.ldb = 2 * Np; a.C = grad_log_emit; a.ldc = ly.P; a.cols = ly.P;
+    a.epilogue = NT_EPI_LEAF_EMIT; a.E = p.leafE; a.lde = Pp; a.rowexp = p.uexp;
+    a.row_b = p.row_b; a.row_i = p.row_i; a.n_max = ly.n_max;
+    set_groups(a, plan, ly, p, 1, 0, 2 * Np * Pp);
+  }
+  return a;
+}
+
+// Where the weight packing writes: the panels that some product of the pass reads, null for the others.  A panel of
+// N = P = 2048 takes 33 MB as fp32 and 50 MB as planes: scoring needs none of the reverse ones, and launches that all have few
+// rows no planes (scoring one sentence of 40 words: 700 -> 631 us, 64 treebank sentences 3044 -> 2985 us).
+Ptrs panels_read(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfma, bool fwd, bool bwd) {
+  Ptrs q = p;
+  q.Wn = q.Wp = q.Wtn = q.Wtp = nullptr;
+  q.Wn3 = q.Wp3 = q.Wtn3 = q.Wtp3 = nullptr;
+  double flop;
+  auto use = [](const NtArgs& a, float* W, void* W3, float** to, void** to3) {
+    if (a.planes3 && gemm_nt_reads_planes(a)) *to3 = W3;
+    else *to = W;
+  };
+  if (fwd) use(forward_product(plan, ly, p, fp32_mfma, 1, &flop), p.Wp, p.Wp3, &q.Wp, &q.Wp3);
+  if (bwd) use(reverse_product(plan, ly, p, fp32_mfma, 1, nullptr, &flop), p.Wtp, p.Wtp3, &q.Wtp, &q.Wtp3);
+  bool f = fwd, r = bwd;  // some wider launch may read another form
+  for (int w = 2; w < ly.n_max && plan.cnt[w] > 0 && (f || r); ++w) {
+    if (f) {
+      NtArgs a = forward_product(plan, ly, p, fp32_mfma, w, &flop);
+      use(a, p.Wn, p.Wn3, &q.Wn, &q.Wn3);
+      a.parts = 0; a.cols = (int)(2 * ly.Np);  // as one product: at least the work of every wider launch
+      f = !(q.Wn && q.Wn3) && (q.Wn3 || (a.planes3 && gemm_nt_reads_planes(a)));
+    }
+    if (r) {
+      NtArgs a = reverse_product(plan, ly, p, fp32_mfma, w, nullptr, &flop);
+      use(a, p.Wtn, p.Wtn3, &q.Wtn, &q.Wtn3);
+      a.parts = 0;
+      r = !(q.Wtn && q.Wtn3) && (q.Wtn3 || (a.planes3 && gemm_nt_reads_planes(a)));
+    }
+  }
+  if (!fwd) q.colmax = nullptr;
+  return q;
+}
+
+int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const Ptrs& p, const float* log_root,
+            const float* L, const float* R, const float* log_emit, float* logZ, bool with_backward, hipStream_t st) {
+  const int n_max = ly.n_max;
+  const int fp32_mfma = (cfg->flags & SPCFG_FLAG_FP32_MFMA) ? 1 : 0;
+  const NtArgs leaf = forward_product(plan, ly, p, fp32_mfma, 1, nullptr);
   {
     Scope s(SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * 3 + 8.0 * ly.S1 * ly.P);
     launch_plan(ly, p, plan.lens, st);
     if (ly.G > 1) launch_plan_sentrows(ly, p, st);
-    launch_pack_weights(ly, p, L, R, st);
+    launch_pack_weights(ly, panels_read(plan, ly, p, fp32_mfma, true, with_backward), L, R, st);
     // operand planes are written only for the launches that read them (bf16 mode: all of them)
     launch_leaf_prep(ly, p, log_emit, (ly.bf16 && !ly.fwd_fp32) || gemm_nt_reads_planes(leaf), st);
   }
@@ -422,31 +525,8 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
       launch_split_fwd(ly, p, w, row0, rows, false, st);
       break;
     }
-    NtArgs a{};
-    double skipped = 0.0;
-    a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.b_bf16 = ly.bf16 && !ly.fwd_fp32; a.fp32_mfma = fp32_mfma;
-    a.A = p.T + (row0 - ly.S1) * Np; a.lda = Np; a.Bm = p.Wn; a.ldb = Np;
-    if (ly.bf16 && !ly.fwd_fp32) { a.A = static_cast<const uint16_t*>(p.Tb) + (row0 - ly.S1) * Np; a.a_bf16 = 1; }
-    if (ly.planes >= 2) {
-      a.A3 = static_cast<const uint16_t*>(p.Tb) + (row0 - ly.S1) * Np; a.Bm3 = p.Wn3;
-      a.planes3 = ly.planes; a.a_plane = ly.S2 * Np; a.b_plane = 2 * Np * Np;
-      a.a_bf16 = 0; a.b_bf16 = 0;
-    }
-    a.C = p.HZ + row0 * 2 * Np; a.ldc = 2 * Np;
-    a.rows = (int)rows; a.cols = (int)(2 * Np); a.K = (int)Np;
-    a.epilogue = NT_EPI_ROWSCALE; a.rowmaxb = p.tmaxb + row0;
-    // eta for the prefix and middle rows, zeta for the middle and suffix rows (when Np is not a whole number of
-    // 128-column tiles the two column blocks would each pad their last tile: one product of 2Np columns then)
-    if (use_parts(ly, w, true) && Np % 128 == 0) {
-      const WidthBlocks k = width_blocks(plan, ly, w);
-      const int kt = (int)(Np / 32);
-      // the profile counts the executed flop: one of the two projections is left out for k.nP + k.nS rows
-      skipped = 2.0 * ly.N * (double)ly.N * (k.nP + k.nS);
-      a.parts = 2; a.cols = (int)Np;
-      set_part(a, 0, 0, k.nP + k.nM, 0, 0, kt);
-      set_part(a, 1, k.nP, k.nM + k.nS, (int)Np, 0, kt);
-    }
-    set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
+    double skipped = 0.0;  // flop of the projections that the launch leaves out
+    const NtArgs a = forward_product(plan, ly, p, fp32_mfma, w, &skipped);
     {
       Scope s(SPCFG_PROF_SPLIT_FWD, split_bytes);
       launch_split_fwd(ly, p, w, row0, rows, (ly.bf16 && !ly.fwd_fp32) || gemm_nt_reads_planes(a), st);
@@ -462,13 +542,19 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
   return hip_status();
 }
 
-int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const Ptrs& p, const float* log_root,
+// (L, R: null where the forward call packed the reverse panels too)
+int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const Ptrs& p, const float* log_root, const float* L,
+             const float* R,
              const float* grad_logZ, float* grad_L, float* grad_R, float* grad_log_root, float* grad_log_emit,
              hipStream_t st) {
   const int n_max = ly.n_max;
   const int64_t Np = ly.Np, Pp = ly.Pp;
   const int fp32_mfma = (cfg->flags & SPCFG_FLAG_FP32_MFMA) ? 1 : 0;
   const int acc = (cfg->flags & SPCFG_FLAG_ACCUMULATE_GRADS) ? 1 : 0;
+  if (L) {
+    Scope s(SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * 2);
+    launch_pack_weights(ly, panels_read(plan, ly, p, fp32_mfma, false, true), L, R, st);
+  }
   {
     Scope s(SPCFG_PROF_ROOT, 16.0 * ly.N * ly.B);
     launch_root_bwd(ly, p, log_root, grad_logZ, grad_log_root, acc, st);
@@ -478,37 +564,8 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
     const int64_t row0 = plan.off[w], rows = plan.cnt[w];
     if (rows == 0) continue;
     const double split_bytes = g_prof.on ? split_bwd_bytes(plan, ly, w) : 0.0;
-    NtArgs a{};
     double gemm_flop;
-    a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.b_bf16 = ly.bf16; a.fp32_mfma = fp32_mfma;
-    a.A = p.UV + row0 * 2 * Np; a.lda = 2 * Np; a.K = (int)(2 * Np); a.rows = (int)rows;
-    if (ly.bf16) { a.A = static_cast<const uint16_t*>(p.UVb) + row0 * 2 * Np; a.a_bf16 = 1; }
-    if (ly.planes_bwd == 3) {
-      a.A3 = static_cast<const uint16_t*>(p.UVb) + row0 * 2 * Np; a.Bm3 = w >= 2 ? p.Wtn3 : p.Wtp3;
-      a.planes3 = 3; a.a_plane = ly.uvb_plane; a.b_plane = 2 * Np * (w >= 2 ? Np : Pp);
-    }
-    if (w >= 2) {
-      gemm_flop = 4.0 * ly.N * (double)ly.N * rows;
-      a.Bm = p.Wtn; a.ldb = 2 * Np; a.C = p.BH + (row0 - ly.S1) * Np; a.ldc = Np; a.cols = (int)Np;
-      a.epilogue = NT_EPI_MASKROWS; a.rowmask = p.rootmask + row0; a.rowmaxb = p.umaxb + row0;
-      if (use_parts(ly, w, false)) {  // prefix rows: only the eta adjoint (first half of K); suffix rows: only zeta's
-        const WidthBlocks k = width_blocks(plan, ly, w);
-        const int kt = (int)(Np / 32);
-        a.parts = 3;
-        set_part(a, 0, 0, k.nP, 0, 0, kt);
-        set_part(a, 1, k.nP, k.nM, 0, 0, 2 * kt);
-        set_part(a, 2, k.nP + k.nM, k.nS, 0, kt, kt);
-        // (the profile counts the executed flop)
-        if (gemm_nt_keep_parts(a)) gemm_flop -= 2.0 * ly.N * (double)ly.N * (k.nP + k.nS);
-      }
-      set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
-    } else {
-      gemm_flop = 4.0 * ly.N * (double)ly.P * rows;
-      a.Bm = p.Wtp; a.ldb = 2 * Np; a.C = grad_log_emit; a.ldc = ly.P; a.cols = ly.P;
-      a.epilogue = NT_EPI_LEAF_EMIT; a.E = p.leafE; a.lde = Pp; a.rowexp = p.uexp;
-      a.row_b = p.row_b; a.row_i = p.row_i; a.n_max = n_max;
-      set_groups(a, plan, ly, p, 1, 0, 2 * Np * Pp);
-    }
+    const NtArgs a = reverse_product(plan, ly, p, fp32_mfma, w, grad_log_emit, &gemm_flop);
     {
       Scope s(SPCFG_PROF_SPLIT_BWD, split_bytes);
       // (the rule-gradient product on planes reads the adjoint planes of every row)
@@ -643,7 +700,7 @@ int spcfg_inside_static(const spcfg_config* cfg, const float* log_root, const fl
   if (ly.total > (size_t)SPCFG_STATIC_SCRATCH_BYTES) return SPCFG_ERR_STATIC_CAPACITY;
   void* ws = static_scratch();
   if (!ws) return SPCFG_ERR_HIP;
-  return forward(cfg, plan, ly, resolve(ly, ws), log_root, L, R, log_emit, logZ, (hipStream_t)hip_stream);
+  return forward(cfg, plan, ly, resolve(ly, ws), log_root, L, R, log_emit, logZ, false, (hipStream_t)hip_stream);
 }
 
 int spcfg_workspace_bytes(const spcfg_config* cfg, size_t* out_bytes) {
@@ -684,7 +741,7 @@ int spcfg_inside(const spcfg_config* cfg, const float* log_root, const float* L,
   if (rc) return rc;
   rc = check_ws(ly, workspace, workspace_bytes);
   if (rc) return rc;
-  return forward(cfg, plan, ly, resolve(ly, workspace), log_root, L, R, log_emit, logZ, (hipStream_t)hip_stream);
+  return forward(cfg, plan, ly, resolve(ly, workspace), log_root, L, R, log_emit, logZ, false, (hipStream_t)hip_stream);
 }
 
 int spcfg_inside_backward(const spcfg_config* cfg, const float* log_root, const float* L, const float* R,
@@ -700,7 +757,7 @@ int spcfg_inside_backward(const spcfg_config* cfg, const float* log_root, const 
   if (rc) return rc;
   rc = check_ws(ly, workspace, workspace_bytes);
   if (rc) return rc;
-  return backward(cfg, plan, ly, resolve(ly, workspace), log_root, grad_logZ, grad_L, grad_R, grad_log_root,
+  return backward(cfg, plan, ly, resolve(ly, workspace), log_root, L, R, grad_logZ, grad_L, grad_R, grad_log_root,
                   grad_log_emit, (hipStream_t)hip_stream);
 }
 
@@ -719,9 +776,9 @@ int spcfg_inside_forward_backward(const spcfg_config* cfg, const float* log_root
   rc = check_ws(ly, workspace, workspace_bytes);
   if (rc) return rc;
   const Ptrs p = resolve(ly, workspace);
-  rc = forward(cfg, plan, ly, p, log_root, L, R, log_emit, logZ, (hipStream_t)hip_stream);
+  rc = forward(cfg, plan, ly, p, log_root, L, R, log_emit, logZ, true, (hipStream_t)hip_stream);
   if (rc) return rc;
-  return backward(cfg, plan, ly, p, log_root, grad_logZ, grad_L, grad_R, grad_log_root, grad_log_emit,
+  return backward(cfg, plan, ly, p, log_root, nullptr, nullptr, grad_logZ, grad_L, grad_R, grad_log_root, grad_log_emit,
                   (hipStream_t)hip_stream);
 }
 
