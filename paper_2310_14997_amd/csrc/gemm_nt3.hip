@@ -279,7 +279,7 @@ __global__ void __launch_bounds__(256, 1) k_gemm_nt3(NtArgs g, int ipw, int tota
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // every load has landed and every operand is in registers before the ring is reused
 
-    finish_tile<BM>(g.partial, g.counters, acc, tile, ustart, k0, k1, KTt, ipw, wg, it, wg_begin, tid, &s_last,
+    finish_tile<BM, BN, 4, 2>(g.partial, g.counters, acc, tile, ustart, k0, k1, KTt, ipw, wg, it, wg_begin, tid, &s_last,
                     [&](floatx16(&t)[MI][NI]) { epilogue<EPI, BM>(g, t, row0, col0, wm, wn, lane, row_end, c_shift); });
     it += k1 - k0;
   }

@@ -76,23 +76,23 @@ constexpr int BN = 128;
 // (16-byte aligned, and 16-byte reads of 8 consecutive rows touch all banks once).
 constexpr int LDT = 36;  // LDS row stride in 4-byte words
 
-// Tile geometry for a row-tile height BM (spans per tile).  Widths with few spans use shorter tiles so that
-// the matrix cores do not multiply padding rows.
-template <int BM> struct Geo {
+// Tile geometry for a row-tile height BM (spans per tile), width BNW and NW wavefronts.  Widths with few spans use
+// shorter tiles so that the matrix cores do not multiply padding rows.
+template <int BM, int BNW = BN, int NW = 4> struct Geo {
   static constexpr int WM = BM == 32 ? 1 : 2;            // wavefronts along rows
-  static constexpr int WN = 4 / WM;                      // wavefronts along columns
+  static constexpr int WN = NW / WM;                     // wavefronts along columns
   static constexpr int MI = BM / (32 * WM);              // 32x32 MFMA tiles per wavefront along rows
-  static constexpr int NI = BN / (32 * WN);              // ... along columns
+  static constexpr int NI = BNW / (32 * WN);             // ... along columns
   static constexpr int QA = BM / 32;                     // 16-byte chunks of A staged per thread and K-step
   static constexpr int kStage = (BM + BN) * LDT;         // words per LDS stage
   static constexpr size_t kLdsBytes = 2 * kStage * sizeof(float);
-  static constexpr int kSlotFloats = BM * BN;
+  static constexpr int kSlotFloats = BM * BNW;
 };
 
-template <int EPI, int BM>
-__device__ __forceinline__ void epilogue(const NtArgs& g, floatx16 (&acc)[Geo<BM>::MI][Geo<BM>::NI], int row0, int col0,
-                                         int wm, int wn, int lane, int row_end, int c_shift = 0) {
-  using G = Geo<BM>;
+template <int EPI, int BM, int BNW = BN, int NW = 4>
+__device__ __forceinline__ void epilogue(const NtArgs& g, floatx16 (&acc)[Geo<BM, BNW, NW>::MI][Geo<BM, BNW, NW>::NI], int row0,
+                                         int col0, int wm, int wn, int lane, int row_end, int c_shift = 0) {
+  using G = Geo<BM, BNW, NW>;
   // accumulator layout of a 32x32 tile: column = lane % 32, row = 8*(v/4) + 4*(lane/32) + v%4
 #pragma unroll
   for (int mi = 0; mi < G::MI; ++mi) {
@@ -208,12 +208,15 @@ __device__ __forceinline__ int find_group(const NtArgs& g, const int* s_tile0, c
 }
 
 // After the K loop of one tile segment [k0, k1): run the epilogue if the segment is the whole tile, else
-// publish the partial tile, count the arrival, and let the last arriver reduce in fixed order.
-template <int BM, typename Epi>
-__device__ __forceinline__ void finish_tile(float* partial, int32_t* counters, floatx16 (&acc)[Geo<BM>::MI][Geo<BM>::NI],
+// publish the partial tile, count the arrival, and let the last arriver reduce in fixed order (kParts of more than two parts at a
+// time: as registers allow).
+template <int BM, int BNW = BN, int NW = 4, int kParts = 1, typename Epi>
+__device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
+                                            floatx16 (&acc)[Geo<BM, BNW, NW>::MI][Geo<BM, BNW, NW>::NI],
                                             int tile, int ustart, int k0, int k1, int KT, int ipw, int wg, int it,
                                             int wg_begin, int tid, int* s_last_ptr, Epi&& run_epilogue) {
-  using G = Geo<BM>;
+  using G = Geo<BM, BNW, NW>;
+  constexpr int kThreads = 64 * NW;
   int& s_last = *s_last_ptr;
   if (k0 == 0 && k1 == KT) {
     run_epilogue(acc);
@@ -230,7 +233,7 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters, f
       for (int ni = 0; ni < G::NI; ++ni)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          st_agent(slot + (((mi * G::NI + ni) * 8 + j) * 256 + tid) * 2, acc[mi][ni][2 * j], acc[mi][ni][2 * j + 1]);
+          st_agent(slot + (((mi * G::NI + ni) * 8 + j) * kThreads + tid) * 2, acc[mi][ni][2 * j], acc[mi][ni][2 * j + 1]);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // my stores have landed before the arrival is counted
     __syncthreads();
     if (tid == 0)
@@ -238,37 +241,49 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters, f
                 parts - 1) ? 1 : 0;
     __syncthreads();
     if (s_last) {
-      // one 32x32 accumulator tile at a time (8 loads in flight per lane), parts in ascending order
+      // Parts in ascending order, kParts whole ones (up to 64 loads a lane) in flight: what the reducing workgroup waits for is
+      // the number of such rounds.  Of two parts one is still in registers, and the order of two terms does not matter.
       const int odd0 = (ustart != first_g * ipw) ? 1 : 0;
+      const int own = wg - first_g;
+      auto fetch = [&](int p, F2 (&x)[G::MI][G::NI][8]) {
+        const float* src = partial + (size_t)(2 * (first_g + p) + (p == 0 ? odd0 : 0)) * G::kSlotFloats;
 #pragma unroll
-      for (int mi = 0; mi < G::MI; ++mi)
+        for (int mi = 0; mi < G::MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < G::NI; ++ni) {
-          floatx16 sum;
+          for (int ni = 0; ni < G::NI; ++ni)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
-          const size_t off = (size_t)((mi * G::NI + ni) * 8 * 256 + tid) * 2;
-          for (int p0 = 0; p0 < parts; p0 += 4) {  // four parts (32 loads per lane) in flight
-            F2 x[4][8];
+            for (int j = 0; j < 8; ++j) x[mi][ni][j] = ld_agent(src + (((mi * G::NI + ni) * 8 + j) * kThreads + tid) * 2);
+      };
+      auto add = [&](float keep, const F2 (&x)[G::MI][G::NI][8]) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const int p = min(p0 + u, parts - 1);
-              const float* src = partial + (size_t)(2 * (first_g + p) + (p == 0 ? odd0 : 0)) * G::kSlotFloats + off;
+        for (int mi = 0; mi < G::MI; ++mi)
 #pragma unroll
-              for (int j = 0; j < 8; ++j) x[u][j] = ld_agent(src + j * 512);
+          for (int ni = 0; ni < G::NI; ++ni)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              acc[mi][ni][2 * j] += keep * x[mi][ni][j].a;
+              acc[mi][ni][2 * j + 1] += keep * x[mi][ni][j].b;
             }
+      };
+      if (parts == 2) {
+        F2 x[G::MI][G::NI][8];
+        fetch(1 - own, x);
+        add(1.0f, x);
+      } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const float keep = (p0 + u < parts) ? 1.0f : 0.0f;  // the clamped duplicate of the last part adds nothing
+        for (int mi = 0; mi < G::MI; ++mi)
 #pragma unroll
-              for (int j = 0; j < 8; ++j) {
-                sum[2 * j] += keep * x[u][j].a;
-                sum[2 * j + 1] += keep * x[u][j].b;
-              }
-            }
-          }
-          acc[mi][ni] = sum;
+          for (int ni = 0; ni < G::NI; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
+        for (int p0 = 0; p0 < parts; p0 += kParts) {
+          F2 x[kParts][G::MI][G::NI][8];
+#pragma unroll
+          for (int u = 0; u < kParts; ++u) fetch(min(p0 + u, parts - 1), x[u]);
+#pragma unroll
+          for (int u = 0; u < kParts; ++u) add(p0 + u < parts ? 1.0f : 0.0f, x[u]);  // (past the end: the last part again, adds nothing)
         }
+      }
       run_epilogue(acc);
       if (tid == 0)  // ready for the next launch on this stream
         __hip_atomic_store(&counters[tile], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

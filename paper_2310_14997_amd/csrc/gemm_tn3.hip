@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // every load has landed and every operand is in registers before the ring is reused
 
-    finish_tile<128>(g.partial, g.counters, acc, tile, tile * KT, k0, k1, KT, ipw, wg, it, wg_begin, tid, &s_last,
+    finish_tile<128, BN, 4, 2>(g.partial, g.counters, acc, tile, tile * KT, k0, k1, KT, ipw, wg, it, wg_begin, tid, &s_last,
                      [&](floatx16(&t)[2][2]) {
       // accumulator layout of a 32x32 tile: column = lane % 32, row = 8*(v/4) + 4*(lane/32) + v%4
 #pragma unroll
