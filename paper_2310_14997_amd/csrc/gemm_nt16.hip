@@ -150,18 +150,10 @@ void launch(const NtArgs& a, hipStream_t st) {
 
 template <int EPI>
 void launch_bm(const NtArgs& a, hipStream_t st) {
-  if (a.grouped) {
-    switch (chosen_bm(a)) {
-      case 32: launch<EPI, 32, true>(a, st); break;
-      case 64: launch<EPI, 64, true>(a, st); break;
-      default: launch<EPI, 128, true>(a, st); break;
-    }
-    return;
-  }
   switch (chosen_bm(a)) {
-    case 32: launch<EPI, 32, false>(a, st); break;
-    case 64: launch<EPI, 64, false>(a, st); break;
-    default: launch<EPI, 128, false>(a, st); break;
+    case 32: launch<EPI, 32, true>(a, st); break;
+    case 64: launch<EPI, 64, true>(a, st); break;
+    default: launch<EPI, 128, true>(a, st); break;
   }
 }
 

@@ -361,10 +361,7 @@ WidthBlocks width_blocks(const Plan& plan, const Layout& ly, int w) {
   }
   return k;
 }
-// (the bf16 mode has a kernel with parts for its forward products only)
-bool use_parts(const Layout& ly, int w, bool forward_product) {
-  return ly.G == 1 && (!ly.bf16 || (forward_product && ly.planes == 2)) && w >= 2;
-}
+bool use_parts(const Layout& ly, int w) { return ly.G == 1 && w >= 2; }
 void set_part(NtArgs& a, int i, int row0, int rows, int c0, int kbeg, int kt) {
   a.prt_row0[i] = row0; a.prt_rows[i] = rows; a.prt_c0[i] = c0; a.prt_kbeg[i] = kbeg; a.prt_kt[i] = kt;
 }
@@ -396,6 +393,8 @@ NtArgs forward_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
     if (ly.planes >= 2) {
       a.A3 = p.leafEb; a.Bm3 = p.Wp3; a.planes3 = ly.planes; a.a_plane = ly.S1 * Pp; a.b_plane = 2 * Np * Pp;
       a.a_bf16 = 0; a.b_bf16 = 0;
+    } else if (ly.planes == 1 && ly.G == 1) {
+      a.A3 = a.A; a.Bm3 = a.Bm; a.planes3 = 1; a.b_bf16 = 0;
     }
     a.rows = (int)ly.S1; a.cols = (int)(2 * Np); a.K = (int)Pp;
     a.epilogue = NT_EPI_ROWSCALE; a.rowmaxb = p.tmaxb;
@@ -410,13 +409,15 @@ NtArgs forward_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
     a.A3 = static_cast<const uint16_t*>(p.Tb) + (row0 - ly.S1) * Np; a.Bm3 = p.Wn3;
     a.planes3 = ly.planes; a.a_plane = ly.S2 * Np; a.b_plane = 2 * Np * Np;
     a.a_bf16 = 0; a.b_bf16 = 0;
+  } else if (ly.planes == 1 && ly.G == 1) {
+    a.A3 = a.A; a.Bm3 = a.Bm; a.planes3 = 1; a.b_bf16 = 0;
   }
   a.C = p.HZ + row0 * 2 * Np; a.ldc = 2 * Np;
   a.rows = (int)rows; a.cols = (int)(2 * Np); a.K = (int)Np;
   a.epilogue = NT_EPI_ROWSCALE; a.rowmaxb = p.tmaxb + row0;
   // eta for the prefix and middle rows, zeta for the middle and suffix rows (when Np is not a whole number of
   // 128-column tiles the two column blocks would each pad their last tile: one product of 2Np columns then)
-  if (use_parts(ly, w, true) && Np % 128 == 0) {
+  if (use_parts(ly, w) && Np % 128 == 0) {
     const WidthBlocks k = width_blocks(plan, ly, w);
     const int kt = (int)(Np / 32);
     // the profile counts the executed flop: one of the two projections is left out for k.nP + k.nS rows
@@ -445,7 +446,7 @@ NtArgs reverse_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
     *flop = 4.0 * ly.N * (double)ly.N * rows;
     a.Bm = p.Wtn; a.ldb = 2 * Np; a.C = p.BH + (row0 - ly.S1) * Np; a.ldc = Np; a.cols = (int)Np;
     a.epilogue = NT_EPI_MASKROWS; a.rowmask = p.rootmask + row0; a.rowmaxb = p.umaxb + row0;
-    if (use_parts(ly, w, false)) {  // prefix rows: only the eta adjoint (first half of K); suffix rows: only zeta's
+    if (use_parts(ly, w)) {  // prefix rows: only the eta adjoint (first half of K); suffix rows: only zeta's
       const WidthBlocks k = width_blocks(plan, ly, w);
       const int kt = (int)(Np / 32);
       a.parts = 3;
@@ -463,6 +464,7 @@ NtArgs reverse_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
     a.row_b = p.row_b; a.row_i = p.row_i; a.n_max = ly.n_max;
     set_groups(a, plan, ly, p, 1, 0, 2 * Np * Pp);
   }
+  if (ly.bf16 && ly.G == 1) { a.A3 = a.A; a.Bm3 = a.Bm; a.planes3 = 1; a.b_bf16 = 0; }
   return a;
 }
 
@@ -475,7 +477,7 @@ Ptrs panels_read(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfm
   q.Wn3 = q.Wp3 = q.Wtn3 = q.Wtp3 = nullptr;
   double flop;
   auto use = [](const NtArgs& a, float* W, void* W3, float** to, void** to3) {
-    if (a.planes3 && gemm_nt_reads_planes(a)) *to3 = W3;
+    if (a.planes3 >= 2 && gemm_nt_reads_planes(a)) *to3 = W3;
     else *to = W;
   };
   if (fwd) use(forward_product(plan, ly, p, fp32_mfma, 1, &flop), p.Wp, p.Wp3, &q.Wp, &q.Wp3);

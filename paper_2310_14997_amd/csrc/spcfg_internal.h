@@ -199,7 +199,7 @@ struct NtArgs {
   // b_plane; the launches with tall row tiles run on them in gemm_nt3.hip.  A / Bm stay the fp32 operands, which the
   // launches with short row tiles use (their time goes into reading the panel once, and the fp32 panel is a third
   // shorter than its three planes).  planes3 = 2: two planes (hi, lo) and every launch runs on them (forward products
-  // of the bf16 mode).
+  // of the bf16 mode).  planes3 = 1: A3 = A and Bm3 = Bm are bf16 (the other products of the bf16 mode).
   int planes3; int64_t a_plane, b_plane;
   const void* A3; const void* Bm3;
   int parts;
