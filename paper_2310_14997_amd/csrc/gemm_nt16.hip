@@ -1,6 +1,6 @@
-// bf16-operand MFMA GEMM (fp32 accumulate) for the projections in SPCFG_PRECISION_BF16:
-//   C[r][c] = sum_k A[r][k] * Bm[c][k],  Bm = packed bf16 [L;R] panel, A = the bf16 copy of the chart rows that
-// their producers write next to the fp32 ones (or the transposed operands of the rule-gradient product).
+// bf16-operand MFMA GEMM (fp32 accumulate) for the projections in SPCFG_PRECISION_BF16 with one grammar per sentence:
+//   C[r][c] = sum_k A[r][k] * Bm[c][k],  Bm = packed bf16 [L;R] panel of the row's sentence, A = the bf16 copy of the chart
+// rows that their producers write next to the fp32 ones.
 // Same tiling, work sharing and epilogues as the fp32 kernel; one K-step is 64 values, and every
 // MFMA operand is one 16-byte LDS read of 8 consecutive bf16 (v_mfma_f32_32x32x16_bf16: lane l holds row
 // l % 32, k = 8 * (l / 32) .. + 7).
@@ -13,19 +13,18 @@ namespace {
 using namespace nt;
 constexpr int BK = 64;  // bf16 values per K-step
 
-template <int EPI, int BM, bool GROUPED>
+template <int EPI, int BM>
 __global__ void __launch_bounds__(256, 2) k_gemm_nt16(NtArgs g, int ipw, int total_iters) {
   using G = Geo<BM>;
   extern __shared__ __align__(16) float lds[];
   __shared__ int s_last;
-  // grouped mode (one grammar per sentence): first row tile, first row and row count of every sentence
-  __shared__ int s_tile0[GROUPED ? kMaxB + 1 : 1], s_row0[GROUPED ? kMaxB : 1], s_cnt[GROUPED ? kMaxB : 1];
+  // first row tile, first row and row count of every sentence
+  __shared__ int s_tile0[kMaxB + 1], s_row0[kMaxB], s_cnt[kMaxB];
   __shared__ int s_wsum[4];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave % G::WM, wn = wave / G::WM;
-  int tiles_m = (g.rows + BM - 1) / BM;
-  if (GROUPED) tiles_m = build_group_table<BM>(g, s_tile0, s_row0, s_cnt, s_wsum, tid);
+  const int tiles_m = build_group_table<BM>(g, s_tile0, s_row0, s_cnt, s_wsum, tid);
   const int KT = g.K / BK;
   // staging of both operands: 8 chunks of 16 bytes (8 bf16) per row and K-step, 32 rows per pass
   const int lc8 = tid & 7, lr8 = tid >> 3;
@@ -46,7 +45,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_nt16(NtArgs g, int ipw, int tot
     int row0 = tile_m * BM, row_end = g.rows;
     const int col0 = tile_n * BN;
     const __bf16* Bh = static_cast<const __bf16*>(g.Bm);
-    if (GROUPED) Bh += (int64_t)find_group<BM>(g, s_tile0, s_row0, s_cnt, tile_m, &row0, &row_end) * g.grp_b_stride;
+    Bh += (int64_t)find_group<BM>(g, s_tile0, s_row0, s_cnt, tile_m, &row0, &row_end) * g.grp_b_stride;
 
     // element offsets of this thread's chunks (row clamped into range: out-of-range rows are never stored)
     int64_t oa[QA], ob[4];
@@ -136,33 +135,32 @@ __global__ void __launch_bounds__(256, 2) k_gemm_nt16(NtArgs g, int ipw, int tot
   }
 }
 
-template <int EPI, int BM, bool GROUPED>
+template <int EPI, int BM>
 void launch(const NtArgs& a, hipStream_t st) {
   using G = Geo<BM>;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_nt16<EPI, BM, GROUPED>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_nt16<EPI, BM>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLdsBytes);
     attr_set = true;
   }
-  launch_shared(k_gemm_nt16<EPI, BM, GROUPED>, a, BM, BK, G::kLdsBytes, st);
+  launch_shared(k_gemm_nt16<EPI, BM>, a, BM, BK, G::kLdsBytes, st);
 }
 
 template <int EPI>
 void launch_bm(const NtArgs& a, hipStream_t st) {
   switch (chosen_bm(a)) {
-    case 32: launch<EPI, 32, true>(a, st); break;
-    case 64: launch<EPI, 64, true>(a, st); break;
-    default: launch<EPI, 128, true>(a, st); break;
+    case 32: launch<EPI, 32>(a, st); break;
+    case 64: launch<EPI, 64>(a, st); break;
+    default: launch<EPI, 128>(a, st); break;
   }
 }
 
 }  // namespace
 
 void launch_gemm_nt16(const NtArgs& a, hipStream_t st) {
-  if (a.rows <= 0 || a.cols <= 0 || !a.a_bf16 || !a.b_bf16) return;  // both operands are bf16 here
+  if (a.rows <= 0 || a.cols <= 0 || !a.a_bf16 || !a.b_bf16 || !a.grouped) return;
   switch (a.epilogue) {
-    case NT_EPI_GRAD: launch<NT_EPI_GRAD, 128, false>(a, st); break;
     case NT_EPI_ROWSCALE: launch_bm<NT_EPI_ROWSCALE>(a, st); break;
     case NT_EPI_MASKROWS: launch_bm<NT_EPI_MASKROWS>(a, st); break;
     default: launch_bm<NT_EPI_LEAF_EMIT>(a, st); break;

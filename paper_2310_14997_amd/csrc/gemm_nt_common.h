@@ -111,19 +111,6 @@ __device__ __forceinline__ void epilogue(const NtArgs& g, floatx16 (&acc)[Geo<BM
         const int f = max((int)((mb >> 23) & 0xffu) - 126, -126);
         scale = mb == 0u ? 0.0f : ldexpf(1.0f, -f);
       }
-      if (EPI == NT_EPI_GRAD) {  // rows are the stacked parents [L;R]: scatter into grad_L / grad_R
-        const int half = r >= g.Np ? 1 : 0;
-        const int arow = r - half * g.Np;
-        if (arow >= g.Nvalid) continue;
-        float* dst = (half ? g.gR : g.gL) + (int64_t)arow * g.ldg + g.col0;
-#pragma unroll
-        for (int ni = 0; ni < G::NI; ++ni) {
-          const int c = col0 + (wn * G::NI + ni) * 32 + (lane & 31);
-          if (c >= g.cols) continue;
-          dst[c] = g.accumulate ? dst[c] + acc[mi][ni][v] : acc[mi][ni][v];
-        }
-        continue;
-      }
       if (EPI == NT_EPI_LEAF_EMIT) {
         const int q = g.rowexp[r];
         scale = (q == kExpZero || q < -160) ? 0.0f : ldexpf(1.0f, min(q, 127));

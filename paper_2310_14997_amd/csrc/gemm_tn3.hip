@@ -1,7 +1,7 @@
 // Rule-gradient GEMM on operands that arrive already cut into three bf16 planes:
 //   d/d[L;R][a][b] = sum_s A[s][a] * B[s][b],  A = adjoint rows of [eta | zeta], B = scale[s] * inside vector of row s
 // (chain rule through the stacked projection of Sec. 3.2; the per-span power-of-two scale is folded into B's planes
-// by their producer, so this kernel does no vector work).  Both operands are reduction-major ([s][column]): tiles of
+// by their producer, so this kernel does no vector work).  In the bf16 mode the operands are one plane, the bf16 rounding.  Both operands are reduction-major ([s][column]): tiles of
 // 32 span rows x 128 columns go straight from global memory into LDS as they lie (global_load_lds_dwordx4, 1 KB per
 // wavefront instruction = 4 rows of 256 bytes), into a ring of three stages, and the matrix operands - eight
 // consecutive reduction rows of one column per lane - come out of LDS through the transposing read
@@ -25,17 +25,32 @@ using namespace nt;
 
 typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
 
-constexpr int T3M = 128, T3N = 128, T3K = 32;
-constexpr int kOpnd = T3K * 256;            // bytes of one operand tile of one plane: 32 rows of 128 bf16
-constexpr int kPlane = 2 * kOpnd;           // [A tile | B tile]
-constexpr int kStage3 = 3 * kPlane;         // three planes
+constexpr int T3M = 128, T3K = 32;
+constexpr int kOpnd = T3K * 256;            // bytes of one operand tile: 32 rows of 128 bf16
 constexpr int kNS = 3;
-constexpr size_t kLdsTn3 = (size_t)kNS * kStage3;
-constexpr int kND = 12;                     // 1 KB load instructions per wavefront and stage (48 per workgroup)
-constexpr int kNF = 4;                      // operand fragments per plane and 16-row chunk (2 of A, 2 of B)
-constexpr int kNR = 3 * kNF * 2;            // transposing reads per chunk (two per fragment: rows 0..3 and 4..7 of its 8)
-constexpr int kNM = 6 * 2 * 2;              // matrix instructions per chunk
+constexpr int kNF = 4;                      // operand fragments per slot and 16-row chunk (2 of A, 2 of B)
 constexpr int kNB = 2;                      // matrix instructions ahead of the barrier
+
+// A stage has slots of one A tile and one or two B tiles: with three planes (fp32 mode) a slot is a plane of 32 rows, with one plane
+// (bf16 mode) two slots are 64 rows.  One plane has a sixth of the matrix work for a third of the bytes: there the output
+// tile is 128 x 256 and eight wavefronts share it (N = P = 4096, 24 960 spans: 1.46 ms and 0.11 ms for the scaled rows; transposing
+// both operands in memory for the K-contiguous kernel took 1.77 + 0.54 ms).
+template <int PLANES> struct GeoT {
+  static constexpr int SLOTS = PLANES == 3 ? 3 : 2;
+  static constexpr int BH = PLANES == 3 ? 1 : 2;          // B tiles of 128 columns
+  static constexpr int NW = 4 * BH;
+  static constexpr int T3N = 128 * BH;
+  static constexpr int KROWS = PLANES == 3 ? T3K : 2 * T3K;  // reduction rows of a step
+  static constexpr int SLOT = (1 + BH) * kOpnd;           // [A tile | B tiles]
+  static constexpr int STAGE = SLOTS * SLOT;
+  static constexpr size_t kLds = (size_t)kNS * STAGE;
+  static constexpr int ND = SLOTS * (1 + BH) * 8 / NW;    // 1 KB load instructions per wavefront and stage
+  static constexpr int NR = SLOTS * kNF * 2;              // transposing reads per chunk (two per fragment: rows 0..3 and 4..7 of its 8)
+  static constexpr int NM = (PLANES == 3 ? 6 : 2) * 4;    // matrix instructions per chunk
+  static constexpr int RPS = PLANES == 3 ? 2 : 3;         // reads behind each matrix instruction of the second half
+  static constexpr int slot_of(int t) { return t * NW / (8 * (1 + BH)); }
+  static constexpr int opnd_of(int t) { return t * NW % (8 * (1 + BH)) / 8; }
+};
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -67,17 +82,20 @@ struct Frag { uintx2 lo, hi; };
 __device__ __forceinline__ bf16x8 operand(const Frag& f) {
   return __builtin_bit_cast(bf16x8, uintx4{f.lo[0], f.lo[1], f.hi[0], f.hi[1]});
 }
-template <int R = 0>
-__device__ __forceinline__ void tie_frags(Frag (&F)[3][kNF]) {
-  if constexpr (R < 3 * kNF) {
+template <int SLOTS, int R = 0>
+__device__ __forceinline__ void tie_frags(Frag (&F)[SLOTS][kNF]) {
+  if constexpr (R < SLOTS * kNF) {
     asm volatile("" : "+v"(F[R / kNF][R % kNF].lo), "+v"(F[R / kNF][R % kNF].hi));
-    tie_frags<R + 1>(F);
+    tie_frags<SLOTS, R + 1>(F);
   }
 }
 
 #define SPCFG_SB __builtin_amdgcn_sched_barrier(0);
 
-__global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int total_iters) {
+template <int PLANES>
+__global__ void __launch_bounds__(64 * GeoT<PLANES>::NW, 1) k_gemm_tn3(Tn3Args g, int ipw, int total_iters) {
+  using Q = GeoT<PLANES>;
+  constexpr int SLOTS = Q::SLOTS, ND = Q::ND, NR = Q::NR, NM = Q::NM;
   extern __shared__ __align__(16) unsigned char lds3[];
   __shared__ int s_last;
   const int tid = threadIdx.x;
@@ -85,7 +103,7 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
   const int uw = __builtin_amdgcn_readfirstlane(wave);
   const int wm = wave & 1, wn = wave >> 1;
   const int tiles_a = (2 * g.Np) / T3M;
-  const int tiles_b = (g.cols + T3N - 1) / T3N;
+  const int tiles_b = (g.cols + Q::T3N - 1) / Q::T3N;
   const int KT = g.KT;
   const unsigned lds0 = lds_address(lds3);
   // transposing reads: lane = 16 q + i reads row 8 (q / 2) + i / 4 of the chunk, columns 32 f + 16 (q % 2) + 4 (i % 4) .. + 3
@@ -96,19 +114,18 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
   unsigned fbase[kNF];  // byte offset inside a stage of fragment f, plane 0, chunk 0, first half
 #pragma unroll
   for (int f = 0; f < kNF; ++f) {
-    const unsigned blk = (unsigned)((f < 2 ? wm : wn) * 2 + (f & 1));
-    fbase[f] = (f < 2 ? 0u : (unsigned)kOpnd) + row_in * 256u + ((blk ^ (unsigned)(li >> 2)) * 64u) + in_blk;
+    const unsigned blk = (unsigned)((f < 2 ? wm : wn & 1) * 2 + (f & 1));
+    fbase[f] = (f < 2 ? 0u : (unsigned)((1 + (wn >> 1)) * kOpnd)) + row_in * 256u + ((blk ^ (unsigned)(li >> 2)) * 64u) + in_blk;
   }
-  // this wavefront's load instructions: entry e = uw + 4 t of the stage's 48: plane e / 16 = t / 4, operand A for
-  // (e % 16) < 8, i.e. t % 4 < 2, rows 4 ((e % 16) % 8) .. + 3; lane l lands at + 16 l: row l / 16 of the four, 16-byte
-  // chunk l % 16
-  int e_row[kND];
-  unsigned e_lds[kND];
+  // this wavefront's load instructions: entry e = uw + NW t of the stage's list, eight (rows 4 (e % 8) .. + 3) per operand tile;
+  // lane l lands at + 16 l: row l / 16 of the four, 16-byte chunk l % 16
+  int e_row[ND];
+  unsigned e_lds[ND];
 #pragma unroll
-  for (int t = 0; t < kND; ++t) {
-    const int j = (uw + 4 * t) & 15;
-    e_row[t] = 4 * (j & 7) + (lane >> 4);
-    e_lds[t] = (unsigned)((t / 4) * kPlane + ((t % 4) < 2 ? 0 : kOpnd) + (j & 7) * 1024);
+  for (int t = 0; t < ND; ++t) {
+    const int j = (uw + Q::NW * t) & 7;
+    e_row[t] = 4 * j + (lane >> 4);
+    e_lds[t] = (unsigned)(Q::slot_of(t) * Q::SLOT + Q::opnd_of(t) * kOpnd + j * 1024);
   }
   const int c16 = lane & 15;
   // global column (elements) of this lane's 16 bytes: 64-byte block (c16 / 4) XOR (row mod 4), 16-byte piece c16 % 4
@@ -130,23 +147,25 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
       tile_a = (blk % blocks_a) * 8 + (l & 7);
       tile_b = (blk / blocks_a) * 8 + (l >> 3);
     }
-    const int a0 = tile_a * T3M, b0 = tile_b * T3N;
+    const int a0 = tile_a * T3M, b0 = tile_b * Q::T3N;
     // position p of the tile's K loop is step (p + krot) mod KT (see gemm_nt3.hip: shares of any size stay in phase)
     const int krot = ((tile * KT) % ipw) % KT;
 
-    const unsigned char* gp[kND];
+    const unsigned char* gp[ND];
+    // a slot's distance: a plane, or 32 rows of the one plane
+    const int64_t next_a = PLANES == 3 ? g.a_plane : T3K * g.lda, next_b = PLANES == 3 ? g.b_plane : T3K * g.ldb;
 #pragma unroll
-    for (int t = 0; t < kND; ++t) {
-      if ((t % 4) < 2) {
-        gp[t] = reinterpret_cast<const unsigned char*>(g.A3 + (int64_t)(t / 4) * g.a_plane + (int64_t)e_row[t] * g.lda +
-                                                       a0 + gcol);
+    for (int t = 0; t < ND; ++t) {
+      if (Q::opnd_of(t) == 0) {
+        gp[t] = reinterpret_cast<const unsigned char*>(g.A3 + Q::slot_of(t) * next_a + (int64_t)e_row[t] * g.lda + a0 + gcol);
       } else {
-        const int c = b0 + gcol;  // columns past the padded width are read from column 0 and feed dropped outputs only
-        gp[t] = reinterpret_cast<const unsigned char*>(g.B3 + (int64_t)(t / 4) * g.b_plane + (int64_t)e_row[t] * g.ldb +
+        // columns past the padded width are read from column 0 and feed dropped outputs only
+        const int c = b0 + (Q::opnd_of(t) - 1) * 128 + gcol;
+        gp[t] = reinterpret_cast<const unsigned char*>(g.B3 + Q::slot_of(t) * next_b + (int64_t)e_row[t] * g.ldb +
                                                        (c < (int)g.ldb ? c : 0));
       }
     }
-    const int64_t step_a = 2 * (int64_t)T3K * g.lda, step_b = 2 * (int64_t)T3K * g.ldb;  // bytes per K-step
+    const int64_t step_a = 2 * (int64_t)Q::KROWS * g.lda, step_b = 2 * (int64_t)Q::KROWS * g.ldb;  // bytes per K-step
 
     floatx16 acc[2][2];
 #pragma unroll
@@ -156,44 +175,45 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
 
-    Frag X[3][kNF], Y[3][kNF];
+    Frag X[SLOTS][kNF], Y[SLOTS][kNF];
     auto load_stage = [&](int stage, int kpos) {
       const int kr = kpos + krot;
       const int64_t ks = kr >= KT ? kr - KT : kr;
-      static_for<0, kND>([&](auto t) {
+      static_for<0, ND>([&](auto t) {
         constexpr int tv = decltype(t)::value;
-        dma16(gp[tv] + ks * ((tv % 4) < 2 ? step_a : step_b), lds0 + stage * kStage3 + e_lds[tv]);
+        dma16(gp[tv] + ks * (Q::opnd_of(tv) == 0 ? step_a : step_b), lds0 + stage * Q::STAGE + e_lds[tv]);
       });
     };
-    // read r of a chunk: plane r / 8, fragment (r % 8) / 2, half r % 2
-    auto read_one = [&](Frag(&F)[3][kNF], auto r, unsigned stage_chunk) {
+    // read r of a chunk: slot r / 8, fragment (r % 8) / 2, half r % 2
+    auto read_one = [&](Frag(&F)[SLOTS][kNF], auto r, unsigned stage_chunk) {
       constexpr int pl = decltype(r)::value / 8, f = (decltype(r)::value % 8) / 2, h = decltype(r)::value % 2;
       const unsigned addr = stage_chunk + fbase[f];
       if constexpr (h == 0) {
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(F[pl][f].lo) : "v"(addr), "n"(pl * kPlane));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(F[pl][f].lo) : "v"(addr), "n"(pl * Q::SLOT));
       } else {
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(F[pl][f].hi) : "v"(addr), "n"(pl * kPlane + 1024));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(F[pl][f].hi) : "v"(addr), "n"(pl * Q::SLOT + 1024));
       }
     };
-    auto mfma_one = [&](Frag(&F)[3][kNF], auto i) {
+    auto mfma_one = [&](Frag(&F)[SLOTS][kNF], auto i) {
       // piece products, small terms first: lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi (planes: 0 hi, 1 mid, 2 lo)
       constexpr int pp = decltype(i)::value / 4, rem = decltype(i)::value % 4;
       constexpr int mi = rem / 2, ni = rem % 2;
-      constexpr int pa = pp == 0 ? 2 : (pp == 2 || pp == 3 ? 1 : 0);
-      constexpr int pb = pp == 1 ? 2 : (pp == 2 || pp == 4 ? 1 : 0);
+      // (one plane: each slot with itself)
+      constexpr int pa = PLANES == 1 ? pp : pp == 0 ? 2 : (pp == 2 || pp == 3 ? 1 : 0);
+      constexpr int pb = PLANES == 1 ? pp : pp == 1 ? 2 : (pp == 2 || pp == 4 ? 1 : 0);
       acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(F[pa][mi]), operand(F[pb][2 + ni]), acc[mi][ni], 0, 0, 0);
     };
-    auto wait_reads = [&](Frag(&F)[3][kNF]) {
+    auto wait_reads = [&](Frag(&F)[SLOTS][kNF]) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      tie_frags(F);
+      tie_frags<SLOTS>(F);
     };
 
     // prologue: the first two steps in flight (steps past the end repeat the last one into a stage that is never read)
     static_for<0, kNS - 1>([&](auto s) { load_stage(decltype(s)::value, min(k0 + decltype(s)::value, k1 - 1)); });
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kND * (kNS - 2)) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ND * (kNS - 2)) : "memory");
     __builtin_amdgcn_s_barrier();
     SPCFG_SB
-    static_for<0, kNR>([&](auto r) { read_one(X, r, lds0); });
+    static_for<0, NR>([&](auto r) { read_one(X, r, lds0); });
     int cur = 0;
     for (int kt = k0; kt < k1; ++kt) {
       const int nxt = cur + 1 == kNS ? 0 : cur + 1;
@@ -201,24 +221,24 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
       const int kfill = min(kt + kNS - 1, k1 - 1) + krot;
       const int64_t ks = kfill >= KT ? kfill - KT : kfill;
       const int64_t off_a = ks * step_a, off_b = ks * step_b;
-      const unsigned fill_lds = lds0 + fill * kStage3;
-      const unsigned chunk1 = lds0 + cur * kStage3 + 16 * 256;  // rows 16..31 of this step
-      const unsigned chunk0n = lds0 + nxt * kStage3;            // rows 0..15 of the next step
+      const unsigned fill_lds = lds0 + fill * Q::STAGE;
+      const unsigned chunk1 = lds0 + cur * Q::STAGE + 16 * 256;  // rows 16..31 of this step's slots
+      const unsigned chunk0n = lds0 + nxt * Q::STAGE;            // rows 0..15 of the next step
       SPCFG_SB
       wait_reads(X);
       SPCFG_SB
       // first half: products of rows 0..15, reads of rows 16..31, loads of step kt + 2
-      static_for<0, kNM>([&](auto i) {
+      static_for<0, NM>([&](auto i) {
         constexpr int iv = decltype(i)::value;
         mfma_one(X, i);
         SPCFG_SB
-        static_for<0, 2>([&](auto q) {  // two reads behind each of the first twelve: all have landed by the end of the half
+        static_for<0, 2>([&](auto q) {  // two reads behind each of the first: all have landed by the end of the half
           constexpr int r = iv * 2 + decltype(q)::value;
-          if constexpr (r < kNR) read_one(Y, std::integral_constant<int, r>{}, chunk1);
+          if constexpr (r < NR) read_one(Y, std::integral_constant<int, r>{}, chunk1);
         });
-        static_for<0, kND>([&](auto t) {
+        static_for<0, ND>([&](auto t) {
           constexpr int tv = decltype(t)::value;
-          if constexpr ((tv * kNM) / kND == iv) dma16(gp[tv] + ((tv % 4) < 2 ? off_a : off_b), fill_lds + e_lds[tv]);
+          if constexpr ((tv * NM) / ND == iv) dma16(gp[tv] + (Q::opnd_of(tv) == 0 ? off_a : off_b), fill_lds + e_lds[tv]);
         });
         SPCFG_SB
       });
@@ -228,16 +248,16 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
       // have landed, every wavefront has its operands of step kt), then the reads of the next step's rows 0..15
       static_for<0, kNB>([&](auto i) { mfma_one(Y, i); });
       SPCFG_SB
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kND * (kNS - 2)) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ND * (kNS - 2)) : "memory");
       __builtin_amdgcn_s_barrier();
       SPCFG_SB
-      static_for<kNB, kNM>([&](auto i) {
+      static_for<kNB, NM>([&](auto i) {
         constexpr int s = decltype(i)::value - kNB;
         mfma_one(Y, i);
         SPCFG_SB
-        static_for<0, 2>([&](auto q) {
-          constexpr int r = s * 2 + decltype(q)::value;
-          if constexpr (r < kNR) read_one(X, std::integral_constant<int, r>{}, chunk0n);
+        static_for<0, Q::RPS>([&](auto q) {
+          constexpr int r = s * Q::RPS + decltype(q)::value;
+          if constexpr (r < NR) read_one(X, std::integral_constant<int, r>{}, chunk0n);
         });
         SPCFG_SB
       });
@@ -247,7 +267,7 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // every load has landed and every operand is in registers before the ring is reused
 
-    finish_tile<128, BN, 4, 2>(g.partial, g.counters, acc, tile, tile * KT, k0, k1, KT, ipw, wg, it, wg_begin, tid, &s_last,
+    finish_tile<128, Q::T3N, Q::NW, Q::NW == 4 ? 2 : 1>(g.partial, g.counters, acc, tile, tile * KT, k0, k1, KT, ipw, wg, it, wg_begin, tid, &s_last,
                      [&](floatx16(&t)[2][2]) {
       // accumulator layout of a 32x32 tile: column = lane % 32, row = 8*(v/4) + 4*(lane/32) + v%4
 #pragma unroll
@@ -275,21 +295,24 @@ __global__ void __launch_bounds__(256, 1) k_gemm_tn3(Tn3Args g, int ipw, int tot
 
 }  // namespace
 
-void launch_gemm_tn3(const Tn3Args& a, hipStream_t st) {
+namespace {
+template <int PLANES>
+void launch_tn3(const Tn3Args& a, hipStream_t st) {
+  using Q = GeoT<PLANES>;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tn3), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kLdsTn3);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_tn3<PLANES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)Q::kLds);
     attr_set = true;
   }
   if (a.KT <= 0 || a.cols <= 0) return;
-  const int tiles = ((2 * a.Np) / T3M) * ((a.cols + T3N - 1) / T3N);
+  const int tiles = ((2 * a.Np) / T3M) * ((a.cols + Q::T3N - 1) / Q::T3N);
   if (tiles > a.n_counters) { launch_refused("rule-gradient product: more output tiles than arrival counters"); return; }
   const int64_t total64 = (int64_t)tiles * a.KT;
   if (total64 >= ((int64_t)1 << 31)) { launch_refused("rule-gradient product: too many (tile, step) units"); return; }
   const int total = (int)total64;
   int Gn = 256;  // one workgroup per CU
-  if (Gn > a.max_wgs) Gn = a.max_wgs;  // the partial-tile scratch holds 2 * max_wgs slots
+  if (Gn > a.max_wgs / Q::BH) Gn = a.max_wgs / Q::BH;  // the partial-tile scratch holds 2 * max_wgs slots of 128 x 128
   if (Gn > total / 2) Gn = total / 2 > 0 ? total / 2 : 1;
   int ipw = (total + Gn - 1) / Gn;
   // A tile costs its share's steps in a row, then the last workgroup adds up KT / ipw partial tiles at about half a step's time
@@ -297,7 +320,13 @@ void launch_gemm_tn3(const Tn3Args& a, hipStream_t st) {
   // B = 7, N = 141, n <= 37 (6 tiles of 66 steps): whole call 638 -> 620 us; larger outputs have longer shares anyway.
   while (2 * (int64_t)ipw * ipw < a.KT) ++ipw;
   Gn = (total + ipw - 1) / ipw;
-  launch_k(k_gemm_tn3, dim3(Gn), dim3(256), kLdsTn3, st, a, ipw, total);
+  launch_k(k_gemm_tn3<PLANES>, dim3(Gn), dim3(64 * Q::NW), Q::kLds, st, a, ipw, total);
+}
+}  // namespace
+
+void launch_gemm_tn3(const Tn3Args& a, hipStream_t st) {
+  if (a.planes == 1) launch_tn3<1>(a, st);
+  else launch_tn3<3>(a, st);
 }
 
 }  // namespace spcfg

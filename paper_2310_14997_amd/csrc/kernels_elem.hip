@@ -336,8 +336,8 @@ k_pack_weights(const float* __restrict__ L, const float* __restrict__ R, int N, 
   }
 }
 
-// Operand planes of the rule-gradient product on planes: the three bf16 pieces of sc[s] * X[s][.] for s < S, zero for
-// the rows up to the end of the last 32-row step (the product reads whole steps).  One thread per four columns.
+// Operand planes of the rule-gradient product on planes: the three bf16 pieces (or the rounding) of sc[s] * X[s][.] for s < S, zero
+// for the rows up to the end of the last step (the product reads whole steps).  One thread per four columns.
 __global__ void k_scaled_planes(const float* __restrict__ X, int64_t ld, const float* __restrict__ sc, int64_t S,
                                 uint16_t* __restrict__ planes, int64_t plane_stride) {
   const int64_t s = blockIdx.x;
@@ -349,35 +349,13 @@ __global__ void k_scaled_planes(const float* __restrict__ X, int64_t ld, const f
     const float4 x = *reinterpret_cast<const float4*>(X + s * ld + c);
     v = make_float4(f * x.x, f * x.y, f * x.z, f * x.w);
   }
-  store_planes4(planes, 3, plane_stride, s * ld + c, v);
+  store_planes4(planes, plane_stride ? 3 : 1, plane_stride, s * ld + c, v);
 }
 
 __global__ void k_zero_plane_rows(uint16_t* __restrict__ planes, int64_t plane_stride, int64_t first, int64_t count) {
   uint16_t* p = planes + (int64_t)blockIdx.y * plane_stride + first;
   for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8; i < count; i += (int64_t)gridDim.x * blockDim.x * 8)
     *reinterpret_cast<uint4*>(p + i) = uint4{0u, 0u, 0u, 0u};  // count and first are multiples of 8 elements
-}
-
-// Xt[c][s] = bf16(sc[s] * X[s][c]) for s < S, 0 for S <= s < Spad: the reduction-major operands of the
-// rule-gradient product, transposed so that the bf16 GEMM reads both K-contiguously.
-__global__ void k_transpose_bf16(const float* __restrict__ X, int64_t ldx, const float* __restrict__ sc, int64_t S,
-                                 int64_t Spad, __bf16* __restrict__ Xt) {
-  __shared__ float tile[64][65];
-  const int64_t s0 = (int64_t)blockIdx.x * 64;
-  const int c0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 64 x 4
-#pragma unroll 4
-  for (int q = 0; q < 16; ++q) {
-    const int64_t s = s0 + ty + 4 * q;
-    float v = 0.0f;
-    if (s < S) v = X[s * ldx + c0 + tx] * (sc ? sc[s] : 1.0f);
-    tile[ty + 4 * q][tx] = v;
-  }
-  __syncthreads();
-  const int c = threadIdx.x >> 2, sq = (threadIdx.x & 3) * 16;
-  __bf16* out = Xt + (int64_t)(c0 + c) * Spad + s0 + sq;
-#pragma unroll
-  for (int j = 0; j < 16; ++j) out[j] = (__bf16)tile[sq + j][c];
 }
 
 // ------------------------------------------------------------------------------------------ leaves
@@ -1518,14 +1496,8 @@ void launch_scaled_planes(const float* X, int64_t ld, const float* sc, int64_t S
 
 void launch_zero_plane_rows(void* planes, int64_t plane_stride, int64_t ld, int64_t row0, int64_t rows, hipStream_t st) {
   const int64_t count = rows * ld;  // ld is a multiple of 64
-  launch_k(k_zero_plane_rows, dim3((unsigned)((count / 8 + 255) / 256 < 256 ? (count / 8 + 255) / 256 : 256), 3), dim3(256), 0, st,
+  launch_k(k_zero_plane_rows, dim3((unsigned)((count / 8 + 255) / 256 < 256 ? (count / 8 + 255) / 256 : 256), plane_stride ? 3 : 1), dim3(256), 0, st,
            static_cast<uint16_t*>(planes), plane_stride, row0 * ld, count);
-}
-
-void launch_transpose_bf16(const float* X, int64_t ldx, int cols, const float* sc, int64_t S, int64_t Spad, void* Xt,
-                           hipStream_t st) {
-  dim3 grid((unsigned)(Spad / 64), (unsigned)(cols / 64));
-  launch_k(k_transpose_bf16, grid, dim3(256), 0, st, X, ldx, sc, S, Spad, (__bf16*)Xt);
 }
 
 void launch_leaf_prep(const Layout& ly, const Ptrs& p, const float* log_emit, bool write_planes, hipStream_t st) {

@@ -65,7 +65,6 @@ Layout make_layout(int N, int P, int B, int n_max, int64_t S1, int64_t S2, int b
   ly.planes_bwd = bf16 ? 1 : ly.planes;
   ly.N = N; ly.P = P; ly.B = B; ly.n_max = n_max; ly.bf16 = bf16;
   ly.G = per_sentence ? B : 1;
-  ly.S1pad = (S1 + 63) / 64 * 64; ly.S2pad = (S2 + 63) / 64 * 64;
   ly.Np = round_up(N, kPad);
   ly.Pp = round_up(P, kPad);
   ly.S1 = S1; ly.S2 = S2; ly.Sall = S1 + S2;
@@ -115,25 +114,20 @@ Layout make_layout(int N, int P, int B, int n_max, int64_t S1, int64_t S2, int b
     ly.Wtn3 = take(6 * 2 * (size_t)ly.Np * ly.Np); ly.Wtp3 = take(6 * 2 * (size_t)ly.Np * ly.Pp);
   }
   if (per_sentence) { ly.sentrows = take(i4 * (size_t)S2); ly.sentoff = take(i4 * (size_t)B); }
-  if (bf16) {
-    ly.UVt_n = take(2 * 2 * (size_t)ly.Np * ly.S2pad);
-    ly.Tt = take(2 * (size_t)ly.Np * ly.S2pad);
-    ly.UVt_p = take(2 * 2 * (size_t)ly.Np * ly.S1pad);
-    ly.Et = take(2 * (size_t)ly.Pp * ly.S1pad);
-  }
   if (ly.planes > 0) {
     ly.Tb = take(2 * (size_t)ly.planes * S2 * ly.Np);
     ly.leafEb = take(2 * (size_t)ly.planes * S1 * ly.Pp);
   }
-  // rule gradients on planes (fp32 mode, shared grammar): the adjoint planes get 32 zeroed rows behind the last row (the
-  // product reads whole 32-row steps), and the scaled inside vectors get planes of their own, padded to whole steps
-  ly.tn3 = ly.planes_bwd == 3;
-  ly.S1p32 = (S1 + 31) / 32 * 32; ly.S2p32 = (S2 + 31) / 32 * 32;
-  ly.uvb_plane = (ly.Sall + (ly.tn3 ? 32 : 0)) * 2 * ly.Np;
+  // rule gradients on planes (shared grammar): the adjoint planes get the zeroed rows of a step behind the last row (the
+  // product reads whole steps), and the scaled inside vectors get planes of their own, padded to whole steps
+  ly.tn3 = shared ? ly.planes_bwd : 0;
+  const int64_t step = ly.tn3 ? kTn3Rows(ly.tn3) : 1;
+  ly.S1p = (S1 + step - 1) / step * step; ly.S2p = (S2 + step - 1) / step * step;
+  ly.uvb_plane = (ly.Sall + (ly.tn3 ? step : 0)) * 2 * ly.Np;
   if (ly.planes_bwd > 0) ly.UVb = take(2 * (size_t)ly.planes_bwd * ly.uvb_plane);
   if (ly.tn3) {
-    ly.Tg3 = take(6 * (size_t)ly.S2p32 * ly.Np);
-    ly.Eg3 = take(6 * (size_t)ly.S1p32 * ly.Pp);
+    ly.Tg3 = take(2 * ly.tn3 * (size_t)ly.S2p * ly.Np);
+    ly.Eg3 = take(2 * ly.tn3 * (size_t)ly.S1p * ly.Pp);
   }
   ly.leafE = take(f4 * (size_t)S1 * ly.Pp);
   ly.T = take(f4 * (size_t)S2 * ly.Np);
@@ -159,7 +153,6 @@ Ptrs resolve(const Layout& ly, void* ws) {
   p.partial = (float*)(b + ly.partial); p.counters = (int32_t*)(b + ly.counters);
   p.sentrows = (int32_t*)(b + ly.sentrows); p.sentoff = (int32_t*)(b + ly.sentoff);
   p.Tb = ly.planes ? b + ly.Tb : nullptr; p.UVb = ly.planes_bwd ? b + ly.UVb : nullptr; p.leafEb = ly.planes ? b + ly.leafEb : nullptr;
-  p.UVt_n = b + ly.UVt_n; p.Tt = b + ly.Tt; p.UVt_p = b + ly.UVt_p; p.Et = b + ly.Et;
   p.Tg3 = b + ly.Tg3; p.Eg3 = b + ly.Eg3;
   p.Wn3 = b + ly.Wn3; p.Wp3 = b + ly.Wp3; p.Wtn3 = b + ly.Wtn3; p.Wtp3 = b + ly.Wtp3;
   p.Wn = (float*)(b + ly.Wn); p.Wp = (float*)(b + ly.Wp); p.Wtn = (float*)(b + ly.Wtn); p.Wtp = (float*)(b + ly.Wtp);
@@ -571,7 +564,7 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
     {
       Scope s(SPCFG_PROF_SPLIT_BWD, split_bytes);
       // (the rule-gradient product on planes reads the adjoint planes of every row)
-      launch_split_bwd(ly, p, w, row0, rows, ly.bf16 || (ly.tn3 && !fp32_mfma) || gemm_nt_reads_planes(a), st);
+      launch_split_bwd(ly, p, w, row0, rows, ly.bf16 || ly.tn3 || gemm_nt_reads_planes(a), st);
     }
     {
       Scope s(SPCFG_PROF_GEMM_BWD, gemm_flop);
@@ -597,22 +590,24 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
       t.Bm = p.leafE; t.ldb = Pp; t.cols = ly.P; t.col0 = ly.N;
       t.grp_kt_max = (n_longest + 31) / 32;
       launch_gemm_tn(t, st);
-    } else if (ly.tn3 && !fp32_mfma) {
+    } else if (ly.tn3) {
       // on planes: the adjoint rows as their producers cut them, the inside vectors times the span scale cut here
-      launch_scaled_planes(p.T, Np, p.gsc + ly.S1, ly.S2, ly.S2p32, p.Tg3, ly.S2p32 * Np, st);
-      launch_scaled_planes(p.leafE, Pp, p.gsc, ly.S1, ly.S1p32, p.Eg3, ly.S1p32 * Pp, st);
-      launch_zero_plane_rows(p.UVb, ly.uvb_plane, 2 * Np, ly.Sall, 32, st);
+      const int64_t step = kTn3Rows(ly.tn3), planes = ly.tn3 == 3 ? 1 : 0;
+      launch_scaled_planes(p.T, Np, p.gsc + ly.S1, ly.S2, ly.S2p, p.Tg3, planes * ly.S2p * Np, st);
+      launch_scaled_planes(p.leafE, Pp, p.gsc, ly.S1, ly.S1p, p.Eg3, planes * ly.S1p * Pp, st);
+      launch_zero_plane_rows(p.UVb, planes * ly.uvb_plane, 2 * Np, ly.Sall, step, st);
       Tn3Args t{};
+      t.planes = ly.tn3;
       t.partial = p.partial; t.counters = p.counters; t.max_wgs = ly.gemm_wgs; t.n_counters = ly.n_counters;
       t.Np = (int)Np; t.N = ly.N; t.gL = grad_L; t.gR = grad_R; t.ldg = ly.N + ly.P; t.accumulate = acc;
       t.a_plane = ly.uvb_plane; t.lda = 2 * Np;
       t.A3 = static_cast<const uint16_t*>(p.UVb) + ly.S1 * 2 * Np; t.B3 = static_cast<const uint16_t*>(p.Tg3);
-      t.b_plane = ly.S2p32 * Np; t.ldb = Np; t.KT = (int)(ly.S2p32 / 32); t.cols = ly.N; t.col0 = 0;
+      t.b_plane = ly.S2p * Np; t.ldb = Np; t.KT = (int)(ly.S2p / step); t.cols = ly.N; t.col0 = 0;
       launch_gemm_tn3(t, st);
       t.A3 = static_cast<const uint16_t*>(p.UVb); t.B3 = static_cast<const uint16_t*>(p.Eg3);
-      t.b_plane = ly.S1p32 * Pp; t.ldb = Pp; t.KT = (int)(ly.S1p32 / 32); t.cols = ly.P; t.col0 = ly.N;
+      t.b_plane = ly.S1p * Pp; t.ldb = Pp; t.KT = (int)(ly.S1p / step); t.cols = ly.P; t.col0 = ly.N;
       launch_gemm_tn3(t, st);
-    } else if (!ly.bf16) {
+    } else {
       TnArgs t{};
       t.fp32_mfma = fp32_mfma;
       t.partial = p.partial; t.counters = p.counters; t.max_wgs = ly.gemm_wgs; t.n_counters = ly.n_counters;
@@ -622,20 +617,6 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
       launch_gemm_tn(t, st);
       t.A = p.UV; t.Bm = p.leafE; t.ldb = Pp; t.sc = p.gsc; t.S = ly.S1; t.cols = ly.P; t.col0 = ly.N;
       launch_gemm_tn(t, st);
-    } else {
-      // both operands transposed to bf16 (span scale folded into the adjoint rows), then the NT kernel
-      launch_transpose_bf16(p.UV + ly.S1 * 2 * Np, 2 * Np, (int)(2 * Np), p.gsc + ly.S1, ly.S2, ly.S2pad, p.UVt_n, st);
-      launch_transpose_bf16(p.T, Np, (int)Np, nullptr, ly.S2, ly.S2pad, p.Tt, st);
-      launch_transpose_bf16(p.UV, 2 * Np, (int)(2 * Np), p.gsc, ly.S1, ly.S1pad, p.UVt_p, st);
-      launch_transpose_bf16(p.leafE, Pp, (int)Pp, nullptr, ly.S1, ly.S1pad, p.Et, st);
-      NtArgs a{};
-      a.partial = p.partial; a.counters = p.counters; a.max_wgs = ly.gemm_wgs; a.n_counters = ly.n_counters; a.a_bf16 = 1; a.b_bf16 = 1;
-      a.epilogue = NT_EPI_GRAD; a.gL = grad_L; a.gR = grad_R; a.ldg = ly.N + ly.P; a.Np = (int)Np; a.Nvalid = ly.N;
-      a.accumulate = acc; a.rows = (int)(2 * Np);
-      a.A = p.UVt_n; a.lda = ly.S2pad; a.Bm = p.Tt; a.ldb = ly.S2pad; a.K = (int)ly.S2pad; a.cols = ly.N; a.col0 = 0;
-      launch_gemm_nt(a, st);
-      a.A = p.UVt_p; a.lda = ly.S1pad; a.Bm = p.Et; a.ldb = ly.S1pad; a.K = (int)ly.S1pad; a.cols = ly.P; a.col0 = ly.N;
-      launch_gemm_nt(a, st);
     }
   }
   return hip_status();

@@ -61,20 +61,18 @@ struct Layout {
                          // grammar per sentence), 2 hi + lo (bf16 mode, shared grammar), 3 the exact cut hi + mid + lo
                          // of every fp32 value (fp32 mode, shared grammar)
   int planes_bwd;        // the same for the adjoint rows of the reverse products: 0, 1 (bf16 mode) or 3
-  int tn3;               // rule gradients on operand planes (fp32 mode, shared grammar): Tg3 / Eg3 below, padded UVb
-  int64_t S1p32, S2p32;  // row counts rounded up to whole 32-row steps of that product
-  int64_t uvb_plane;     // elements between the planes of UVb: (Sall [+ 32 zeroed rows]) * 2Np
+  int tn3;               // planes of the rule-gradient product's operands (shared grammar): Tg3 / Eg3 below, padded UVb; 0: k_gemm_tn
+  int64_t S1p, S2p;      // row counts rounded up to whole steps of that product
+  int64_t uvb_plane;     // elements between the planes of UVb: (Sall [+ the zeroed rows of a step]) * 2Np
   int fwd_fp32;          // bf16 mode with one grammar per sentence: the forward products read fp32 operands (Wn / Wp are
                          // fp32 then, Wtn / Wtp bf16)
-  int64_t S1pad, S2pad;  // row counts rounded up to 64 (K of the bf16 rule-gradient product)
   int64_t S1, S2, Sall;  // leaf rows, rows of width >= 2, all rows
   // byte offsets into the workspace
   size_t lens, rowbase, row_b, row_i, rootmask, rootrow, mexp, uexp, tmaxb, umaxb, hmaxb, zmaxb, gsc, xs, ztil, rmax;
   size_t leafE, T, HZ, UV, BH, Wn, Wp, Wtn, Wtp, partial, counters;
   size_t colmax;  // [G][2][Np + Pp]: largest entry of every column of L (then of R), nonterminal columns first
   size_t Wn3, Wp3, Wtn3, Wtp3;  // the packed panels once more, cut into bf16 planes: Wn3 / Wp3 `planes` of them (if >= 2), Wtn3 / Wtp3 three (planes_bwd == 3)
-  size_t UVt_n, Tt, UVt_p, Et;  // bf16 mode only
-  size_t Tg3, Eg3;              // tn3: three bf16 planes of gsc[s] * T[s] ([3][S2p32][Np]) and of gsc[s] * leafE[s] ([3][S1p32][Pp])
+  size_t Tg3, Eg3;              // tn3: bf16 planes of gsc[s] * T[s] ([tn3][S2p][Np]) and of gsc[s] * leafE[s] ([tn3][S1p][Pp])
   size_t Tb, UVb, leafEb;       // planes > 0: bf16 planes of T, UV, leafE ([planes][rows][cols]), written by their producers
   size_t sentrows, sentoff;     // per-sentence grammars only: rows of width >= 2 listed sentence by sentence, first entry of each
   // bands: widths kBandW * k .. + kBandW - 1 take their split-point sums (reverse: parent sums) partly in one pass
@@ -99,7 +97,6 @@ struct Ptrs {  // device pointers resolved from a Layout
   float* colmax;
   float *gsc, *xs, *ztil, *rmax;
   float *leafE, *T, *HZ, *UV, *BH, *Wn, *Wp, *Wtn, *Wtp, *partial;  // W* hold bf16 data in bf16 mode
-  void *UVt_n, *Tt, *UVt_p, *Et;
   void *Tg3, *Eg3;
   void *Tb, *UVb, *leafEb;  // null when the layout has no planes
   void *Wn3, *Wp3, *Wtn3, *Wtp3;
@@ -143,8 +140,6 @@ void launch_refused(const char* what);
 void launch_plan(const Layout& ly, const Ptrs& p, const LenArg& lens, hipStream_t st);
 void launch_plan_sentrows(const Layout& ly, const Ptrs& p, hipStream_t st);
 void launch_pack_weights(const Layout& ly, const Ptrs& p, const float* L, const float* R, hipStream_t st);
-void launch_transpose_bf16(const float* X, int64_t ldx, int cols, const float* sc, int64_t S, int64_t Spad, void* Xt,
-                           hipStream_t st);
 void launch_leaf_prep(const Layout& ly, const Ptrs& p, const float* log_emit, bool write_planes, hipStream_t st);
 // write_planes: also write the operand planes of the rows (the projection launch of this width reads them)
 void launch_split_fwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int64_t rows, bool write_planes,
@@ -159,7 +154,7 @@ void launch_zero_pad_emit(const Layout& ly, const Ptrs& p, float* grad_log_emit,
 void launch_span_marginals(const Layout& ly, const Ptrs& p, float* mu, int32_t* label, hipStream_t st);
 
 // C[r][c] = sum_k A[r][k] * Bm[c][k]   (both operands K-contiguous), r < rows, c < cols, K % 32 == 0.
-enum NtEpilogue { NT_EPI_ROWSCALE = 0, NT_EPI_MASKROWS = 1, NT_EPI_LEAF_EMIT = 2, NT_EPI_GRAD = 3 };
+enum NtEpilogue { NT_EPI_ROWSCALE = 0, NT_EPI_MASKROWS = 1, NT_EPI_LEAF_EMIT = 2 };
 struct NtArgs {
   // fp32 mode: A, Bm are float.  bf16 mode (a_bf16 = b_bf16 = 1): both point to bf16 data.  lda/ldb count
   // elements; K % 64 == 0 in bf16 mode.
@@ -175,8 +170,6 @@ struct NtArgs {
   const float* E; int64_t lde;
   const int32_t* rowexp;
   const int32_t* row_b; const int32_t* row_i; int n_max;
-  // GRAD: rows are stacked parents; row r -> (r < Np ? gL : gR)[(r mod Np) * ldg + col0 + c], rows >= Nvalid per half dropped
-  float* gL; float* gR; int64_t ldg; int col0, Np, Nvalid, accumulate;
   // work sharing across workgroups: scratch for partial tiles and per-tile arrival counters (zero between launches)
   float* partial; int32_t* counters; int max_wgs;
   int n_counters;  // capacity of `counters`: a launch with more output tiles is refused (see launch_refused)
@@ -240,24 +233,27 @@ struct TnArgs {
 };
 void launch_gemm_tn(const TnArgs& a, hipStream_t st);
 
-// The same product on operands that their producers have cut into three bf16 planes (gemm_tn3.hip): A3 = planes of the
-// adjoint rows UV ([3][..][lda], planes a_plane elements apart, pointing at the first row of the block), B3 = planes of
-// scale[s] * (inside vector of row s), zero from row S to the end of the last 32-row step.  A3 must be readable (and
-// finite) for 31 rows past the end of the reduction.
+// The same product on operands that their producers have cut into three bf16 planes, or rounded to one (gemm_tn3.hip): A3 =
+// planes of the adjoint rows UV ([planes][..][lda], a_plane elements apart, pointing at the first row of the block), B3 = planes
+// of scale[s] * (inside vector of row s), zero from row S to the end of the last step of kTn3Rows(planes) rows.  A3 must be
+// readable (and finite) to the end of that step.
+constexpr int kTn3Rows(int planes) { return planes == 1 ? 64 : 32; }
 struct Tn3Args {
+  int planes;                       // 3, or 1 (bf16 mode)
   const uint16_t* A3; int64_t a_plane, lda;
   const uint16_t* B3; int64_t b_plane, ldb;
-  int KT;                           // 32-row steps of the reduction: ceil(S / 32)
+  int KT;                           // steps of the reduction
   int Np, N, cols;                  // as in TnArgs
   float* gL; float* gR; int64_t ldg; int col0;
   int accumulate;
   float* partial; int32_t* counters; int max_wgs, n_counters;
 };
 void launch_gemm_tn3(const Tn3Args& a, hipStream_t st);
-// planes of sc[s] * X[s][.] for s < S and of zero for S <= s < Srows (X is [S x ld], ld a multiple of 4)
+// planes of sc[s] * X[s][.] for s < S and of zero for S <= s < Srows (X is [S x ld], ld a multiple of 4): three, plane_stride
+// elements apart, or (plane_stride 0) the bf16 rounding alone
 void launch_scaled_planes(const float* X, int64_t ld, const float* sc, int64_t S, int64_t Srows, void* planes,
                           int64_t plane_stride, hipStream_t st);
-// zeroes rows [row0, row0 + rows) of every plane of a [3][..][ld] array of bf16
+// zeroes rows [row0, row0 + rows) of every plane of a [3][..][ld] array of bf16 (plane_stride 0: of its one plane)
 void launch_zero_plane_rows(void* planes, int64_t plane_stride, int64_t ld, int64_t row0, int64_t rows, hipStream_t st);
 
 }  // namespace spcfg
