@@ -347,6 +347,7 @@ bool gemm_nt_reads_planes(const NtArgs& a) {
 
 void launch_gemm_nt(const NtArgs& a, hipStream_t st) {
   if (a.rows <= 0 || a.cols <= 0) return;
+  if (a.step) { launch_step(*a.step, st); return; }
   if (a.b_bf16) { launch_gemm_nt16(a, st); return; }
   if (a.planes3) {
     // tall row tiles: the kernel on pre-cut operands; short ones keep the fp32 operands (fewer panel bytes)

@@ -266,11 +266,13 @@ int make_plan(const spcfg_config* cfg, const int32_t* lengths, int B, int n_max,
 // start/stop event pair (see launch_k), so a class's time is the sum of its kernels' own durations.
 // The counters are process-wide; a mutex guards them, and the class that a thread's launches are charged to is that
 // thread's own, so concurrent callers do not corrupt the records (their launches simply add up).
-thread_local int t_cur_cls = -1;
+// A launch of two classes at once (a product together with the sums that wait for it) counts in both and is charged to
+// each with half its time.
+thread_local int t_cur_cls = -1, t_cur_also = -1;
 struct Prof {
   std::atomic<bool> on{false};
   std::mutex mu;
-  struct Rec { hipEvent_t a, b; int cls; };
+  struct Rec { hipEvent_t a, b; int cls, also; };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
   double work[SPCFG_PROF_CLASSES] = {0};
@@ -288,14 +290,16 @@ struct Prof {
 } g_prof;
 
 struct Scope {
-  int prev;
-  Scope(int c, double work) : prev(t_cur_cls) {
+  int prev, prev_also;
+  Scope(int c, double work, int also = -1, double also_work = 0.0) : prev(t_cur_cls), prev_also(t_cur_also) {
     if (!g_prof.on) return;
     t_cur_cls = c;
+    t_cur_also = also;
     std::lock_guard<std::mutex> lock(g_prof.mu);
     g_prof.work[c] += work;
+    if (also >= 0) g_prof.work[also] += also_work;
   }
-  ~Scope() { t_cur_cls = prev; }
+  ~Scope() { t_cur_cls = prev; t_cur_also = prev_also; }
 };
 
 }  // namespace
@@ -307,6 +311,7 @@ LaunchEvents prof_launch_events() {
   if (!g_prof.on || t_cur_cls < 0) return ev;
   std::lock_guard<std::mutex> lock(g_prof.mu);
   ++g_prof.launches[t_cur_cls];
+  if (t_cur_also >= 0) ++g_prof.launches[t_cur_also];
   ev.start = g_prof.get();
   ev.stop = g_prof.get();
   if (!ev.start || !ev.stop) {
@@ -314,7 +319,7 @@ LaunchEvents prof_launch_events() {
     if (ev.stop) g_prof.pool.push_back(ev.stop);
     return LaunchEvents{};
   }
-  g_prof.recs.push_back({ev.start, ev.stop, t_cur_cls});
+  g_prof.recs.push_back({ev.start, ev.stop, t_cur_cls, t_cur_also});
   return ev;
 }
 
@@ -494,11 +499,74 @@ Ptrs panels_read(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfm
   return q;
 }
 
+// Whether the product of width w and the sums that wait for it go in one launch (gemm_step.hip): 0 not, 1 in small tiles, 2 in tall ones.
+// Small tiles pay while all workgroups start at once, one a CU, and the product's K is short.  The grid has a tile for every
+// start of the longest sentence in every sentence, and those without spans cost their dispatch (N = 512, B = 32, n = 10 .. 30
+// training 937 us separate, 963 us with up to four grids of the chip, 935 us with two).  Tall tiles, forward only, where 64
+// or 128 padded nonterminals leave most lanes of the separate sums idle: N = 64, B = 128, n = 30 scoring 381 -> 245 us; N = 128,
+// B = 30, n = 20 .. 40 390 -> 310 us, but with two blocks of 64 and more than kStepTallTerms terms they fall behind (N = 124, B = 38,
+// n = 25 .. 71: 915 us separate, 903 us so, 957 us without the limit), as with more nonterminals (N = 256, B = 12: 278, 289)
+// and in reverse (N = 64, B = 128: 100 us slower).
+constexpr int kStepWgs = 256, kStepGrid = 512, kStepK = 512, kStepTallNp = 64, kStepTallTerms = 24;
+int step_form(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfma, int w, bool fwd) {
+  if (ly.bf16 || fp32_mfma) return 0;
+  const int next = fwd ? w + 1 : w - 1;
+  if (next < 1 || next > ly.n_long || plan.cnt[w] == 0) return 0;
+  // (a band's launch has to come between)
+  if (fwd ? ly.band_fwd[next / kBandW] && next % kBandW == 0 : ly.band_bwd[next / kBandW] && next == band_top(ly, next / kBandW * kBandW))
+    return 0;
+  if ((fwd ? (w == 1 ? ly.Pp : ly.Np) : ly.Np) > kStepK) return 0;
+  double flop;
+  // (the forward launch writes no operand planes of the sums)
+  if (fwd && next < ly.n_long && gemm_nt_reads_planes(forward_product(plan, ly, p, fp32_mfma, next, &flop))) return 0;
+  const int terms = fwd && ly.band_fwd[next / kBandW] ? 2 * (next % kBandW) : next - 1;
+  const bool tall_too = fwd && (ly.Np <= kStepTallNp || (ly.Np <= 2 * kStepTallNp && terms <= kStepTallTerms));
+  for (int tall = 0; tall <= (tall_too ? 1 : 0); ++tall) {
+    const int per = step_spans(tall);
+    int64_t tiles = 0;
+    for (int b = 0; b < ly.B; ++b) {
+      const int sums = plan.lens.v[b] > next || (fwd && plan.lens.v[b] == next) ? plan.lens.v[b] - next + 1 : 0;
+      tiles += (sums + per - 1) / per;
+    }
+    // (the grid has a tile for every start of the longest sentence in every sentence; those without spans end at once)
+    const int64_t cols = ly.Np / step_nonterminals(tall), grid = (int64_t)ly.B * ((ly.n_long - next + per) / per);
+    if (tiles * cols <= kStepWgs && grid * cols <= kStepGrid) return 1 + tall;
+  }
+  return 0;
+}
+StepArgs step_args(const Layout& ly, const Ptrs& p, int w, bool fwd, int tall) {
+  StepArgs s{};
+  s.forward = fwd; s.tall = tall; s.w = w;
+  s.B = ly.B; s.Np = ly.Np; s.Pp = ly.Pp; s.n_long = ly.n_long; s.stride = (ly.n_max + 1) * ly.B; s.per_sentence = ly.G > 1;
+  s.S1 = ly.S1; s.lens = p.lens; s.rowtab = p.rowbase;
+  s.K = fwd ? (w == 1 ? ly.Pp : ly.Np) : 2 * ly.Np;
+  s.A = fwd ? (w == 1 ? p.leafE : p.T) : p.UV;
+  s.a_row0 = fwd && w > 1 ? ly.S1 : 0;
+  s.Bm = fwd ? (w == 1 ? p.Wp : p.Wn) : p.Wtn;
+  s.b_stride = ly.G > 1 ? 2 * (int64_t)ly.Np * (fwd && w == 1 ? ly.Pp : ly.Np) : 0;
+  s.HZ = p.HZ; s.T = p.T; s.UV = p.UV; s.BH = p.BH;
+  s.mexp = p.mexp; s.uexp = p.uexp; s.tmaxb = p.tmaxb; s.umaxb = p.umaxb; s.hmaxb = p.hmaxb; s.zmaxb = p.zmaxb;
+  s.gsc = p.gsc; s.xs = p.xs; s.rootmask = p.rootmask; s.colmax = p.colmax;
+  const int next = fwd ? w + 1 : w - 1, w0 = next / kBandW * kBandW;
+  if (fwd) s.w0 = ly.band_fwd[next / kBandW] ? w0 : 0;
+  else s.w0 = ly.band_bwd[next / kBandW] ? w0 + kBandW : 0;
+  return s;
+}
+
+bool with_step(NtArgs& a, StepArgs* step, const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfma, int w, bool fwd) {
+  const int form = gemm_nt_reads_planes(a) ? 0 : step_form(plan, ly, p, fp32_mfma, w, fwd);
+  if (form == 0) return false;
+  *step = step_args(ly, p, w, fwd, form - 1);
+  if (ly.tn3) { step->UVb = p.UVb; step->planes = ly.planes_bwd; step->plane_stride = ly.uvb_plane; }  // (rule gradients read them)
+  a.step = step;
+  return true;
+}
+
 int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const Ptrs& p, const float* log_root,
             const float* L, const float* R, const float* log_emit, float* logZ, bool with_backward, hipStream_t st) {
   const int n_max = ly.n_max;
   const int fp32_mfma = (cfg->flags & SPCFG_FLAG_FP32_MFMA) ? 1 : 0;
-  const NtArgs leaf = forward_product(plan, ly, p, fp32_mfma, 1, nullptr);
+  NtArgs leaf = forward_product(plan, ly, p, fp32_mfma, 1, nullptr);
   {
     Scope s(SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * 3 + 8.0 * ly.S1 * ly.P);
     launch_plan(ly, p, plan.lens, st);
@@ -507,8 +575,12 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
     // operand planes are written only for the launches that read them (bf16 mode: all of them)
     launch_leaf_prep(ly, p, log_emit, (ly.bf16 && !ly.fwd_fp32) || gemm_nt_reads_planes(leaf), st);
   }
+  StepArgs step;
+  bool summed;  // the sums of the next width were taken in the launch of the last product
   {
-    Scope s(SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.P * ly.S1);
+    summed = with_step(leaf, &step, plan, ly, p, fp32_mfma, 1, true);
+    Scope s(SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.P * ly.S1, summed ? SPCFG_PROF_SPLIT_FWD : -1,
+            summed && g_prof.on ? split_fwd_bytes(plan, ly, 2) : 0.0);
     launch_gemm_nt(leaf, st);
   }
   for (int w = 2; w <= n_max; ++w) {
@@ -516,17 +588,21 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
     if (rows == 0) continue;
     const double split_bytes = g_prof.on ? split_fwd_bytes(plan, ly, w) : 0.0;
     if (w == n_max) {  // every span of the largest width is a root span: never a child, not projected
-      Scope s(SPCFG_PROF_SPLIT_FWD, split_bytes);
-      launch_split_fwd(ly, p, w, row0, rows, false, st);
+      if (!summed) {
+        Scope s(SPCFG_PROF_SPLIT_FWD, split_bytes);
+        launch_split_fwd(ly, p, w, row0, rows, false, st);
+      }
       break;
     }
     double skipped = 0.0;  // flop of the projections that the launch leaves out
-    const NtArgs a = forward_product(plan, ly, p, fp32_mfma, w, &skipped);
-    {
+    NtArgs a = forward_product(plan, ly, p, fp32_mfma, w, &skipped);
+    if (!summed) {
       Scope s(SPCFG_PROF_SPLIT_FWD, split_bytes);
       launch_split_fwd(ly, p, w, row0, rows, (ly.bf16 && !ly.fwd_fp32) || gemm_nt_reads_planes(a), st);
     }
-    Scope s(SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.N * rows - skipped);
+    summed = with_step(a, &step, plan, ly, p, fp32_mfma, w, true);
+    Scope s(SPCFG_PROF_GEMM_FWD, 4.0 * ly.N * (double)ly.N * rows - skipped, summed ? SPCFG_PROF_SPLIT_FWD : -1,
+            summed && g_prof.on ? split_fwd_bytes(plan, ly, w + 1) : 0.0);
     launch_gemm_nt(a, st);
   }
   {
@@ -555,19 +631,23 @@ int backward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const 
     launch_root_bwd(ly, p, log_root, grad_logZ, grad_log_root, acc, st);
     launch_zero_pad_emit(ly, p, grad_log_emit, st);
   }
+  StepArgs step;
+  bool summed = false;  // the sums of this width were taken in the launch of the last product
   for (int w = n_max - 1; w >= 1; --w) {  // spans of width n_max are all roots
     const int64_t row0 = plan.off[w], rows = plan.cnt[w];
     if (rows == 0) continue;
     const double split_bytes = g_prof.on ? split_bwd_bytes(plan, ly, w) : 0.0;
     double gemm_flop;
-    const NtArgs a = reverse_product(plan, ly, p, fp32_mfma, w, grad_log_emit, &gemm_flop);
-    {
+    NtArgs a = reverse_product(plan, ly, p, fp32_mfma, w, grad_log_emit, &gemm_flop);
+    if (!summed) {
       Scope s(SPCFG_PROF_SPLIT_BWD, split_bytes);
       // (the rule-gradient product on planes reads the adjoint planes of every row)
       launch_split_bwd(ly, p, w, row0, rows, ly.bf16 || ly.tn3 || gemm_nt_reads_planes(a), st);
     }
     {
-      Scope s(SPCFG_PROF_GEMM_BWD, gemm_flop);
+      summed = w >= 2 && with_step(a, &step, plan, ly, p, fp32_mfma, w, false);
+      Scope s(SPCFG_PROF_GEMM_BWD, gemm_flop, summed ? SPCFG_PROF_SPLIT_BWD : -1,
+              summed && g_prof.on ? split_bwd_bytes(plan, ly, w - 1) : 0.0);
       launch_gemm_nt(a, st);
     }
   }
@@ -814,7 +894,8 @@ int spcfg_profile_read(double* ms, int64_t* launches, double* work) {
   for (auto& r : g_prof.recs) {
     float t = 0.0f;
     if (hipEventSynchronize(r.b) != hipSuccess || hipEventElapsedTime(&t, r.a, r.b) != hipSuccess) rc = SPCFG_ERR_HIP;
-    ms[r.cls] += t;
+    ms[r.cls] += r.also >= 0 ? 0.5 * t : t;
+    if (r.also >= 0) ms[r.also] += 0.5 * t;
   }
   g_prof.recycle();
   for (int c = 0; c < SPCFG_PROF_CLASSES; ++c) {

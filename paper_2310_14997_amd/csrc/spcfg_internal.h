@@ -153,6 +153,33 @@ void launch_split_bwd(const Layout& ly, const Ptrs& p, int w, int64_t row0, int6
 void launch_zero_pad_emit(const Layout& ly, const Ptrs& p, float* grad_log_emit, hipStream_t st);
 void launch_span_marginals(const Layout& ly, const Ptrs& p, float* mu, int32_t* label, hipStream_t st);
 
+// A projection product and the split-point sums that only wait for it, in one launch (gemm_step.hip): forward the product of
+// width w and the sums of width w + 1, reverse the product of width w and the parents' sums of width w - 1.
+struct StepArgs {
+  int forward, tall, w;  // tall: tiles of 32 spans and 32 nonterminals instead of 16 and 16
+  int B, Np, Pp, n_long, stride, per_sentence;
+  int64_t S1;
+  const int32_t *lens, *rowtab;
+  // the product's operands, fp32: row r of the chart at A + (r - a_row0) * K, the panel's rows K apart, panels b_stride apart
+  const void *A, *Bm;
+  int64_t a_row0, b_stride;
+  int K;
+  float *HZ, *T, *UV, *BH;
+  void* UVb;  // reverse: operand planes of the adjoints, null if nothing reads them
+  int planes;
+  int64_t plane_stride;
+  int32_t *mexp, *uexp;
+  uint32_t *tmaxb, *umaxb;
+  int32_t *hmaxb, *zmaxb;
+  float *gsc, *xs;
+  int32_t* rootmask;
+  const float* colmax;
+  int w0;  // 0: all terms; forward: first width of the band of width w + 1; reverse: first width above the band of width w - 1
+};
+constexpr int step_spans(int tall) { return tall ? 31 : 15; }         // sums of a tile
+constexpr int step_nonterminals(int tall) { return tall ? 32 : 16; }
+void launch_step(const StepArgs& a, hipStream_t st);  // (called through launch_gemm_nt)
+
 // C[r][c] = sum_k A[r][k] * Bm[c][k]   (both operands K-contiguous), r < rows, c < cols, K % 32 == 0.
 enum NtEpilogue { NT_EPI_ROWSCALE = 0, NT_EPI_MASKROWS = 1, NT_EPI_LEAF_EMIT = 2 };
 struct NtArgs {
@@ -195,6 +222,7 @@ struct NtArgs {
   // of the bf16 mode).  planes3 = 1: A3 = A and Bm3 = Bm are bf16 (the other products of the bf16 mode).
   int planes3; int64_t a_plane, b_plane;
   const void* A3; const void* Bm3;
+  const StepArgs* step;  // host only; if set, the launch also takes the sums that wait for this product
   int parts;
   int prt_row0[3], prt_rows[3], prt_c0[3], prt_kbeg[3], prt_kt[3];
 };
