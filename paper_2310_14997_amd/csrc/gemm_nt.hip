@@ -345,10 +345,23 @@ bool gemm_nt_reads_planes(const NtArgs& a) {
   return a.planes3 <= 2 || nt::chosen_bm(a) == 128;
 }
 
+namespace { constexpr int kShortK16 = 1024; }
+
 void launch_gemm_nt(const NtArgs& a, hipStream_t st) {
   if (a.rows <= 0 || a.cols <= 0) return;
   if (a.step) { launch_step(*a.step, st); return; }
   if (a.b_bf16) { launch_gemm_nt16(a, st); return; }
+  // One bf16 plane: launches of few rows with a short K take the kernel that stages tiles through registers, whose two workgroups a
+  // CU and finer shares suit them (scoring with single operands N = 64, n = 20 262 us on the planes kernel, 242 us so; N = 512, B = 4
+  // 432, 404); from K = 2000 on the planes kernel is faster at every row count (N = 2000, B = 2: 770, 842).
+  if (a.planes3 == 1 && a.K <= kShortK16 && nt::chosen_bm(a) < 128) {
+    NtArgs b = a;  // as one product: without the parts, which only the planes kernel knows
+    if (a.parts == 2) b.cols = a.prt_c0[1] + a.cols;
+    b.parts = 0;
+    b.b_bf16 = 1;
+    launch_gemm_nt16(b, st);
+    return;
+  }
   if (a.planes3) {
     // tall row tiles: the kernel on pre-cut operands; short ones keep the fp32 operands (fewer panel bytes)
     if (gemm_nt_reads_planes(a)) { launch_gemm_nt3(a, st); return; }

@@ -1,6 +1,7 @@
-// bf16-operand MFMA GEMM (fp32 accumulate) for the projections in SPCFG_PRECISION_BF16 with one grammar per sentence:
-//   C[r][c] = sum_k A[r][k] * Bm[c][k],  Bm = packed bf16 [L;R] panel of the row's sentence, A = the bf16 copy of the chart
-// rows that their producers write next to the fp32 ones.
+// bf16-operand MFMA GEMM (fp32 accumulate) for the projections in SPCFG_PRECISION_BF16, with one grammar per sentence and for
+// launches too small for the planes kernel (see launch_gemm_nt):
+//   C[r][c] = sum_k A[r][k] * Bm[c][k],  Bm = packed bf16 [L;R] panel, A = the bf16 copy of the chart rows that
+// their producers write next to the fp32 ones.
 // Same tiling, work sharing and epilogues as the fp32 kernel; one K-step is 64 values, and every
 // MFMA operand is one 16-byte LDS read of 8 consecutive bf16 (v_mfma_f32_32x32x16_bf16: lane l holds row
 // l % 32, k = 8 * (l / 32) .. + 7).
@@ -13,18 +14,19 @@ namespace {
 using namespace nt;
 constexpr int BK = 64;  // bf16 values per K-step
 
-template <int EPI, int BM>
+template <int EPI, int BM, bool GROUPED>
 __global__ void __launch_bounds__(256, 2) k_gemm_nt16(NtArgs g, int ipw, int total_iters) {
   using G = Geo<BM>;
   extern __shared__ __align__(16) float lds[];
   __shared__ int s_last;
-  // first row tile, first row and row count of every sentence
-  __shared__ int s_tile0[kMaxB + 1], s_row0[kMaxB], s_cnt[kMaxB];
+  // grouped mode (one grammar per sentence): first row tile, first row and row count of every sentence
+  __shared__ int s_tile0[GROUPED ? kMaxB + 1 : 1], s_row0[GROUPED ? kMaxB : 1], s_cnt[GROUPED ? kMaxB : 1];
   __shared__ int s_wsum[4];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave % G::WM, wn = wave / G::WM;
-  const int tiles_m = build_group_table<BM>(g, s_tile0, s_row0, s_cnt, s_wsum, tid);
+  int tiles_m = (g.rows + BM - 1) / BM;
+  if (GROUPED) tiles_m = build_group_table<BM>(g, s_tile0, s_row0, s_cnt, s_wsum, tid);
   const int KT = g.K / BK;
   // staging of both operands: 8 chunks of 16 bytes (8 bf16) per row and K-step, 32 rows per pass
   const int lc8 = tid & 7, lr8 = tid >> 3;
@@ -45,7 +47,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_nt16(NtArgs g, int ipw, int tot
     int row0 = tile_m * BM, row_end = g.rows;
     const int col0 = tile_n * BN;
     const __bf16* Bh = static_cast<const __bf16*>(g.Bm);
-    Bh += (int64_t)find_group<BM>(g, s_tile0, s_row0, s_cnt, tile_m, &row0, &row_end) * g.grp_b_stride;
+    if (GROUPED) Bh += (int64_t)find_group<BM>(g, s_tile0, s_row0, s_cnt, tile_m, &row0, &row_end) * g.grp_b_stride;
 
     // element offsets of this thread's chunks (row clamped into range: out-of-range rows are never stored)
     int64_t oa[QA], ob[4];
@@ -135,35 +137,40 @@ __global__ void __launch_bounds__(256, 2) k_gemm_nt16(NtArgs g, int ipw, int tot
   }
 }
 
-template <int EPI, int BM>
+template <int EPI, int BM, bool GROUPED>
 void launch(const NtArgs& a, hipStream_t st) {
   using G = Geo<BM>;
   static bool attr_set = false;
   if (!attr_set) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_nt16<EPI, BM>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_nt16<EPI, BM, GROUPED>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::kLdsBytes);
     attr_set = true;
   }
-  launch_shared(k_gemm_nt16<EPI, BM>, a, BM, BK, G::kLdsBytes, st);
+  launch_shared(k_gemm_nt16<EPI, BM, GROUPED>, a, BM, BK, G::kLdsBytes, st);
 }
 
-template <int EPI>
+template <int EPI, bool GROUPED>
 void launch_bm(const NtArgs& a, hipStream_t st) {
   switch (chosen_bm(a)) {
-    case 32: launch<EPI, 32>(a, st); break;
-    case 64: launch<EPI, 64>(a, st); break;
-    default: launch<EPI, 128>(a, st); break;
+    case 32: launch<EPI, 32, GROUPED>(a, st); break;
+    case 64: launch<EPI, 64, GROUPED>(a, st); break;
+    default: launch<EPI, 128, GROUPED>(a, st); break;
   }
+}
+template <int EPI>
+void launch_mode(const NtArgs& a, hipStream_t st) {
+  if (a.grouped) launch_bm<EPI, true>(a, st);
+  else launch_bm<EPI, false>(a, st);
 }
 
 }  // namespace
 
 void launch_gemm_nt16(const NtArgs& a, hipStream_t st) {
-  if (a.rows <= 0 || a.cols <= 0 || !a.a_bf16 || !a.b_bf16 || !a.grouped) return;
+  if (a.rows <= 0 || a.cols <= 0 || !a.a_bf16 || !a.b_bf16) return;  // both operands are bf16 here
   switch (a.epilogue) {
-    case NT_EPI_ROWSCALE: launch_bm<NT_EPI_ROWSCALE>(a, st); break;
-    case NT_EPI_MASKROWS: launch_bm<NT_EPI_MASKROWS>(a, st); break;
-    default: launch_bm<NT_EPI_LEAF_EMIT>(a, st); break;
+    case NT_EPI_ROWSCALE: launch_mode<NT_EPI_ROWSCALE>(a, st); break;
+    case NT_EPI_MASKROWS: launch_mode<NT_EPI_MASKROWS>(a, st); break;
+    default: launch_mode<NT_EPI_LEAF_EMIT>(a, st); break;
   }
 }
 

@@ -233,10 +233,16 @@ __global__ void __launch_bounds__(64 * NW, 1) k_gemm_nt3(NtArgs g, int ipw, int 
       tie_registers<NPL, NF>(F);
     };
 
-    // prologue: the first NS - 1 steps in flight (steps past the end repeat the last one: the count of loads in flight
-    // stays the same in every step, and the repeated data lands in a stage that is never read)
-    static_for<0, NS - 1>([&](auto s) { load_stage(decltype(s)::value, min(k0 + decltype(s)::value, k1 - 1)); });
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ND * (NS - 2)) : "memory");
+    // prologue: the first NS - 1 steps in flight (from there on steps past the end repeat the last one: the count of loads in
+    // flight stays the same in every step, and the repeated data lands in a stage that is never read).  A share of fewer
+    // steps asks for those alone and waits for them here: every wait of the loop is then met
+    if (k1 - k0 >= NS - 1) {
+      static_for<0, NS - 1>([&](auto s) { load_stage(decltype(s)::value, k0 + decltype(s)::value); });
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(ND * (NS - 2)) : "memory");
+    } else {
+      static_for<0, NS - 1>([&](auto s) { if (k0 + decltype(s)::value < k1) load_stage(decltype(s)::value, k0 + decltype(s)::value); });
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();
     SPCFG_SB
     static_for<0, NR>([&](auto r) { read_one(X, r, a_frag, b_frag); });

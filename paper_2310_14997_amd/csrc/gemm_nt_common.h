@@ -195,15 +195,16 @@ __device__ __forceinline__ int find_group(const NtArgs& g, const int* s_tile0, c
 }
 
 // After the K loop of one tile segment [k0, k1): run the epilogue if the segment is the whole tile, else
-// publish the partial tile, count the arrival, and let the last arriver reduce in fixed order (kParts of more than two parts at a
-// time: as registers allow).
-template <int BM, int BNW = BN, int NW = 4, int kParts = 1, typename Epi>
+// publish the partial tile, count the arrival, and let the last arriver reduce in fixed order (of more than two
+// parts kWhole at a time, as registers allow, or four of the shorter tiles).
+template <int BM, int BNW = BN, int NW = 4, int kWhole = 1, typename Epi>
 __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
                                             floatx16 (&acc)[Geo<BM, BNW, NW>::MI][Geo<BM, BNW, NW>::NI],
                                             int tile, int ustart, int k0, int k1, int KT, int ipw, int wg, int it,
                                             int wg_begin, int tid, int* s_last_ptr, Epi&& run_epilogue) {
   using G = Geo<BM, BNW, NW>;
   constexpr int kThreads = 64 * NW;
+  constexpr int kParts = G::MI * G::NI >= 4 ? kWhole : 4;
   int& s_last = *s_last_ptr;
   if (k0 == 0 && k1 == KT) {
     run_epilogue(acc);
@@ -228,7 +229,7 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
                 parts - 1) ? 1 : 0;
     __syncthreads();
     if (s_last) {
-      // Parts in ascending order, kParts whole ones (up to 64 loads a lane) in flight: what the reducing workgroup waits for is
+      // Parts in ascending order, kParts of them (32 to 64 loads a lane) in flight: what the reducing workgroup waits for is
       // the number of such rounds.  Of two parts one is still in registers, and the order of two terms does not matter.
       const int odd0 = (ustart != first_g * ipw) ? 1 : 0;
       const int own = wg - first_g;
@@ -241,21 +242,21 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
 #pragma unroll
             for (int j = 0; j < 8; ++j) x[mi][ni][j] = ld_agent(src + (((mi * G::NI + ni) * 8 + j) * kThreads + tid) * 2);
       };
-      auto add = [&](float keep, const F2 (&x)[G::MI][G::NI][8]) {
+      auto add = [&](const F2 (&x)[G::MI][G::NI][8]) {
 #pragma unroll
         for (int mi = 0; mi < G::MI; ++mi)
 #pragma unroll
           for (int ni = 0; ni < G::NI; ++ni)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              acc[mi][ni][2 * j] += keep * x[mi][ni][j].a;
-              acc[mi][ni][2 * j + 1] += keep * x[mi][ni][j].b;
+              acc[mi][ni][2 * j] += x[mi][ni][j].a;
+              acc[mi][ni][2 * j + 1] += x[mi][ni][j].b;
             }
       };
       if (parts == 2) {
         F2 x[G::MI][G::NI][8];
         fetch(1 - own, x);
-        add(1.0f, x);
+        add(x);
       } else {
 #pragma unroll
         for (int mi = 0; mi < G::MI; ++mi)
@@ -266,9 +267,11 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
         for (int p0 = 0; p0 < parts; p0 += kParts) {
           F2 x[kParts][G::MI][G::NI][8];
 #pragma unroll
-          for (int u = 0; u < kParts; ++u) fetch(min(p0 + u, parts - 1), x[u]);
+          for (int u = 0; u < kParts; ++u)
+            if (p0 + u < parts) fetch(p0 + u, x[u]);
 #pragma unroll
-          for (int u = 0; u < kParts; ++u) add(p0 + u < parts ? 1.0f : 0.0f, x[u]);  // (past the end: the last part again, adds nothing)
+          for (int u = 0; u < kParts; ++u)
+            if (p0 + u < parts) add(x[u]);
         }
       }
       run_epilogue(acc);

@@ -319,6 +319,9 @@ void launch_tn3(const Tn3Args& a, hipStream_t st) {
   // each: shares of at least sqrt(KT / 2) steps balance the two when few tiles would be cut for the whole chip.
   // B = 7, N = 141, n <= 37 (6 tiles of 66 steps): whole call 638 -> 620 us; larger outputs have longer shares anyway.
   while (2 * (int64_t)ipw * ipw < a.KT) ++ipw;
+  // A short reduction on one plane is not worth the exchange (14 us against 0.95 us a step).  With three planes it would be as well,
+  // but the longer sums are less accurate (N = 141, 7 sentences: 1.2e-7 from 64 bits instead of 8.5e-8).
+  if (PLANES == 1 && a.KT - ipw <= 14) ipw = a.KT;
   Gn = (total + ipw - 1) / ipw;
   launch_k(k_gemm_tn3<PLANES>, dim3(Gn), dim3(64 * Q::NW), Q::kLds, st, a, ipw, total);
 }
