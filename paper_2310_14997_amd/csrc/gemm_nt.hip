@@ -11,7 +11,7 @@
 //    lane fetches its operands as one 16-byte LDS read covering four K values (the K order inside an 8-wide chunk
 //    is permuted identically for both operands, which leaves the sum over K unchanged).
 // Work sharing across workgroups and the epilogues are in gemm_nt_common.h.
-#include "gemm_nt_common.h"
+#include "gemm_forms.h"
 
 namespace spcfg {
 
@@ -323,12 +323,24 @@ void launch_bm(const NtArgs& a, hipStream_t st) {
 int gemm_nt_tiles(int rows, int cols) { return ((rows + 31) / 32) * ((cols + nt::BN - 1) / nt::BN); }
 size_t gemm_nt_partial_bytes(int max_wgs) { return (size_t)2 * max_wgs * nt::Geo<128>::kSlotFloats * sizeof(float); }
 
+// On one or two planes: chooses the form of the launch and gives its parts up where that has none.
+static void choose_form(NtArgs& a) {
+  if (a.form != 0) return;
+  const nt::Form f = nt::pick_form(a);
+  a.form = 1 + 2 * f.shape + (f.whole ? 1 : 0);
+  if (!f.parts) nt::drop_parts(a);
+}
+
 // Parts that cover all columns over different K ranges of the same rows (the reverse product: the adjoint half
 // they leave out is zero) can also run as one plain product.  Each part rounds its rows up to whole tiles, so with
 // few prefix / suffix rows per width and tall tiles the plain product has fewer (tile, K-step) units: then the parts
 // are dropped.  Returns whether the launch keeps its parts.
 bool gemm_nt_keep_parts(NtArgs& a) {
   if (a.parts == 0) return false;
+  if (a.planes3 == 1 || a.planes3 == 2) {
+    choose_form(a);
+    return a.parts > 0;
+  }
   const int bm = nt::chosen_bm(a);
   int units_parts = 0;
   for (int p = 0; p < a.parts; ++p) {
@@ -345,19 +357,14 @@ bool gemm_nt_reads_planes(const NtArgs& a) {
   return a.planes3 <= 2 || nt::chosen_bm(a) == 128;
 }
 
-namespace { constexpr int kShortK16 = 1024; }
-
 void launch_gemm_nt(const NtArgs& a, hipStream_t st) {
   if (a.rows <= 0 || a.cols <= 0) return;
   if (a.step) { launch_step(*a.step, st); return; }
   if (a.b_bf16) { launch_gemm_nt16(a, st); return; }
-  // One bf16 plane: launches of few rows with a short K take the kernel that stages tiles through registers, whose two workgroups a
-  // CU and finer shares suit them (scoring with single operands N = 64, n = 20 262 us on the planes kernel, 242 us so; N = 512, B = 4
-  // 432, 404); from K = 2000 on the planes kernel is faster at every row count (N = 2000, B = 2: 770, 842).
-  if (a.planes3 == 1 && a.K <= kShortK16 && nt::chosen_bm(a) < 128) {
-    NtArgs b = a;  // as one product: without the parts, which only the planes kernel knows
-    if (a.parts == 2) b.cols = a.prt_c0[1] + a.cols;
-    b.parts = 0;
+  if (a.planes3 == 1 || a.planes3 == 2) {
+    NtArgs b = a;
+    choose_form(b);
+    if (b.form != 1 + 2 * nt::kStaged) { launch_gemm_nt3(b, st); return; }
     b.b_bf16 = 1;
     launch_gemm_nt16(b, st);
     return;

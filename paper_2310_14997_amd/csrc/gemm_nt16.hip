@@ -1,5 +1,5 @@
 // bf16-operand MFMA GEMM (fp32 accumulate) for the projections in SPCFG_PRECISION_BF16, with one grammar per sentence and for
-// launches too small for the planes kernel (see launch_gemm_nt):
+// launches that run faster in it than on planes (see gemm_forms.h):
 //   C[r][c] = sum_k A[r][k] * Bm[c][k],  Bm = packed bf16 [L;R] panel, A = the bf16 copy of the chart rows that
 // their producers write next to the fp32 ones.
 // Same tiling, work sharing and epilogues as the fp32 kernel; one K-step is 64 values, and every
@@ -149,18 +149,14 @@ void launch(const NtArgs& a, hipStream_t st) {
   launch_shared(k_gemm_nt16<EPI, BM, GROUPED>, a, BM, BK, G::kLdsBytes, st);
 }
 
-template <int EPI, bool GROUPED>
-void launch_bm(const NtArgs& a, hipStream_t st) {
-  switch (chosen_bm(a)) {
-    case 32: launch<EPI, 32, GROUPED>(a, st); break;
-    case 64: launch<EPI, 64, GROUPED>(a, st); break;
-    default: launch<EPI, 128, GROUPED>(a, st); break;
-  }
-}
 template <int EPI>
 void launch_mode(const NtArgs& a, hipStream_t st) {
-  if (a.grouped) launch_bm<EPI, true>(a, st);
-  else launch_bm<EPI, false>(a, st);
+  if (!a.grouped) { launch<EPI, 32, false>(a, st); return; }  // (see pick_form in gemm_forms.h)
+  switch (chosen_bm(a)) {
+    case 32: launch<EPI, 32, true>(a, st); break;
+    case 64: launch<EPI, 64, true>(a, st); break;
+    default: launch<EPI, 128, true>(a, st); break;
+  }
 }
 
 }  // namespace

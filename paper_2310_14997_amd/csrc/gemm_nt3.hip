@@ -22,15 +22,13 @@
 #include <type_traits>
 #include <utility>
 
-#include "gemm_nt_common.h"
+#include "gemm_forms.h"
 
 namespace spcfg {
 
 namespace {
 
 using namespace nt;
-
-constexpr int BK3 = 32;  // K values per step: one 64-byte row per plane
 
 template <int BM, int NPL_, int BNW, int NW> struct Geo3 {
   using G = Geo<BM, BNW, NW>;
@@ -305,27 +303,6 @@ __global__ void __launch_bounds__(64 * NW, 1) k_gemm_nt3(NtArgs g, int ipw, int 
   }
 }
 
-// Output tiles and (tile, K-step) units of a launch with this tile shape; *kt: the steps of a tile, 0 where parts differ in them.
-struct Units { int tiles, total, kt; };
-inline Units units_of(const NtArgs& a, int bm, int bn, int ks) {
-  const int tiles_n = (a.cols + bn - 1) / bn;
-  Units u{0, 0, a.K / (BK3 * ks)};
-  if (a.parts == 0) {
-    u.tiles = ((a.rows + bm - 1) / bm) * tiles_n;
-    u.total = u.tiles * u.kt;
-    return u;
-  }
-  u.kt = -1;
-  for (int p = 0; p < a.parts; ++p) {
-    const int tp = ((a.prt_rows[p] + bm - 1) / bm) * tiles_n, kt = a.prt_kt[p] / ks;
-    u.tiles += tp;
-    u.total += tp * kt;
-    if (tp > 0) u.kt = u.kt < 0 || u.kt == kt ? kt : 0;
-  }
-  if (u.kt < 0) u.kt = 0;
-  return u;
-}
-
 // whole: a workgroup per output tile; otherwise equal shares of the (tile, K-step) space, at most one workgroup per CU
 template <int EPI, int BM, int MODE, int NPL, int BNW = BN, int NW = 4>
 void launch3(const NtArgs& a, bool whole, hipStream_t st) {
@@ -370,63 +347,33 @@ void launch_mode3(const NtArgs& a, bool whole, hipStream_t st) {
   else launch3<EPI, BM, 0, NPL, BNW, NW>(a, whole, st);
 }
 
-// Tile shape of the launches on one or two planes, and whether a workgroup keeps its tile: the least estimated time.  Per K-step a
-// workgroup takes b + c * (share of the chip that is busy) us: operands come from L2 and past it, so a full chip is slower
-// per workgroup.  Tiles cut between workgroups cost an exchange on top (`cut`), whole tiles their last, partly filled round.
-// From sweeps at N = 4096, n = 40, 32 sentences (64 to 1250 rows, both directions), within about 10 %.  Projection products
-// of a scoring pass on one plane: 2.99 ms with 128 x 128 tiles of register-staged operands and shares only, 2.2 ms so;
-// two planes 5.5 -> 5.0 ms; reverse 3.06 -> 2.3 ms.
-struct Shape3 { int bm, bn; double cut; double b[2], c[2]; };  // (one plane, 64 values a step; two planes, 32)
-constexpr Shape3 kShapes3[] = {
-    {128, 256, 14.0, {0.54, 0.62}, {0.41, 0.70}},
-    {128, 128, 11.0, {0.28, 0.35}, {0.27, 0.44}},
-    {64, 128, 8.0, {0.26, 0.33}, {0.06, 0.08}},
-};
-inline int pick_shape3(const NtArgs& a, int planes, bool* whole) {
-  int best = 0;
-  double t_best = 1e30;
-  for (int i = 0; i < 3; ++i) {
-    const Shape3& s = kShapes3[i];
-    const Units u = units_of(a, s.bm, s.bn, planes == 1 ? 2 : 1);
-    const double b = s.b[planes - 1], c = s.c[planes - 1];
-    const double full = s.bm == 64 && u.tiles > 256 ? 1.5 * (b + c) : b + c;  // (short tiles: the panel is read over and over)
-    const double shared = s.cut + (u.total + 255) / 256 * full;
-    if (shared < t_best) { t_best = shared; best = i; *whole = false; }
-    if (u.kt == 0) continue;
-    const int rest = u.tiles % 256;
-    const double kept = u.kt * (u.tiles / 256 * full + (rest ? b + c * rest / 256.0 : 0.0) * (full / (b + c)));
-    if (kept < t_best) { t_best = kept; best = i; *whole = true; }
-  }
-  return best;
-}
-
 template <int EPI, int NPL>
-void launch_bm3(const NtArgs& a, hipStream_t st) {
-  if (chosen_bm(a) == 32) { launch_mode3<EPI, 32, NPL, 128, 4>(a, false, st); return; }
-  bool whole = false;
-  switch (pick_shape3(a, NPL, &whole)) {
-    case 0: launch_mode3<EPI, 128, NPL, 256, 8>(a, whole, st); break;
-    case 1: launch_mode3<EPI, 128, NPL, 128, 8>(a, whole, st); break;
-    default: launch_mode3<EPI, 64, NPL, 128, 4>(a, whole, st); break;
+void launch_form(const NtArgs& a, const Form& f, hipStream_t st) {
+  switch (f.shape) {
+    case 0: launch_mode3<EPI, 128, NPL, 256, 8>(a, f.whole, st); break;
+    case 1: launch_mode3<EPI, 128, NPL, 128, 8>(a, f.whole, st); break;
+    case 2: launch_mode3<EPI, 64, NPL, 128, 4>(a, f.whole, st); break;
+    default: launch_mode3<EPI, 32, NPL, 128, 4>(a, false, st); break;
   }
 }
 
 }  // namespace
 
-// planes3 == 3: the launches with 128-row tiles of the fp32 mode (gemm_nt_reads_planes); planes3 == 2: every forward
-// product of the bf16 mode.
+// planes3 == 3: the launches with 128-row tiles of the fp32 mode (gemm_nt_reads_planes); planes3 == 2: the forward products of the
+// bf16 mode; planes3 == 1: its reverse products, and its forward ones on single operands, that do not take gemm_nt16.hip.
 void launch_gemm_nt3(const NtArgs& a, hipStream_t st) {
   if (a.rows <= 0 || a.cols <= 0 || !a.planes3 || a.grouped) return;
+  const Form f{(a.form - 1) / 2, (a.form - 1) % 2 != 0, a.parts > 0};  // (planes3 <= 2: chosen in launch_gemm_nt)
   if (a.planes3 == 2) {
     if (a.epilogue != NT_EPI_ROWSCALE) { launch_refused("two-plane projection product: forward epilogue only"); return; }
-    launch_bm3<NT_EPI_ROWSCALE, 2>(a, st);
+    launch_form<NT_EPI_ROWSCALE, 2>(a, f, st);
     return;
   }
   if (a.planes3 == 1) {
     switch (a.epilogue) {
-      case NT_EPI_ROWSCALE: launch_bm3<NT_EPI_ROWSCALE, 1>(a, st); break;
-      case NT_EPI_MASKROWS: launch_bm3<NT_EPI_MASKROWS, 1>(a, st); break;
-      default: launch_bm3<NT_EPI_LEAF_EMIT, 1>(a, st); break;
+      case NT_EPI_ROWSCALE: launch_form<NT_EPI_ROWSCALE, 1>(a, f, st); break;
+      case NT_EPI_MASKROWS: launch_form<NT_EPI_MASKROWS, 1>(a, f, st); break;
+      default: launch_form<NT_EPI_LEAF_EMIT, 1>(a, f, st); break;
     }
     return;
   }

@@ -418,11 +418,11 @@ NtArgs forward_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
   if (use_parts(ly, w) && Np % 128 == 0) {
     const WidthBlocks k = width_blocks(plan, ly, w);
     const int kt = (int)(Np / 32);
-    // the profile counts the executed flop: one of the two projections is left out for k.nP + k.nS rows
-    *skipped = 2.0 * ly.N * (double)ly.N * (k.nP + k.nS);
     a.parts = 2; a.cols = (int)Np;
     set_part(a, 0, 0, k.nP + k.nM, 0, 0, kt);
     set_part(a, 1, k.nP, k.nM + k.nS, (int)Np, 0, kt);
+    // the profile counts the executed flop: one of the two projections is left out for k.nP + k.nS rows
+    if (gemm_nt_keep_parts(a)) *skipped = 2.0 * ly.N * (double)ly.N * (k.nP + k.nS);
   }
   set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
   return a;
@@ -440,9 +440,11 @@ NtArgs reverse_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
     a.A3 = static_cast<const uint16_t*>(p.UVb) + row0 * 2 * Np; a.Bm3 = w >= 2 ? p.Wtn3 : p.Wtp3;
     a.planes3 = 3; a.a_plane = ly.uvb_plane; a.b_plane = 2 * Np * (w >= 2 ? Np : Pp);
   }
+  a.Bm = w >= 2 ? p.Wtn : p.Wtp;
+  if (ly.bf16 && ly.G == 1) { a.A3 = a.A; a.Bm3 = a.Bm; a.planes3 = 1; a.b_bf16 = 0; }
   if (w >= 2) {
     *flop = 4.0 * ly.N * (double)ly.N * rows;
-    a.Bm = p.Wtn; a.ldb = 2 * Np; a.C = p.BH + (row0 - ly.S1) * Np; a.ldc = Np; a.cols = (int)Np;
+    a.ldb = 2 * Np; a.C = p.BH + (row0 - ly.S1) * Np; a.ldc = Np; a.cols = (int)Np;
     a.epilogue = NT_EPI_MASKROWS; a.rowmask = p.rootmask + row0; a.rowmaxb = p.umaxb + row0;
     if (use_parts(ly, w)) {  // prefix rows: only the eta adjoint (first half of K); suffix rows: only zeta's
       const WidthBlocks k = width_blocks(plan, ly, w);
@@ -457,12 +459,11 @@ NtArgs reverse_product(const Plan& plan, const Layout& ly, const Ptrs& p, int fp
     set_groups(a, plan, ly, p, w, row0, 2 * Np * Np);
   } else {
     *flop = 4.0 * ly.N * (double)ly.P * rows;
-    a.Bm = p.Wtp; a.ldb = 2 * Np; a.C = grad_log_emit; a.ldc = ly.P; a.cols = ly.P;
+    a.ldb = 2 * Np; a.C = grad_log_emit; a.ldc = ly.P; a.cols = ly.P;
     a.epilogue = NT_EPI_LEAF_EMIT; a.E = p.leafE; a.lde = Pp; a.rowexp = p.uexp;
     a.row_b = p.row_b; a.row_i = p.row_i; a.n_max = ly.n_max;
     set_groups(a, plan, ly, p, 1, 0, 2 * Np * Pp);
   }
-  if (ly.bf16 && ly.G == 1) { a.A3 = a.A; a.Bm3 = a.Bm; a.planes3 = 1; a.b_bf16 = 0; }
   return a;
 }
 
@@ -486,13 +487,13 @@ Ptrs panels_read(const Plan& plan, const Layout& ly, const Ptrs& p, int fp32_mfm
       NtArgs a = forward_product(plan, ly, p, fp32_mfma, w, &flop);
       use(a, p.Wn, p.Wn3, &q.Wn, &q.Wn3);
       a.parts = 0; a.cols = (int)(2 * ly.Np);  // as one product: at least the work of every wider launch
-      f = !(q.Wn && q.Wn3) && (q.Wn3 || (a.planes3 && gemm_nt_reads_planes(a)));
+      f = !(q.Wn && q.Wn3) && a.planes3 == 3 && (q.Wn3 || gemm_nt_reads_planes(a));  // (one or two planes: all read the same)
     }
     if (r) {
       NtArgs a = reverse_product(plan, ly, p, fp32_mfma, w, nullptr, &flop);
       use(a, p.Wtn, p.Wtn3, &q.Wtn, &q.Wtn3);
       a.parts = 0;
-      r = !(q.Wtn && q.Wtn3) && (q.Wtn3 || (a.planes3 && gemm_nt_reads_planes(a)));
+      r = !(q.Wtn && q.Wtn3) && a.planes3 == 3 && (q.Wtn3 || gemm_nt_reads_planes(a));
     }
   }
   if (!fwd) q.colmax = nullptr;

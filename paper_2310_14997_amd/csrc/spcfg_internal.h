@@ -223,6 +223,7 @@ struct NtArgs {
   int planes3; int64_t a_plane, b_plane;
   const void* A3; const void* Bm3;
   const StepArgs* step;  // host only; if set, the launch also takes the sums that wait for this product
+  int form;  // host only; planes3 <= 2: the form of least estimated time (gemm_forms.h), 1 + 2 * shape + whole; 0: not chosen yet
   int parts;
   int prt_row0[3], prt_rows[3], prt_c0[3], prt_kbeg[3], prt_kt[3];
 };
