@@ -108,5 +108,30 @@ inline Form pick_form(const NtArgs& a) {
   return best;
 }
 
+// Steps of a workgroup's share of a rule-gradient product (gemm_tn3.hip) of `tiles` output tiles and KT steps each; KT: whole tiles.
+// A tile costs its share's steps in a row, then the last workgroup adds up KT / share partial tiles at about half a step's time
+// each: shares of at least sqrt(KT / 2) steps balance the two when few tiles would be cut for the whole chip.
+// B = 7, N = 141, n <= 37 (6 tiles of 66 steps): whole call 638 -> 620 us; larger outputs have longer shares anyway.
+// On one plane a short reduction is not worth the exchange, and more than one round of whole tiles pays its last, partly filled round
+// in full; estimated in us from 90 launches timed both ways (N = 192 .. 4096, 6 to 390 steps), with 64-row steps of b + c * (share
+// of the chip that is busy): 1.007 times the faster way's time on average.  16 tiles of 6 steps 11.3 us whole, 19.0 in shares; 144 of
+// 20 22.9, 33.0; 297 tiles (N = 2112) of 390 668, 452; 324 of 150 235, 194.  With whole tiles wherever a share comes within 14
+// steps of a tile or past it, 1.061.  With three planes whole tiles would be faster for short reductions as well, but the longer sums
+// are less accurate (N = 141, 7 sentences: 1.2e-7 from 64 bits instead of 8.5e-8).
+constexpr double kTnB = 0.57, kTnC = 0.37, kTnRound = 2.0, kTnCut = 8.0, kTnPart = 2.0;
+inline int tn3_share(int planes, int tiles, int KT, int max_wgs) {
+  const int total = tiles * KT;
+  // (one workgroup per CU; the partial-tile scratch holds 2 * max_wgs slots of 128 x 128, a tile on one plane is two of them)
+  const int wgs = least(least(256, planes == 1 ? max_wgs / 2 : max_wgs), total > 3 ? total / 2 : 1);
+  int share = (total + wgs - 1) / wgs;
+  while (2 * (int64_t)share * share < KT) ++share;
+  if (planes != 1) return share;
+  const int busy = least(256, (total + share - 1) / share), rest = tiles % 256;
+  const double whole = kTnRound * ((tiles + 255) / 256) + KT * (tiles / 256 * (kTnB + kTnC) + (rest ? kTnB + kTnC * rest / 256.0 : 0.0));
+  const double cut = kTnCut + kTnPart * (share < KT ? (KT + share - 1) / share : 2) +
+                     share * (kTnB + kTnC * busy / 256.0) + kTnRound * ((share + KT - 1) / KT);
+  return whole < cut ? KT : share;
+}
+
 }  // namespace nt
 }  // namespace spcfg

@@ -15,7 +15,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "gemm_nt_common.h"
+#include "gemm_forms.h"
 
 namespace spcfg {
 
@@ -311,18 +311,8 @@ void launch_tn3(const Tn3Args& a, hipStream_t st) {
   const int64_t total64 = (int64_t)tiles * a.KT;
   if (total64 >= ((int64_t)1 << 31)) { launch_refused("rule-gradient product: too many (tile, step) units"); return; }
   const int total = (int)total64;
-  int Gn = 256;  // one workgroup per CU
-  if (Gn > a.max_wgs / Q::BH) Gn = a.max_wgs / Q::BH;  // the partial-tile scratch holds 2 * max_wgs slots of 128 x 128
-  if (Gn > total / 2) Gn = total / 2 > 0 ? total / 2 : 1;
-  int ipw = (total + Gn - 1) / Gn;
-  // A tile costs its share's steps in a row, then the last workgroup adds up KT / ipw partial tiles at about half a step's time
-  // each: shares of at least sqrt(KT / 2) steps balance the two when few tiles would be cut for the whole chip.
-  // B = 7, N = 141, n <= 37 (6 tiles of 66 steps): whole call 638 -> 620 us; larger outputs have longer shares anyway.
-  while (2 * (int64_t)ipw * ipw < a.KT) ++ipw;
-  // A short reduction on one plane is not worth the exchange (14 us against 0.95 us a step).  With three planes it would be as well,
-  // but the longer sums are less accurate (N = 141, 7 sentences: 1.2e-7 from 64 bits instead of 8.5e-8).
-  if (PLANES == 1 && a.KT - ipw <= 14) ipw = a.KT;
-  Gn = (total + ipw - 1) / ipw;
+  const int ipw = nt::tn3_share(PLANES, tiles, a.KT, a.max_wgs);
+  const int Gn = (total + ipw - 1) / ipw;
   launch_k(k_gemm_tn3<PLANES>, dim3(Gn), dim3(64 * Q::NW), Q::kLds, st, a, ipw, total);
 }
 }  // namespace

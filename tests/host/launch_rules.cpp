@@ -32,7 +32,9 @@ int main() {
       printf("%d %d %d %d\n", staged ? 0 : spcfg::nt::kShapes3[f.shape].bm, staged ? 0 : spcfg::nt::kShapes3[f.shape].bn, f.whole,
              f.parts);
     } else {
-      return 1;
+      int tiles, steps;
+      if (strcmp(what, "tn") != 0 || scanf("%d %d", &tiles, &steps) != 2) return 1;
+      printf("%d\n", spcfg::nt::tn3_share(1, tiles, steps, spcfg::kGemmWgs));
     }
   }
   return 0;

@@ -1,5 +1,5 @@
 """The products of the bf16 mode in the forms that csrc/gemm_forms.h can give them: tiles staged through registers and on planes, whole and
-in shares, reverse products in parts and as one.
+in shares, reverse products in parts and as one, rule gradients of more than 256 output tiles with a last round that is partly filled.
 Every block of 64 rows and of 64 columns is held against the fp32 mode of the same library, which the oracle checks elsewhere: operands
 rounded to 2^-9 give gradients within 1e-2 (relative 2-norm), every block too, so that a wrong tile shows wherever it lies;
 log Z within 2e-3 with single operands and 1e-4 with two pieces."""
@@ -27,6 +27,9 @@ def blocks_off(got, ref):
     (576, 100, [8] * 240),        # one product and parts, both whole: no whole number of 128-column blocks
     (1088, 130, [6, 5, 7] * 12),  # whole tiles next to staged ones
     (1300, 70, [7] * 100),        # tiles of 32 rows in shares next to whole ones of 64
+    (2112, 2112, [20] * 14),      # rule gradients in 297 tiles, equal shares that go on from tile to tile
+    (2112, 2112, [3] * 8),        # the same, a reduction of one step: whole tiles
+    (2200, 300, [9] * 24),        # 315 tiles, and 70 for the preterminals, whose last ones have 44 columns
 ])
 def test_every_block(N, P, lens):
     d = synth.make_inputs("tiny", seed=6200 + N, pad_value=np.nan, N=N, P=P, B=len(lens), lengths=lens, V=60)

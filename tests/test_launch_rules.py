@@ -114,3 +114,22 @@ def test_projection_forms(ask):
         if not times.get(name, 1e9) <= 1.15 * min(times.values()):
             slow.append((case, name, times))
     assert not slow, slow
+
+
+# (output tiles, steps, us in equal shares, us in whole tiles) of rule-gradient products on one plane
+RULE_GRADIENTS = [
+    (3, 6, 19.4, 11.1), (3, 60, 34.8, 42.4), (16, 390, 75.2, 236.5), (64, 20, 28.4, 21.2), (64, 60, 36.3, 44.3),
+    (144, 20, 33.0, 22.9), (144, 390, 224.6, 264.6), (196, 60, 64.0, 54.4), (196, 390, 296.5, 344.2), (240, 150, 149.8, 135.9),
+    (256, 150, 141.9, 141.9), (297, 60, 84.8, 102.4), (297, 150, 176.7, 235.5), (297, 390, 451.9, 668.4),
+    (306, 390, 473.9, 679.3), (324, 150, 194.1, 235.2), (324, 390, 497.8, 674.8), (400, 20, 51.8, 47.2), (400, 390, 625.6, 716.9),
+    (540, 150, 312.4, 373.7), (540, 390, 823.6, 1037.4), (576, 60, 147.2, 164.4), (784, 150, 446.4, 510.4), (1024, 6, 54.7, 52.5),
+]
+
+
+def test_rule_gradient_shares(ask):
+    shares = ask("tn %d %d" % (tiles, steps) for tiles, steps, _, _ in RULE_GRADIENTS)
+    for (tiles, steps, cut, whole), (share,) in zip(RULE_GRADIENTS, shares):
+        got = whole if share == steps else cut
+        assert got <= 1.1 * min(cut, whole), (tiles, steps, share, cut, whole)
+        if share != steps:  # at most a workgroup per CU, none without work
+            assert -(-tiles * steps // share) <= 256 and share >= 2
