@@ -231,10 +231,10 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
     if (s_last) {
       // Parts in ascending order, kParts of them (32 to 64 loads a lane) in flight: what the reducing workgroup waits for is
       // the number of such rounds.  Of two parts one is still in registers, and the order of two terms does not matter.
-      // Full rounds have no branches, since a short launch's tiles have up to 16 parts or more (N = 512, fp32 matrix instructions, one
-      // sentence of 30 words: a training step 1008 us with a branch around every part's loads, 980 so; N = 1024 on two planes, 60
-      // words scored: 1210, 1180); the last round asks only for the parts that there are (three parts of N = 320: scoring 612 us with
-      // repeated loads in their place, 583 so).
+      // Tiles of 32 rows, of which a short launch cuts up to 32 parts, have full rounds without branches (N = 512, fp32 matrix instructions,
+      // one sentence of 30 words: a training step 1008 us with a branch around every part's loads, 980 so; N = 1024 on two planes, 60
+      // words scored: 1210, 1180), and a last round that asks only for the parts that there are (three parts at N = 320: scoring
+      // 612 us with repeated loads in their place, 583 so).  Taller ones have few parts and lose by it (N = 3000, 8 sentences: 940, 953).
       const int odd0 = (ustart != first_g * ipw) ? 1 : 0;
       const int own = wg - first_g;
       auto fetch = [&](int p, F2 (&x)[G::MI][G::NI][8]) {
@@ -269,21 +269,33 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
         int p0 = 0;
-        for (; p0 + kParts <= parts; p0 += kParts) {
-          F2 x[kParts][G::MI][G::NI][8];
+        if constexpr (G::MI * G::NI == 1) {
+          for (; p0 + kParts <= parts; p0 += kParts) {
+            F2 x[kParts][G::MI][G::NI][8];
 #pragma unroll
-          for (int u = 0; u < kParts; ++u) fetch(p0 + u, x[u]);
+            for (int u = 0; u < kParts; ++u) fetch(p0 + u, x[u]);
 #pragma unroll
-          for (int u = 0; u < kParts; ++u) add(x[u]);
-        }
-        if (kParts > 1 && p0 < parts) {
-          F2 x[kParts][G::MI][G::NI][8];
+            for (int u = 0; u < kParts; ++u) add(x[u]);
+          }
+          if (p0 < parts) {
+            F2 x[kParts - 1][G::MI][G::NI][8];
 #pragma unroll
-          for (int u = 0; u + 1 < kParts; ++u)
-            if (p0 + u < parts) fetch(p0 + u, x[u]);
+            for (int u = 0; u + 1 < kParts; ++u)
+              if (p0 + u < parts) fetch(p0 + u, x[u]);
 #pragma unroll
-          for (int u = 0; u + 1 < kParts; ++u)
-            if (p0 + u < parts) add(x[u]);
+            for (int u = 0; u + 1 < kParts; ++u)
+              if (p0 + u < parts) add(x[u]);
+          }
+        } else {
+          for (; p0 < parts; p0 += kParts) {
+            F2 x[kParts][G::MI][G::NI][8];
+#pragma unroll
+            for (int u = 0; u < kParts; ++u)
+              if (p0 + u < parts) fetch(p0 + u, x[u]);
+#pragma unroll
+            for (int u = 0; u < kParts; ++u)
+              if (p0 + u < parts) add(x[u]);
+          }
         }
       }
       run_epilogue(acc);
