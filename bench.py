@@ -195,20 +195,23 @@ def measure(d, bf16, fp32_mfma, steps, warmup, profile_steps, graph=False, extra
         wl.forward_backward()
     torch.cuda.synchronize()
     prof = bd.spcfg_profile_read()
+    shared = bd.spcfg_profile_read_shared()
     bd.spcfg_profile_enable(False)
     classes = {k: dict(ms_per_step=v["ms"] / psteps, launches_per_step=v["launches"] / psteps,
                        work_per_step=v["work"] / psteps) for k, v in prof.items()}
-    proj_ms = classes["gemm_fwd"]["ms_per_step"] + classes["gemm_bwd"]["ms_per_step"]
-    proj_flop = classes["gemm_fwd"]["work_per_step"] + classes["gemm_bwd"]["work_per_step"]
-    proj_launches = classes["gemm_fwd"]["launches_per_step"] + classes["gemm_bwd"]["launches_per_step"]
-    achieved = proj_flop / (proj_ms * 1e-3) / 1e12
-    split_ms = classes["split_fwd"]["ms_per_step"] + classes["split_bwd"]["ms_per_step"]
-    split_bytes = classes["split_fwd"]["work_per_step"] + classes["split_bwd"]["work_per_step"]
+    # Rates are taken over the launches that do one class's work alone (a small grammar's launch that takes a product and
+    # the sums behind it is charged half to each class, which is no measurement)
+    alone = lambda key, *names: sum(prof[k][key] - shared[k][key] for k in names) / psteps
+    rate = lambda work, ms: work / (ms * 1e-3) if ms > 0 else None
+    frac = lambda x, peak: None if x is None else x / peak
+    proj_ms, proj_flop, proj_launches = (alone(key, "gemm_fwd", "gemm_bwd") for key in ("ms", "work", "launches"))
+    split_ms, split_bytes = (alone(key, "split_fwd", "split_bwd") for key in ("ms", "work"))
+    achieved, split_rate = rate(proj_flop / 1e12, proj_ms), rate(split_bytes / 1e9, split_ms)
     gg = classes["gemm_grad"]
     gg_tflops = gg["work_per_step"] / (gg["ms_per_step"] * 1e-3) / 1e12
     res["classes"] = classes
     res["roofline"] = {"bound": "mfma", "kernel": kernel_name + "; stacked projection, forward + reverse)", "mfma": mfma,
-                       "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
+                       "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": frac(achieved, peak),
                        "launches_per_step": proj_launches, "avg_launch_us": proj_ms * 1e3 / max(proj_launches, 1),
                        "flop_per_launch": proj_flop / max(proj_launches, 1)}
     res["gemm_grad"] = {"bound": "mfma", "kernel": "rule-gradient product (fp32 mode: k_gemm_tn3 on pre-cut bf16 planes incl. the kernel that scales and cuts the inside vectors; fp32 matrix instructions or per-sentence grammars: k_gemm_tn; bf16 mode: k_gemm_tn3 on one bf16 plane)",
@@ -216,9 +219,12 @@ def measure(d, bf16, fp32_mfma, steps, warmup, profile_steps, graph=False, extra
                         "ms_per_step": gg["ms_per_step"]}
     # chart rows that the launches read and write; rows that several workgroups read count for each, so part of them is
     # served by the caches
-    res["split_reduction"] = {"bound": "hbm", "achieved": split_bytes / (split_ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBS,
-                              "unit": "GB/s", "frac": split_bytes / (split_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
-                              "ms_per_step": split_ms}
+    res["split_reduction"] = {"bound": "hbm", "achieved": split_rate, "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                              "frac": frac(split_rate, PEAK_HBM_GBS), "ms_per_step": split_ms}
+    in_shared = sum(v["launches"] for v in shared.values())  # (each counts in its two classes)
+    if in_shared:
+        res["roofline"]["shared_launches"] = {"per_step": in_shared / 2 / psteps,
+                                              "ms_per_step": sum(v["ms"] for v in shared.values()) / psteps}
     return res
 
 

@@ -163,9 +163,13 @@ const char* spcfg_last_hip_error(void);
  * Per-kernel-class timing.  While enabled, every kernel launch carries a pair of HIP events bound to the start
  * and the end of that kernel on the caller's stream; a class's time is the sum of its kernels' durations
  * (this perturbs the schedule slightly, so whole-step timing should be taken with profiling disabled).
+ * Small grammars take a projection product and the split sums that wait for it in one launch: such a shared launch
+ * counts in both classes and is charged to each with half its time, a convention and not a measurement.  The sum of
+ * ms[] over the classes is the device time all the same; spcfg_profile_read_shared gives what shared launches
+ * contributed, so that rates can be taken over the others.
  * spcfg_profile_read synchronises the recorded events, then fills, for class c in [0, SPCFG_PROF_CLASSES):
- *   ms[c]      total device time of the class since spcfg_profile_enable(1)
- *   launches[c] number of kernel launches
+ *   ms[c]      total device time of the class since spcfg_profile_enable(1) (half of it for shared launches)
+ *   launches[c] number of kernel launches (shared launches in both of their classes)
  *   work[c]    work enqueued: flop for the GEMM classes, bytes for the others (split classes: chart rows that the
  *              launches read and write; a row that several workgroups read counts for each, whatever cache it comes from)
  * and resets the counters.  Arrays must hold SPCFG_PROF_CLASSES entries.  The counters are the library's only state:
@@ -183,6 +187,8 @@ enum {
 };
 int spcfg_profile_enable(int on);
 int spcfg_profile_read(double* ms, int64_t* launches, double* work);
+/* The part of the last spcfg_profile_read's figures that comes from shared launches (zeros where there were none). */
+int spcfg_profile_read_shared(double* ms, int64_t* launches, double* work);
 const char* spcfg_profile_class_name(int cls);
 
 /*

@@ -62,10 +62,12 @@ def load():
     lib.spcfg_last_hip_error.restype = C.c_char_p
     lib.spcfg_profile_enable.argtypes = [C.c_int]
     lib.spcfg_profile_read.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double)]
+    lib.spcfg_profile_read_shared.argtypes = [C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double)]
     lib.spcfg_profile_class_name.argtypes = [C.c_int]
     lib.spcfg_profile_class_name.restype = C.c_char_p
     for name in ("spcfg_workspace_bytes", "spcfg_workspace_bytes_for", "spcfg_inside", "spcfg_inside_backward",
-                 "spcfg_inside_forward_backward", "spcfg_inside_static", "spcfg_profile_enable", "spcfg_profile_read"):
+                 "spcfg_inside_forward_backward", "spcfg_inside_static", "spcfg_profile_enable", "spcfg_profile_read",
+                 "spcfg_profile_read_shared"):
         getattr(lib, name).restype = C.c_int
     _lib = lib
     return lib
@@ -256,15 +258,24 @@ def spcfg_profile_enable(on):
     _check(load().spcfg_profile_enable(1 if on else 0))
 
 
-def spcfg_profile_read():
-    """Returns {class name: dict(ms, launches, work)} since profiling was enabled, and resets the counters."""
+def _profile(read):
     lib = load()
     ms = (C.c_double * PROF_CLASSES)()
     ln = (C.c_int64 * PROF_CLASSES)()
     wk = (C.c_double * PROF_CLASSES)()
-    _check(lib.spcfg_profile_read(ms, ln, wk))
+    _check(read(ms, ln, wk))
     return {lib.spcfg_profile_class_name(c).decode(): dict(ms=ms[c], launches=ln[c], work=wk[c])
             for c in range(PROF_CLASSES)}
+
+
+def spcfg_profile_read():
+    """Returns {class name: dict(ms, launches, work)} since profiling was enabled, and resets the counters."""
+    return _profile(load().spcfg_profile_read)
+
+
+def spcfg_profile_read_shared():
+    """The part of the last spcfg_profile_read that comes from launches of two classes at once."""
+    return _profile(load().spcfg_profile_read_shared)
 
 
 class Workload:

@@ -267,7 +267,7 @@ int make_plan(const spcfg_config* cfg, const int32_t* lengths, int B, int n_max,
 // The counters are process-wide; a mutex guards them, and the class that a thread's launches are charged to is that
 // thread's own, so concurrent callers do not corrupt the records (their launches simply add up).
 // A launch of two classes at once (a product together with the sums that wait for it) counts in both and is charged to
-// each with half its time.
+// each with half its time; what comes from such launches is kept apart as well (spcfg_profile_read_shared).
 thread_local int t_cur_cls = -1, t_cur_also = -1;
 struct Prof {
   std::atomic<bool> on{false};
@@ -275,8 +275,12 @@ struct Prof {
   struct Rec { hipEvent_t a, b; int cls, also; };
   std::vector<Rec> recs;
   std::vector<hipEvent_t> pool;
-  double work[SPCFG_PROF_CLASSES] = {0};
-  int64_t launches[SPCFG_PROF_CLASSES] = {0};
+  struct Sums {
+    double ms[SPCFG_PROF_CLASSES] = {0}, work[SPCFG_PROF_CLASSES] = {0};
+    int64_t launches[SPCFG_PROF_CLASSES] = {0};
+  };
+  Sums all, shared;  // (ms: filled when the events are read)
+  Sums last_shared;  // of the last spcfg_profile_read
   hipEvent_t get() {
     if (!pool.empty()) { hipEvent_t e = pool.back(); pool.pop_back(); return e; }
     hipEvent_t e = nullptr;
@@ -296,8 +300,11 @@ struct Scope {
     t_cur_cls = c;
     t_cur_also = also;
     std::lock_guard<std::mutex> lock(g_prof.mu);
-    g_prof.work[c] += work;
-    if (also >= 0) g_prof.work[also] += also_work;
+    g_prof.all.work[c] += work;
+    if (also < 0) return;
+    g_prof.all.work[also] += also_work;
+    g_prof.shared.work[c] += work;
+    g_prof.shared.work[also] += also_work;
   }
   ~Scope() { t_cur_cls = prev; t_cur_also = prev_also; }
 };
@@ -310,8 +317,12 @@ LaunchEvents prof_launch_events() {
   LaunchEvents ev;
   if (!g_prof.on || t_cur_cls < 0) return ev;
   std::lock_guard<std::mutex> lock(g_prof.mu);
-  ++g_prof.launches[t_cur_cls];
-  if (t_cur_also >= 0) ++g_prof.launches[t_cur_also];
+  ++g_prof.all.launches[t_cur_cls];
+  if (t_cur_also >= 0) {
+    ++g_prof.all.launches[t_cur_also];
+    ++g_prof.shared.launches[t_cur_cls];
+    ++g_prof.shared.launches[t_cur_also];
+  }
   ev.start = g_prof.get();
   ev.stop = g_prof.get();
   if (!ev.start || !ev.stop) {
@@ -882,7 +893,7 @@ int spcfg_profile_enable(int on) {
   g_prof.on = on != 0;
   if (g_prof.on) {
     g_prof.recycle();
-    for (int c = 0; c < SPCFG_PROF_CLASSES; ++c) { g_prof.work[c] = 0; g_prof.launches[c] = 0; }
+    g_prof.all = g_prof.shared = Prof::Sums{};
   }
   return SPCFG_OK;
 }
@@ -890,22 +901,33 @@ int spcfg_profile_enable(int on) {
 int spcfg_profile_read(double* ms, int64_t* launches, double* work) {
   if (!ms || !launches || !work) return SPCFG_ERR_ARG;
   std::lock_guard<std::mutex> lock(g_prof.mu);
-  for (int c = 0; c < SPCFG_PROF_CLASSES; ++c) ms[c] = 0.0;
   int rc = SPCFG_OK;
   for (auto& r : g_prof.recs) {
     float t = 0.0f;
     if (hipEventSynchronize(r.b) != hipSuccess || hipEventElapsedTime(&t, r.a, r.b) != hipSuccess) rc = SPCFG_ERR_HIP;
-    ms[r.cls] += r.also >= 0 ? 0.5 * t : t;
-    if (r.also >= 0) ms[r.also] += 0.5 * t;
+    if (r.also < 0) { g_prof.all.ms[r.cls] += t; continue; }
+    for (int c : {r.cls, r.also}) { g_prof.all.ms[c] += 0.5 * t; g_prof.shared.ms[c] += 0.5 * t; }
   }
   g_prof.recycle();
   for (int c = 0; c < SPCFG_PROF_CLASSES; ++c) {
-    launches[c] = g_prof.launches[c];
-    work[c] = g_prof.work[c];
-    g_prof.launches[c] = 0;
-    g_prof.work[c] = 0;
+    ms[c] = g_prof.all.ms[c];
+    launches[c] = g_prof.all.launches[c];
+    work[c] = g_prof.all.work[c];
   }
+  g_prof.last_shared = g_prof.shared;
+  g_prof.all = g_prof.shared = Prof::Sums{};
   return rc;
+}
+
+int spcfg_profile_read_shared(double* ms, int64_t* launches, double* work) {
+  if (!ms || !launches || !work) return SPCFG_ERR_ARG;
+  std::lock_guard<std::mutex> lock(g_prof.mu);
+  for (int c = 0; c < SPCFG_PROF_CLASSES; ++c) {
+    ms[c] = g_prof.last_shared.ms[c];
+    launches[c] = g_prof.last_shared.launches[c];
+    work[c] = g_prof.last_shared.work[c];
+  }
+  return SPCFG_OK;
 }
 
 const char* spcfg_profile_class_name(int cls) {

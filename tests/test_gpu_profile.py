@@ -63,3 +63,25 @@ def test_launches_and_bytes_of_the_split_sums(N, P, lens, n_max):
     f, r = rows_moved(N, lens, n_max)
     assert prof["split_fwd"]["work"] == 4 * N * f
     assert prof["split_bwd"]["work"] == 4 * N * r
+
+
+@pytest.mark.parametrize("N,P,lens,all_shared", [(30, 10, [9, 4], True), (1024, 600, [9, 4], False)])
+def test_shared_launches_are_kept_apart(N, P, lens, all_shared):
+    d = synth.make_inputs("tiny", seed=4700 + N, N=N, P=P, B=len(lens), lengths=lens, V=50)
+    print("case shared launches", N, len(lens), flush=True)
+    wl = bd.Workload(d)
+    wl.forward_backward()
+    torch.cuda.synchronize()
+    bd.spcfg_profile_enable(True)
+    wl.forward_backward()
+    torch.cuda.synchronize()
+    prof, shared = bd.spcfg_profile_read(), bd.spcfg_profile_read_shared()
+    for product, sums in (("gemm_fwd", "split_fwd"), ("gemm_bwd", "split_bwd")):
+        assert shared[product]["launches"] == shared[sums]["launches"] and shared[product]["ms"] == shared[sums]["ms"]
+        # a small grammar's sums all come with a product, but the reverse pass's first; a large one's none
+        assert prof[sums]["launches"] - shared[sums]["launches"] == ((sums == "split_bwd") if all_shared else prof[sums]["launches"])
+        for c in (product, sums):
+            for key in ("ms", "work"):
+                assert (shared[c][key] > 0) == all_shared and shared[c][key] <= prof[c][key]
+    assert all(not any(shared[c].values()) for c in ("setup", "root", "gemm_grad"))
+    bd.spcfg_profile_enable(False)
