@@ -580,7 +580,8 @@ int forward(const spcfg_config* cfg, const Plan& plan, const Layout& ly, const P
   const int fp32_mfma = (cfg->flags & SPCFG_FLAG_FP32_MFMA) ? 1 : 0;
   NtArgs leaf = forward_product(plan, ly, p, fp32_mfma, 1, nullptr);
   {
-    Scope s(SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * 3 + 8.0 * ly.S1 * ly.P);
+    // (L and R read, the panels of the passes to come written)
+    Scope s(SPCFG_PROF_SETUP, 4.0 * 2 * (double)ly.N * (ly.N + ly.P) * (with_backward ? 3 : 2) + 8.0 * ly.S1 * ly.P);
     launch_plan(ly, p, plan.lens, st);
     if (ly.G > 1) launch_plan_sentrows(ly, p, st);
     launch_pack_weights(ly, panels_read(plan, ly, p, fp32_mfma, true, with_backward), L, R, st);

@@ -85,3 +85,23 @@ def test_shared_launches_are_kept_apart(N, P, lens, all_shared):
                 assert (shared[c][key] > 0) == all_shared and shared[c][key] <= prof[c][key]
     assert all(not any(shared[c].values()) for c in ("setup", "root", "gemm_grad"))
     bd.spcfg_profile_enable(False)
+
+
+def test_bytes_of_the_set_up():
+    N, P = 30, 10
+    d = synth.make_inputs("tiny", seed=4800, N=N, P=P, B=2, lengths=[9, 4], V=50)
+    print("case set-up bytes", flush=True)
+    wl = bd.Workload(d)
+    bd.spcfg_profile_enable(True)
+    # scoring: L and R read, the forward panels written; the reverse pass writes its own
+    tokens = int(np.sum(d["lengths"]))
+    wl.forward()
+    torch.cuda.synchronize()
+    assert bd.spcfg_profile_read()["setup"]["work"] == 4 * 2 * N * (N + P) * 2 + 8 * tokens * P
+    wl.backward()
+    torch.cuda.synchronize()
+    assert bd.spcfg_profile_read()["setup"]["work"] == 4 * 2 * N * (N + P) * 2
+    wl.forward_backward()
+    torch.cuda.synchronize()
+    assert bd.spcfg_profile_read()["setup"]["work"] == 4 * 2 * N * (N + P) * 3 + 8 * tokens * P
+    bd.spcfg_profile_enable(False)
