@@ -49,30 +49,6 @@ template <int BM, int NPL_, int BNW, int NW> struct Geo3 {
   static constexpr size_t kLds = (size_t)NS * STAGE;
 };
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
-__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) unsigned char lds_u8;
-  __builtin_amdgcn_global_load_lds(gptr, (lds_u8*)(uintptr_t)lds_addr, 16, 0, 0);
-#else
-  (void)gptr; (void)lds_addr;
-#endif
-}
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) unsigned char lds_u8;
-  return (unsigned)(uintptr_t)(lds_u8*)p;
-#else
-  (void)p; return 0;
-#endif
-}
 __device__ __forceinline__ int swz(int row) { return (row >> 2) & 3; }
 
 // Makes every register of F[NPL][NF] an in/out operand of an empty statement: instructions that use them stay behind it.

@@ -8,6 +8,8 @@
 // whichever workgroup arrives last sums the slots in fixed order (so the result does not depend on the
 // arrival order) and runs the epilogue.  Nobody waits on anybody: there is no spinning.
 #pragma once
+#include <type_traits>
+
 #include "spcfg_internal.h"
 
 namespace spcfg {
@@ -15,6 +17,33 @@ namespace nt {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+template <int I, int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+// 16 bytes a lane from global memory straight to LDS (1 KB a wavefront instruction, lane l at + 16 l)
+__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef __attribute__((address_space(3))) unsigned char lds_u8;
+  __builtin_amdgcn_global_load_lds(gptr, (lds_u8*)(uintptr_t)lds_addr, 16, 0, 0);
+#else
+  (void)gptr; (void)lds_addr;
+#endif
+}
+__device__ __forceinline__ unsigned lds_address(const void* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef const __attribute__((address_space(3))) unsigned char lds_u8;
+  return (unsigned)(uintptr_t)(lds_u8*)p;
+#else
+  (void)p;
+  return 0;
+#endif
+}
 
 // Partial tiles travel between workgroups (possibly on different XCDs, whose L2 caches are not coherent
 // with each other) as relaxed agent-scope atomic 8-byte accesses: stores write through, loads read the

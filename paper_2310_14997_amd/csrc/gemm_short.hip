@@ -26,24 +26,6 @@ namespace {
 
 using namespace nt;
 
-__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) unsigned char lds_u8;
-  __builtin_amdgcn_global_load_lds(gptr, (lds_u8*)(uintptr_t)lds_addr, 16, 0, 0);
-#else
-  (void)gptr; (void)lds_addr;
-#endif
-}
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef const __attribute__((address_space(3))) unsigned char lds_u8;
-  return (unsigned)(uintptr_t)(lds_u8*)p;
-#else
-  (void)p;
-  return 0;
-#endif
-}
-
 // Both 16-byte chunks that this lane contributes to a 16-row operand of one 32-wide K-step (issued only: see wait_lds).
 struct Raw { floatx4 u, v; };
 // NF operands (16 rows = 2048 bytes apart) read and waited for in one block

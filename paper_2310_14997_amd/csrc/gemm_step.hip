@@ -72,13 +72,6 @@ __device__ __forceinline__ int quad_max(int v) {
   v = max(v, __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, true));  // quad_perm [1, 0, 3, 2]
   return max(v, __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, true));  // quad_perm [2, 3, 0, 1]
 }
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
 __device__ __forceinline__ float exp_coef(int d, int m) { return d == kExpZero ? 0.0f : pow2i(d - m); }
 
 // The product of one wavefront: MI x NI tiles of 16 x 16 over its K-steps wave, wave + kProdWaves, ... of 32 values; partial

@@ -52,31 +52,6 @@ template <int PLANES> struct GeoT {
   static constexpr int opnd_of(int t) { return t * NW % (8 * (1 + BH)) / 8; }
 };
 
-template <int I, int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
-}
-
-__device__ __forceinline__ void dma16(const void* gptr, unsigned lds_addr) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) unsigned char lds_u8;
-  __builtin_amdgcn_global_load_lds(gptr, (lds_u8*)(uintptr_t)lds_addr, 16, 0, 0);
-#else
-  (void)gptr; (void)lds_addr;
-#endif
-}
-__device__ __forceinline__ unsigned lds_address(const void* p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  typedef __attribute__((address_space(3))) unsigned char lds_u8;
-  return (unsigned)(uintptr_t)(lds_u8*)p;
-#else
-  (void)p; return 0;
-#endif
-}
-
 // One operand fragment of one plane: eight reduction rows of a column per lane, as two 64-bit halves.
 struct Frag { uintx2 lo, hi; };
 __device__ __forceinline__ bf16x8 operand(const Frag& f) {
