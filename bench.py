@@ -152,7 +152,7 @@ def measure(d, bf16, fp32_mfma, steps, warmup, profile_steps, graph=False, extra
     peak = PEAK_BF16_MFMA_TFLOPS if bf16 else (PEAK_FP32_MFMA_TFLOPS if fp32_mfma else PEAK_SPLIT_TFLOPS)
     if bf16:
         kernel_name, mfma = ("k_gemm_nt3 (forward: operands as two bf16 pieces, 3 bf16 MFMA products, not counted in "
-                             "the flop) / k_gemm_nt16 (reverse: single bf16 operands", "bf16")
+                             "the flop) / k_gemm_nt3, k_gemm_nt16 (reverse: single bf16 operands", "bf16")
     elif fp32_mfma:
         kernel_name, mfma = "k_gemm_nt (fp32 MFMA", "f32"
     else:

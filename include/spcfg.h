@@ -65,7 +65,7 @@ enum {
      from operands cut into two bf16 pieces (hi + lo, three piece products, operands good to 2^-17), so that log Z
      stays within about 1e-3 of exact arithmetic whatever the grammar and the sentence length.  This flag rounds those
      operands to a single bf16 instead, as the reverse and rule-gradient products always do: a third of the matrix
-     work in the forward products (the Scaled configuration takes 18 % less time), but roundings of 2^-9 per projection
+     work in the forward products (the Scaled configuration takes 23 % less time), but roundings of 2^-9 per projection
      then add up along a tree: measured up to 0.07 absolute in log Z on small peaked grammars with sentences of
      60-100 words, 0.6e-3 to 1.5e-3 on large unpeaked ones at n = 40.  With one grammar per sentence the flag replaces
      the fp32 operands of the forward products by single bf16 ones.  No effect with SPCFG_PRECISION_FP32. */
@@ -113,7 +113,8 @@ int spcfg_inside(const spcfg_config* cfg, const float* log_root, const float* L,
 
 /*
  * Reverse pass (Sec. 3.2 "Recomputation"; chain rule through the stacked projection): gradients of
- * sum_b grad_logZ[b] * logZ[b].  Must follow spcfg_inside on the same inputs, workspace and stream order.
+ * sum_b grad_logZ[b] * logZ[b].  Must follow spcfg_inside on the same inputs, workspace and stream order; L and R are
+ * read again here.
  *   grad_logZ      dev [B] or NULL (= all ones)
  *   grad_L, grad_R dev [N x M]  d/dL[A,B], d/dR[A,C] in probability space, summed over the batch;
  *                               L*grad_L and R*grad_R are expected rule counts

@@ -135,7 +135,8 @@ struct BwdPartExp {
     else rootmask[r] = e;
   }
 };
-// (through the launches' own pointers: a uniform load, which goes through the scalar cache)
+// (through the launches' own pointers: where the row is the same for a wavefront, as in the kernels of one width, a uniform load that
+// goes through the scalar cache)
 __device__ __forceinline__ int2 bwd_part_exp(int w, int64_t r, int64_t S1, int Np, const float* __restrict__ BH,
                                              const float* __restrict__ xs, const int32_t* __restrict__ rootmask) {
   if (w == 1) return make_int2(__float_as_int(xs[r]), rootmask[r]);

@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_gemm_nt3(NtArgs g, int ipw, int 
   const unsigned a_frag1 = lds0 + (a_rel ^ 32u), b_frag1 = lds0 + (b_rel ^ 32u);
   // one plane: the step's second tile along K flips bit 6
   const unsigned a_next = (a_rel & 64u) ? -64u : 64u, b_next = (b_rel & 64u) ? -64u : 64u;
-  // this wavefront's load instructions: entry e = uw + 4 j of the stage's list (A planes first, then Bm planes)
+  // this wavefront's load instructions: entry e = uw + NW j of the stage's list (A planes first, then Bm planes)
   int e_isA[ND], e_plane[ND], e_rg[ND];
   unsigned e_lds[ND];
 #pragma unroll

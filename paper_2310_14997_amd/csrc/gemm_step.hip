@@ -14,11 +14,12 @@
 //    its wavefronts need no word from each other before the one barrier.
 //  * Everything that does not depend on the product is asked for before it: two dependent lookups (length and row tables,
 //    then rows and exponents) lie before the first matrix instruction and before the first sum alike.
-// A launch takes 6 us at N = 64 to 141 (product and sums apart 3.5 + 4.5 us and a launch more), 8 us at N = 512 (9 us).  Whole calls,
+// A forward launch takes 6 us at N = 64 to 141 (product and sums apart 3.5 + 4.5 us and a launch more), 8 us at N = 512 (9 us), a
+// reverse one 7.6 us at N = 141.  Whole calls,
 // separate -> one launch a width, sentences of 30 words: scoring N = 64, B = 32 269 -> 199 us; N = 141, B = 1 238 -> 181; N = 256,
 // B = 4 260 -> 206; a training step 647 -> 499, 524 -> 438 and 553 -> 488 us.  A second round of workgroups costs more than
 // the launch that it saves (N = 141, B = 24: 284 -> 383 us if all widths went this way), long rows of K leave the form behind
-// the separate product's finer tiles (N = 1024, B = 1: 299 -> 316 us): see step_shape in spcfg_api.hip.
+// the separate product's finer tiles (N = 1024, B = 1: 299 -> 316 us): see step_form in spcfg_api.hip.
 #include <type_traits>
 
 #include "chart_device.h"

@@ -334,7 +334,8 @@ k_leaf_prep(const float* __restrict__ log_emit, int P, int Pp, int n_max, const 
 // order.  blockIdx.x is the block of nonterminals.  A tile shares three of its seven Y rows with its neighbour in blockIdx.y;
 // both run on the same XCD, and find them in one L2, only where the grid is a multiple of eight wide (Np a multiple of 2048,
 // in the shared form of 512); elsewhere those rows are read from the Infinity Cache or HBM by several XCDs.
-// Bound by reading rows (6-8 TB/s of rows asked for at the large launches).  Split-point sums of a whole pass before and
+// Bound by reading rows: asked for are 6.4 TB/s in reverse and 5.9 forward at B = 32, N = 4096, n = 40, 4.4 in reverse at B = 4, N = 1024,
+// n = 137 .. 188.  Split-point sums of a whole pass before and
 // after: B = 4, N = 1024, n <= 200: reverse 10.1 -> 6.2 ms, forward 5.6 -> 4.0 ms; B = 32, N = 4096, n = 40: 4.2 -> 2.7 and
 // 2.7 -> 1.8 ms.  kBandShare wavefronts per 64 nonterminals: at n = 200 the launches of the last widths fall from 62 us (four
 // wavefronts) to 25 us; above kBandMinWaves wavefronts in all a wavefront per 64 nonterminals is the faster form, because the

@@ -55,10 +55,10 @@ inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 struct Layout {
   int N, P, Np, Pp, B, n_max;
   int G;                 // number of grammars: 1 (shared by the batch) or B (one per sentence)
-  int bf16;              // projections with bf16 operands: packed weights are bf16, transposed bf16 copies for the rule gradients
+  int bf16;              // products with bf16 operands: packed weights are bf16
   int planes;            // bf16 planes that producers write beside every fp32 chart row for the forward projection products:
-                         // 0 none (fp32 operands are staged and cut in the kernel), 1 the bf16 rounding (bf16 mode, one
-                         // grammar per sentence), 2 hi + lo (bf16 mode, shared grammar), 3 the exact cut hi + mid + lo
+                         // 0 none (fp32 operands are staged and cut in the kernel), 1 the bf16 rounding (bf16 mode with single
+                         // operands), 2 hi + lo (bf16 mode, shared grammar), 3 the exact cut hi + mid + lo
                          // of every fp32 value (fp32 mode, shared grammar)
   int planes_bwd;        // the same for the adjoint rows of the reverse products: 0, 1 (bf16 mode) or 3
   int tn3;               // planes of the rule-gradient product's operands (shared grammar): Tg3 / Eg3 below, padded UVb; 0: k_gemm_tn
@@ -207,7 +207,7 @@ struct NtArgs {
   const int32_t* grp_lens; const int32_t* grp_rowbase; int64_t grp_row_first; int64_t grp_b_stride;
   int grp_tiles_m[3];  // host: number of row tiles for tile heights 32, 64, 128
   int grp_max_rows;    // host: largest row count of one sentence
-  // Parts mode (fp32, shared grammar, width >= 2): `parts` products in one launch.  Part p multiplies the rows
+  // Parts mode (shared grammar, width >= 2): `parts` products in one launch.  Part p multiplies the rows
   // [prt_row0[p], + prt_rows[p]) with the columns [prt_c0[p], + cols) of Bm / C over the K-steps
   // [prt_kbeg[p], + prt_kt[p]) (steps of 32 values).  The span plan puts the prefix spans first and the suffix
   // spans last within a width, so "rows whose eta is used", "rows whose zeta is used" (forward: two parts, one
