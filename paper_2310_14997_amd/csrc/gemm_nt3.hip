@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(64 * NW, 1) k_gemm_nt3(NtArgs g, int ipw, int 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();  // every load has landed and every operand is in registers before the ring is reused
 
-    finish_tile<BM, BNW, NW, NW == 4 ? 2 : 1>(g.partial, g.counters, acc, tile, ustart, k0, k1, KTt, ipw, wg, it, wg_begin, tid, &s_last,
+    finish_tile<BM, BNW, NW, NW == 4 ? 2 : 1, G::MI * G::NI == 1 && !Q::SINGLE>(g.partial, g.counters, acc, tile, ustart, k0, k1, KTt, ipw, wg, it, wg_begin, tid, &s_last,
                     [&](floatx16(&t)[MI][NI]) { epilogue<EPI, BM, BNW, NW>(g, t, row0, col0, wm, wn, lane, row_end, c_shift); });
     it += k1 - k0;
   }

@@ -225,8 +225,9 @@ __device__ __forceinline__ int find_group(const NtArgs& g, const int* s_tile0, c
 
 // After the K loop of one tile segment [k0, k1): run the epilogue if the segment is the whole tile, else
 // publish the partial tile, count the arrival, and let the last arriver reduce in fixed order (of more than two
-// parts kWhole at a time, as registers allow, or four of the shorter tiles).
-template <int BM, int BNW = BN, int NW = 4, int kWhole = 1, typename Epi>
+// parts kWhole at a time, as registers allow, or four of the shorter tiles; kFull: full rounds without branches).
+template <int BM, int BNW = BN, int NW = 4, int kWhole = 1, bool kFull = Geo<BM, BNW, NW>::MI * Geo<BM, BNW, NW>::NI == 1,
+          typename Epi>
 __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
                                             floatx16 (&acc)[Geo<BM, BNW, NW>::MI][Geo<BM, BNW, NW>::NI],
                                             int tile, int ustart, int k0, int k1, int KT, int ipw, int wg, int it,
@@ -263,7 +264,8 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
       // Tiles of 32 rows, of which a short launch cuts up to 32 parts, have full rounds without branches (N = 512, fp32 matrix instructions,
       // one sentence of 30 words: a training step 1008 us with a branch around every part's loads, 980 so; N = 1024 on two planes, 60
       // words scored: 1210, 1180), and a last round that asks only for the parts that there are (three parts at N = 320: scoring
-      // 612 us with repeated loads in their place, 583 so).  Taller ones have few parts and lose by it (N = 3000, 8 sentences: 940, 953).
+      // 612 us with repeated loads in their place, 583 so).  Taller ones have few parts and lose by the longer code (N = 3000, 8 sentences: 940,
+      // 953), and so do 32-row tiles on one plane, whose short launches are gemm_nt16.hip's (one sentence: 662, 670).
       const int odd0 = (ustart != first_g * ipw) ? 1 : 0;
       const int own = wg - first_g;
       auto fetch = [&](int p, F2 (&x)[G::MI][G::NI][8]) {
@@ -298,7 +300,7 @@ __device__ __forceinline__ void finish_tile(float* partial, int32_t* counters,
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.0f;
         int p0 = 0;
-        if constexpr (G::MI * G::NI == 1) {
+        if constexpr (kFull) {
           for (; p0 + kParts <= parts; p0 += kParts) {
             F2 x[kParts][G::MI][G::NI][8];
 #pragma unroll
