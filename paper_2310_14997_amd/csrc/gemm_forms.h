@@ -35,7 +35,8 @@ inline Units units_of(const NtArgs& a, int bm, int bn, int ks) {
 // parts.
 //  * Planes kernel (gemm_nt3.hip), per K-step of a workgroup: b + c * (share of the chip that is busy), since operands come from L2
 //    and past it; `fixed` for the first stages of the ring and the epilogue.  Shares pay an exchange (`cut`) on top, unless they are tiles;
-//    whole tiles their last, partly filled round.  More than one round of 64-row tiles reads the panel over and over: kShortRounds times as long a step.
+//    whole tiles their last, partly filled round.  More than one round of 64-row tiles reads the panel over and over, kShortRounds times as
+//    long a step (N = 3072, 768 rows: 61.6 us, 50 by the steps of a single round).
 //  * Register-staged kernel, with tiles of 32 rows only (its taller ones, 25 to 31 us for 112 to 480 rows at N = 3520, were never the
 //    fastest): the same with two workgroups a CU, and kNextTile where a share goes on to another tile.
 // Fitted to 684 launches on one and 323 on two planes (N = 64 .. 4096, 1 to 64 sentences, 6 to 2000 rows, both directions), every form

@@ -27,6 +27,7 @@ def blocks_off(got, ref):
     (576, 100, [8] * 240),        # one product and parts, both whole: no whole number of 128-column blocks
     (1088, 130, [6, 5, 7] * 12),  # whole tiles next to staged ones
     (1300, 70, [7] * 100),        # tiles of 32 rows in shares next to whole ones of 64
+    (2048, 2048, [8] * 12),       # rule gradients whose tiles run in blocks of 8 x 8
     (2112, 2112, [20] * 14),      # rule gradients in 297 tiles, equal shares that go on from tile to tile
     (2112, 2112, [3] * 8),        # the same, a reduction of one step: whole tiles
     (2200, 300, [9] * 24),        # 315 tiles, and 70 for the preterminals, whose last ones have 44 columns
